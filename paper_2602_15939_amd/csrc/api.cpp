@@ -648,8 +648,8 @@ int32_t maxwell_box(pic_box* b)
     const double tn = time_of(b, b->step), th = tn + 0.5 * dt, t1 = tn + dt;
     hipStream_t st = b->st;
     if (sheared(&b->d)) {
-        // implicit midpoint by fixed-point sweeps from F^0 = F^n (with its own guards, at
-        // t^n); every later iterate has its x images at t^{n+1}.  Three field sets: F^n (free
+        // implicit midpoint by fixed-point sweeps from F^0 = F^n (its x images at t^n); every
+        // later iterate has its x images at t^{n+1}.  Three field sets: F^n (free
         // once the first sweep has read it), C, and the iterates alternating with F^n's set.
         const int K = b->d.maxwell_iters > 0 ? b->d.maxwell_iters : 8;
         const int sn = b->cur_set, sc = (sn + 1) % 3, sb2 = (sn + 2) % 3;
@@ -668,9 +668,7 @@ int32_t maxwell_box(pic_box* b)
                 dfac[c] = f.dfac[c];
             }
             kz = f.kz;
-            if (scale_fields(b->G, b->set[sn], f.fwd, st) != hipSuccess ||
-                fill_guards(b->G, b->set[sn], 6, 1, dys0, st) != hipSuccess)
-                return PIC_EDEVICE;
+            if (scale_fields(b->G, b->set[sn], f.fwd, st) != hipSuccess) return PIC_EDEVICE;
         }
         const bool staged = ksb_staged(b->G) && !comb;
         if (tol && zero_floats(reinterpret_cast<float*>(b->conv), 2 * K, st) != hipSuccess)
@@ -716,16 +714,13 @@ int32_t maxwell_box(pic_box* b)
             }
             if (tol && k == K - 1 && ksb_finalize(ksb_fin(b, K, so), st) != hipSuccess)
                 return PIC_EDEVICE;
-            // the staged 3D sweep reads its whole halo at the (shearing-)periodic images: then
-            // only the last iterate's guards are filled (for the push)
-            if ((!staged || k == K - 1) && fill_guards(b->G, b->set[so], 6, 1, dys1, st) != hipSuccess)
-                return PIC_EDEVICE;
             sk = so;
             so = so == sb2 ? sn : sb2;
         }
-        if (comb && (scale_fields(b->G, b->set[sk], back, st) != hipSuccess ||
-                     fill_guards(b->G, b->set[sk], 6, 1, dys1, st) != hipSuccess))
-            return PIC_EDEVICE;
+        // the sweeps read the cells beyond the faces at their images: only the guards of the
+        // fields handed on are filled, for the push
+        if (comb && scale_fields(b->G, b->set[sk], back, st) != hipSuccess) return PIC_EDEVICE;
+        if (fill_guards(b->G, b->set[sk], 6, 1, dys1, st) != hipSuccess) return PIC_EDEVICE;
         b->cur_set = sk;
         b->last_sweeps = tol ? -1 : K;
         return PIC_OK;
@@ -746,8 +741,6 @@ int32_t maxwell_box(pic_box* b)
         M.J[c] = b->J[c];
     }
     M.dt = (float)dt;
-    float* Bp[3] = {b->B(0), b->B(1), b->B(2)};
-    float* Ep[3] = {b->E(0), b->E(1), b->E(2)};
     // B'^{n+1/2} = B'^n - dt/2 curl(L^n E^n), B^{n+1/2} = (l/ell)^{n+1/2} B'
     for (int c = 0; c < 3; c++) {
         M.fin[c] = (float)(elln / ln[c]);
@@ -755,7 +748,6 @@ int32_t maxwell_box(pic_box* b)
         M.gf[c] = (float)ln[c];
     }
     if (yee_b(M, st) != hipSuccess) return PIC_EDEVICE;
-    if (fill_guards(b->G, Bp, 3, 0, 0.0, st) != hipSuccess) return PIC_EDEVICE;
     // E'^{n+1} = E'^n + dt curl(L^{n+1/2} B^{n+1/2}) - 4 pi dt (l J'), E^{n+1} = (l/ell)^{n+1} E'
     for (int c = 0; c < 3; c++) {
         M.fin[c] = (float)(elln / ln[c]);
@@ -763,16 +755,13 @@ int32_t maxwell_box(pic_box* b)
         M.gf[c] = (float)lh[c];
     }
     if (yee_e(M, st) != hipSuccess) return PIC_EDEVICE;
-    if (fill_guards(b->G, Ep, 3, 0, 0.0, st) != hipSuccess) return PIC_EDEVICE;
     // B'^{n+1} = B'^{n+1/2} - dt/2 curl(L^{n+1} E^{n+1}), B^{n+1} = (l/ell)^{n+1} B'
     for (int c = 0; c < 3; c++) {
         M.fin[c] = (float)(ellh / lh[c]);
         M.fout[c] = (float)(l1[c] / ell1);
         M.gf[c] = (float)l1[c];
     }
-    if (yee_b(M, st) != hipSuccess) return PIC_EDEVICE;
-    if (fill_guards(b->G, Bp, 3, 0, 0.0, st) != hipSuccess) return PIC_EDEVICE;
-    return PIC_OK;
+    return hip_fail(yee_b(M, st));
 }
 
 // ---------------------------------------------------------------- batched step
@@ -858,24 +847,12 @@ struct BatchPlan {
     }
 };
 
-// guard fill of ncomp arrays as batched units (one per slab kind)
+// guard fill of ncomp arrays as a batched unit
 void plan_fill(std::vector<FillArgs>& a, std::vector<uint32_t>& blk, const GridDev& G,
                float* const* comps, int ncomp, int shear, double dys)
 {
-    Comp6 A{};
-    for (int c = 0; c < ncomp; c++) A.p[c] = comps[c];
-    const double fl = std::floor(dys);
-    const int di = (int)fl;
-    const float w = (float)(dys - fl);
-    const int NYg = G.n[1] + 2 * G.g[1], NZg = G.n[2] + 2 * G.g[2];
-    a.push_back(FillArgs{G, A, 0, shear, di, w});
-    blk.push_back(grid_blocks((int64_t)2 * G.g[0] * NYg * NZg));
-    a.push_back(FillArgs{G, A, 1, shear, di, w});
-    blk.push_back(grid_blocks((int64_t)G.n[0] * 2 * G.g[1] * NZg));
-    if (G.g[2] > 0) {
-        a.push_back(FillArgs{G, A, 2, shear, di, w});
-        blk.push_back(grid_blocks((int64_t)G.n[0] * G.n[1] * 2 * G.g[2]));
-    }
+    a.push_back(fill_args(G, comps, ncomp, shear, dys));
+    blk.push_back(fill_blocks(a.back()));
 }
 
 // The host-side state a batched step advances, per box: saved before planning so that a step
@@ -1107,8 +1084,8 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
     {
         std::vector<MaxwellDev> yb1, ye, yb2;
         std::vector<uint32_t> yb1b, yeb, yb2b;
-        std::vector<FillArgs> fb1, fe, fb2, fend;
-        std::vector<uint32_t> fb1b, feb, fb2b, fendb;
+        std::vector<FillArgs> fend;  // guards of every box's fields at t^{n+1}
+        std::vector<uint32_t> fendb;
         int kmax = 0;
         for (int i = 0; i < nb; i++) {
             pic_box* b = boxes[i];
@@ -1134,8 +1111,6 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             }
             M.dt = (float)dt;
             const uint32_t nbk = grid_blocks((int64_t)b->n[0] * b->n[1] * b->n[2]);
-            float* Bp[3] = {b->B(0), b->B(1), b->B(2)};
-            float* Ep[3] = {b->E(0), b->E(1), b->E(2)};
             for (int c = 0; c < 3; c++) {
                 M.fin[c] = (float)(elln / ln[c]);
                 M.fout[c] = (float)(lh[c] / ellh);
@@ -1143,7 +1118,6 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             }
             yb1.push_back(M);
             yb1b.push_back(nbk);
-            plan_fill(fb1, fb1b, b->G, Bp, 3, 0, 0.0);
             for (int c = 0; c < 3; c++) {
                 M.fin[c] = (float)(elln / ln[c]);
                 M.fout[c] = (float)(l1[c] / ell1);
@@ -1151,7 +1125,6 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             }
             ye.push_back(M);
             yeb.push_back(nbk);
-            plan_fill(fe, feb, b->G, Ep, 3, 0, 0.0);
             for (int c = 0; c < 3; c++) {
                 M.fin[c] = (float)(ellh / lh[c]);
                 M.fout[c] = (float)(l1[c] / ell1);
@@ -1159,14 +1132,10 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             }
             yb2.push_back(M);
             yb2b.push_back(nbk);
-            plan_fill(fb2, fb2b, b->G, Bp, 3, 0, 0.0);
         }
         plan.grid(kBatchYeeB, yb1, yb1b, 1);
-        plan.grid(kBatchFill, fb1, fb1b, 3);
         plan.grid(kBatchYeeE, ye, yeb, 1);
-        plan.grid(kBatchFill, fe, feb, 3);
         plan.grid(kBatchYeeB, yb2, yb2b, 1);
-        plan.grid(kBatchFill, fb2, fb2b, 3);
         // shearing boxes: sweep k of every box with at least k+1 sweeps in one launch
         struct Rot {
             int sn, sc, sb2, sk, so;
@@ -1177,13 +1146,11 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             const int sn = b->cur_set;
             rot[i] = Rot{sn, (sn + 1) % 3, (sn + 2) % 3, sn, (sn + 2) % 3};
         }
-        // combined-frame boxes: F^n to the expanding-frame fields at t^n, guards at t^n
+        // combined-frame boxes: F^n to the expanding-frame fields at t^n
         std::vector<CombFactors> cf(nb);
         {
             std::vector<ScaleArgs> sa;
             std::vector<uint32_t> sab;
-            std::vector<FillArgs> sf;
-            std::vector<uint32_t> sfb;
             for (int i = 0; i < nb; i++) {
                 pic_box* b = boxes[i];
                 if (b->d.frame != PIC_FRAME_SHEAR_EXPAND) continue;
@@ -1194,10 +1161,8 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
                 for (int c = 0; c < 3; c++) a.f[c] = cf[i].fwd[c];
                 sa.push_back(a);
                 sab.push_back(grid_blocks((int64_t)b->n[0] * b->n[1] * b->n[2]));
-                plan_fill(sf, sfb, b->G, b->set[rot[i].sn], 6, 1, shear_offset(b, time_of(b, b->step)));
             }
             plan.grid(kBatchScale, sa, sab, 1);
-            plan.grid(kBatchFill, sf, sfb, 6);
         }
         // tolerance-mode boxes: clear their convergence records first
         {
@@ -1215,8 +1180,6 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
         for (int k = 0; k < kmax; k++) {
             std::vector<KsbDev> ks;
             std::vector<uint32_t> ksb;
-            std::vector<FillArgs> kf;
-            std::vector<uint32_t> kfb;
             std::vector<KsbFin> kz;
             std::vector<uint32_t> kzb;
             for (int i = 0; i < nb; i++) {
@@ -1237,6 +1200,12 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
                 Kd.dt = (float)b->d.dt;
                 Kd.sO = (float)(b->d.shear_s * b->d.shear_omega0);
                 Kd.half_nx = 0.5f * (float)b->n[0];
+                {  // x images of F^n at t^n, of the later iterates at t^{n+1}
+                    const double tn = time_of(b, b->step);
+                    const double dys = shear_offset(b, k == 0 ? tn : tn + b->d.dt), fl = std::floor(dys);
+                    Kd.ydys_int = (int)fl;
+                    Kd.ydys_w = (float)(dys - fl);
+                }
                 if (tol) {
                     Kd.conv = b->conv;
                     Kd.tol = (float)b->d.maxwell_tol;
@@ -1256,8 +1225,6 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
                     kz.push_back(ksb_fin(b, K, r.so));
                     kzb.push_back(kKsbFinBlocks);
                 }
-                const double t1 = time_of(b, b->step) + b->d.dt;
-                plan_fill(kf, kfb, b->G, b->set[r.so], 6, 1, shear_offset(b, t1));
                 r.sk = r.so;
                 r.so = r.so == r.sb2 ? r.sn : r.sb2;
                 if (k == K - 1) {
@@ -1267,7 +1234,6 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             }
             plan.grid(k == 0 ? kBatchKsbFirst : kBatchKsbNext, ks, ksb, 1);
             plan.grid(kBatchKsbFinal, kz, kzb, 1);
-            plan.grid(kBatchFill, kf, kfb, 6);
         }
         // combined-frame boxes: the last iterate back to the frame's fields at t^{n+1}
         {
@@ -1282,16 +1248,15 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
                 for (int c = 0; c < 3; c++) a.f[c] = cf[i].back[c];
                 sa.push_back(a);
                 sab.push_back(grid_blocks((int64_t)b->n[0] * b->n[1] * b->n[2]));
-                plan_fill(fend, fendb, b->G, b->set[b->cur_set], 6, 1,
-                          shear_offset(b, time_of(b, b->step) + b->d.dt));
             }
             plan.grid(kBatchScale, sa, sab, 1);
         }
-        // time advance; guard cells of the non-shear fields at t^{n+1}
+        // time advance; guard cells of the fields at t^{n+1}
         for (int i = 0; i < nb; i++) {
             pic_box* b = boxes[i];
+            const double t1 = time_of(b, b->step) + b->d.dt;
             b->step += 1;
-            if (!sheared(&b->d)) plan_fill(fend, fendb, b->G, field_ptrs(b), 6, 0, 0.0);
+            plan_fill(fend, fendb, b->G, field_ptrs(b), 6, sheared(&b->d) ? 1 : 0, shear_offset(b, t1));
         }
         plan.grid(kBatchFill, fend, fendb, 6);
     }

@@ -30,7 +30,9 @@ __device__ inline int wrapn(int i, int n)
 // ------------------------------------------------------------------ guard fill
 // Every guard cell takes its value from interior cells: y, z periodic; x periodic, or for the
 // shearing box F(x_o + m, y) = F(x_i + m, y + dys) and F(x_i - m, y) = F(x_o - m, y - dys)
-// with a fractional dys applied by linear interpolation along y.
+// with a fractional dys applied by linear interpolation along y.  No guard cell reads another one,
+// so the slabs of the three axes are one launch.  The step fills guards once, at its end, for the
+// push: the field kernels below read the periodic images themselves.
 
 // the image of an x guard cell between the two interior values a (at y + js) and b (at
 // y + js + 1), weight w on b; the guard fill and the 3D sweep's x halo share it
@@ -53,32 +55,30 @@ __device__ inline void shear_image(bool hi, int dys_int, float dys_w, int& js, f
 __device__ __attribute__((always_inline)) inline void fill_guards_body(const FillArgs& a, int blk, int, int c)
 {
     const GridDev& G = a.G;
-    const int slab = a.slab, shear = a.shear, dys_int = a.dys_int;
+    const int shear = a.shear, dys_int = a.dys_int;
     const float dys_w = a.dys_w;
     float* F = a.A.p[c];
     // 32-bit index arithmetic: the x and y guard widths are kGuard, the other divisors are
     // invariant (precomputed multipliers)
-    const uint32_t t = (uint32_t)blk * kBlock + threadIdx.x;
+    uint32_t t = (uint32_t)blk * kBlock + threadIdx.x;
     constexpr uint32_t g2 = 2 * kGuard;
     const int gz = G.g[2];
-    const uint32_t NYg = (uint32_t)(G.n[1] + 2 * kGuard), NZg = (uint32_t)(G.n[2] + 2 * gz);
+    const uint32_t NYg = (uint32_t)(G.n[1] + 2 * kGuard);
     int x, y, z;
-    if (slab == 0) {  // x guard slabs over the whole guarded y, z
-        if (t >= g2 * NYg * NZg) return;
+    if (t < a.n[0]) {  // x guard slabs over the whole guarded y, z
         const uint32_t m = t % g2, r = t / g2;
         const uint32_t q = G.divyg.div(r);
         y = (int)(r - q * NYg) - kGuard;
         z = (int)q - gz;
         x = (int)m < kGuard ? (int)m - kGuard : G.n[0] + ((int)m - kGuard);
-    } else if (slab == 1) {  // y guard slabs over interior x, guarded z
-        if (t >= (uint32_t)G.n[0] * g2 * NZg) return;
+    } else if ((t -= a.n[0]) < a.n[1]) {  // y guard slabs over interior x, guarded z
         const uint32_t r = G.div0.div(t);
         x = (int)(t - r * (uint32_t)G.n[0]);
         const uint32_t m = r % g2;
         z = (int)(r / g2) - gz;
         y = (int)m < kGuard ? (int)m - kGuard : G.n[1] + ((int)m - kGuard);
     } else {  // z guard slabs over interior x, y
-        if (t >= (uint32_t)G.n[0] * (uint32_t)G.n[1] * (uint32_t)(2 * gz)) return;
+        if ((t -= a.n[1]) >= a.n[2]) return;
         const uint32_t r = G.div0.div(t);
         x = (int)(t - r * (uint32_t)G.n[0]);
         const uint32_t q = G.div1.div(r);
@@ -272,8 +272,12 @@ PIC_BATCHED_KERNEL(fold_x, FoldXArgs, kBlock)
 
 // ------------------------------------------------------------------ Maxwell
 // Yee curls (c = 1, dx = 1).  E_j and B_j enter multiplied by ge[j], gb[j] (the l_j of the
-// expanding box, 1 otherwise).
+// expanding box, 1 otherwise).  Neighbours beyond a face are read at their periodic images, so the
+// three updates of a step need no guard fill between them.
 
+// element offsets from a cell to its periodic neighbour one up (or down) along an axis
+__device__ inline int step_up(int i, int n, int s) { return i + 1 == n ? -(n - 1) * s : s; }
+__device__ inline int step_down(int i, int n, int s) { return i == 0 ? (n - 1) * s : -s; }
 
 // B_i <- fout_i (fin_i B_i - dt/2 curl(g E)_i)
 __device__ __attribute__((always_inline)) inline void yee_b_cell(const MaxwellDev& M, int64_t t)
@@ -282,15 +286,16 @@ __device__ __attribute__((always_inline)) inline void yee_b_cell(const MaxwellDe
     int x, y, z;
     cell_of(G, t, x, y, z);
     const int64_t i = gidx(G, x, y, z);
-    const int64_t sy = G.sy, sz = G.sz;
     const bool d3 = G.dim == 3;
+    const int sx = step_up(x, G.n[0], 1), sy = step_up(y, G.n[1], G.sy);
+    const int sz = d3 ? step_up(z, G.n[2], G.sz) : 0;
     const float* Ex = M.E[0];
     const float* Ey = M.E[1];
     const float* Ez = M.E[2];
     const float g0 = M.gf[0], g1 = M.gf[1], g2 = M.gf[2];
     const float cx = g2 * (Ez[i + sy] - Ez[i]) - (d3 ? g1 * (Ey[i + sz] - Ey[i]) : 0.f);
-    const float cy = (d3 ? g0 * (Ex[i + sz] - Ex[i]) : 0.f) - g2 * (Ez[i + 1] - Ez[i]);
-    const float cz = g1 * (Ey[i + 1] - Ey[i]) - g0 * (Ex[i + sy] - Ex[i]);
+    const float cy = (d3 ? g0 * (Ex[i + sz] - Ex[i]) : 0.f) - g2 * (Ez[i + sx] - Ez[i]);
+    const float cz = g1 * (Ey[i + sx] - Ey[i]) - g0 * (Ex[i + sy] - Ex[i]);
     const float h = 0.5f * M.dt;
     M.B[0][i] = M.fout[0] * (M.fin[0] * M.B[0][i] - h * cx);
     M.B[1][i] = M.fout[1] * (M.fin[1] * M.B[1][i] - h * cy);
@@ -311,15 +316,16 @@ __device__ __attribute__((always_inline)) inline void yee_e_cell(const MaxwellDe
     int x, y, z;
     cell_of(G, t, x, y, z);
     const int64_t i = gidx(G, x, y, z);
-    const int64_t sy = G.sy, sz = G.sz;
     const bool d3 = G.dim == 3;
+    const int sx = step_down(x, G.n[0], 1), sy = step_down(y, G.n[1], G.sy);
+    const int sz = d3 ? step_down(z, G.n[2], G.sz) : 0;
     const float* Bx = M.B[0];
     const float* By = M.B[1];
     const float* Bz = M.B[2];
     const float g0 = M.gf[0], g1 = M.gf[1], g2 = M.gf[2];
-    const float cx = g2 * (Bz[i] - Bz[i - sy]) - (d3 ? g1 * (By[i] - By[i - sz]) : 0.f);
-    const float cy = (d3 ? g0 * (Bx[i] - Bx[i - sz]) : 0.f) - g2 * (Bz[i] - Bz[i - 1]);
-    const float cz = g1 * (By[i] - By[i - 1]) - g0 * (Bx[i] - Bx[i - sy]);
+    const float cx = g2 * (Bz[i] - Bz[i + sy]) - (d3 ? g1 * (By[i] - By[i + sz]) : 0.f);
+    const float cy = (d3 ? g0 * (Bx[i] - Bx[i + sz]) : 0.f) - g2 * (Bz[i] - Bz[i + sx]);
+    const float cz = g1 * (By[i] - By[i + sx]) - g0 * (Bx[i] - Bx[i + sy]);
     const float fp = 4.f * 3.14159265358979f * M.dt;
     M.E[0][i] = M.fout[0] * (M.fin[0] * M.E[0][i] + M.dt * cx - fp * M.J[0][i]);
     M.E[1][i] = M.fout[1] * (M.fin[1] * M.E[1][i] + M.dt * cy - fp * M.J[1][i]);
@@ -481,7 +487,87 @@ __device__ inline void ksb_store(const KsbDev& K, int64_t i, const float L[6], c
     }
 }
 
-// 2D (and any size): one thread per cell, neighbours straight from memory
+// The values the operator reads at one cell, all loaded before the first is used: the upwind sides
+// and the faces then select between registers, and the loads of a cell wait once.
+struct KsbCell {
+    float v[6][3][3][3];  // [component][dx + 1][dy + 1][dz + 1], the places the operator reads
+    __device__ inline float operator()(int c, int dx, int dy, int dz) const { return v[c][dx + 1][dy + 1][dz + 1]; }
+};
+
+// y, z periodic; x shearing-periodic: the column beyond a face is interpolated between the rows
+// y + dy + js and the next one of the other face's column, as the guard fill does
+template <bool D3>
+__device__ inline void ksb_load(const KsbDev& K, int x, int y, int z, int64_t i, KsbCell& V)
+{
+    const GridDev& G = K.G;
+    const float* const* F = K.Fk;
+    const int nx = G.n[0], ny = G.n[1];
+    const int yu = step_up(y, ny, G.sy), yd = step_down(y, ny, G.sy);
+    const int zu = D3 ? step_up(z, G.n[2], G.sz) : 0, zd = D3 ? step_down(z, G.n[2], G.sz) : 0;
+    const bool lo = x == 0, face = lo || x == nx - 1;
+    // elements at dx = +1 (dy = 0, -1) and dx = -1 (dy = 0, +1); r1: the second row of an image
+    int64_t u0 = i + 1, um = i + 1 + yd, d0 = i - 1, dp = i - 1 + yu;
+    int64_t r1[2] = {0, 0};
+    float w = 0.f;
+    if (face) {
+        int js;
+        shear_image(!lo, K.ydys_int, K.ydys_w, js, w);
+        const int64_t col = gidx(G, lo ? nx - 1 : 0, 0, z);
+        const int t = wrapn(y + js, ny);  // rows t - 1 .. t + 2 of the other face
+        const int64_t c0 = col + (int64_t)G.sy * t, cu = c0 + step_up(t, ny, G.sy);
+        if (lo) {
+            d0 = c0;
+            dp = r1[0] = cu;
+            r1[1] = col + (int64_t)G.sy * wrapn(t + 2, ny);
+        } else {
+            u0 = r1[1] = c0;
+            um = c0 + step_down(t, ny, G.sy);
+            r1[0] = cu;
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 6; c++) {
+        V.v[c][1][1][1] = F[c][i];
+        V.v[c][1][2][1] = F[c][i + yu];
+        V.v[c][1][0][1] = F[c][i + yd];
+    }
+    const float ezu = F[EZ][u0], eyu = F[EY][u0], bxu = F[BX][u0], eyum = F[EY][um], bxum = F[BX][um];
+    const float bzd = F[BZ][d0], byd = F[BY][d0], exd = F[EX][d0], exdp = F[EX][dp];
+    if (D3) {
+        V.v[EY][1][1][2] = F[EY][i + zu];
+        V.v[EX][1][1][2] = F[EX][i + zu];
+        V.v[EY][1][0][2] = F[EY][i + yd + zu];
+        V.v[BY][1][1][0] = F[BY][i + zd];
+        V.v[BX][1][1][0] = F[BX][i + zd];
+        V.v[EZ][1][1][0] = F[EZ][i + zd];
+        V.v[EZ][1][2][0] = F[EZ][i + yu + zd];
+    }
+    float s[5] = {0.f, 0.f, 0.f, 0.f, 0.f};  // the images' second row values, one face's at a time
+    if (face) {
+        s[0] = lo ? F[BZ][r1[0]] : F[EZ][r1[0]];
+        s[1] = lo ? F[BY][r1[0]] : F[EY][r1[0]];
+        s[2] = lo ? F[EX][r1[0]] : F[BX][r1[0]];
+        s[3] = lo ? F[EX][r1[1]] : F[EY][r1[1]];
+        s[4] = lo ? 0.f : F[BX][r1[1]];
+    }
+    const bool hi = face && !lo;
+    V.v[EZ][2][1][1] = hi ? shear_lerp(ezu, s[0], w) : ezu;
+    V.v[EY][2][1][1] = hi ? shear_lerp(eyu, s[1], w) : eyu;
+    V.v[BX][2][1][1] = hi ? shear_lerp(bxu, s[2], w) : bxu;
+    V.v[EY][2][0][1] = hi ? shear_lerp(eyum, s[3], w) : eyum;
+    V.v[BX][2][0][1] = hi ? shear_lerp(bxum, s[4], w) : bxum;
+    V.v[BZ][0][1][1] = lo ? shear_lerp(bzd, s[0], w) : bzd;
+    V.v[BY][0][1][1] = lo ? shear_lerp(byd, s[1], w) : byd;
+    V.v[EX][0][1][1] = lo ? shear_lerp(exd, s[2], w) : exd;
+    V.v[EX][0][2][1] = lo ? shear_lerp(exdp, s[3], w) : exdp;
+}
+
+// 2D (and any size): one thread per cell, neighbours straight from memory, beyond a face at their
+// images, so that no guard fill runs between sweeps.  On small grids a step is bound by its launches
+// (the fills were two of three in 2D): the 64^2 box replayed as a graph 201 -> 176 us a step, a
+// 20 x 12 x 16 box stepped call by call 223 -> 155 us; on 150 x 90 x 84 cells a sweep takes 26 us
+// (2.9 TB/s of the 72 B a cell it must move).  A separate branch for the cells at the x faces was
+// slower than the fills (213 us on 64^2: every wave of a row has such a lane and ran both branches).
 template <bool FIRST>
 __device__ __attribute__((always_inline)) inline void ksb_sweep_body(const KsbDev& K, int blk, int, int)
 {
@@ -493,24 +579,25 @@ __device__ __attribute__((always_inline)) inline void ksb_sweep_body(const KsbDe
         int x, y, z;
         cell_of(G, t, x, y, z);
         const int64_t i = gidx(G, x, y, z);
-        const int64_t sy = G.sy, sz = G.sz;
-        const float* const* F = K.Fk;
-        auto V = [&](int c, int dx, int dy, int dz) { return F[c][i + dx + sy * dy + sz * dz]; };
         const float v0 = -K.sO * ((float)x - K.half_nx);         // at x = i
         const float vh = -K.sO * ((float)x + 0.5f - K.half_nx);  // at x = i + 1/2
         float L[6], Fk[6];
-        if (K.expand) {
-            if (G.dim == 3)
+        KsbCell V;
+        if (G.dim == 3) {
+            ksb_load<true>(K, x, y, z, i, V);
+            if (K.expand)
                 ksb_operator_f<true>(V, v0, vh, K.sO, K.dfac, K.kz, L);
             else
-                ksb_operator_f<false>(V, v0, vh, K.sO, K.dfac, K.kz, L);
-        } else if (G.dim == 3) {
-            ksb_operator<true>(V, v0, vh, K.sO, L);
+                ksb_operator<true>(V, v0, vh, K.sO, L);
         } else {
-            ksb_operator<false>(V, v0, vh, K.sO, L);
+            ksb_load<false>(K, x, y, z, i, V);
+            if (K.expand)
+                ksb_operator_f<false>(V, v0, vh, K.sO, K.dfac, K.kz, L);
+            else
+                ksb_operator<false>(V, v0, vh, K.sO, L);
         }
 #pragma unroll
-        for (int c = 0; c < 6; c++) Fk[c] = F[c][i];
+        for (int c = 0; c < 6; c++) Fk[c] = V(c, 0, 0, 0);
         ksb_store<FIRST>(K, i, L, Fk, dm, fm);
     }
     if (K.conv) ksb_reduce<kBlock>(dm, fm, K.conv + 2 * K.k);
@@ -1239,22 +1326,29 @@ static inline unsigned nblocks(int64_t n) { return (unsigned)((n + kBlock - 1) /
 // 0.18 against 0.22 ms)
 constexpr unsigned kStrideBlocks = 4096;
 
+FillArgs fill_args(const GridDev& G, float* const* comps, int ncomp, int shear, double dys)
+{
+    FillArgs a{};
+    a.G = G;
+    for (int c = 0; c < ncomp; c++) a.A.p[c] = comps[c];
+    const double fl = floor(dys);
+    a.shear = shear;
+    a.dys_int = (int)fl;
+    a.dys_w = (float)(dys - fl);
+    // a guarded array holds less than 2^31 floats: the slabs together stay below 2^32 threads
+    const uint32_t NYg = (uint32_t)(G.n[1] + 2 * G.g[1]), NZg = (uint32_t)(G.n[2] + 2 * G.g[2]);
+    a.n[0] = 2u * G.g[0] * NYg * NZg;
+    a.n[1] = (uint32_t)G.n[0] * 2u * G.g[1] * NZg;
+    a.n[2] = (uint32_t)G.n[0] * (uint32_t)G.n[1] * 2u * G.g[2];
+    return a;
+}
+unsigned fill_blocks(const FillArgs& a) { return nblocks((int64_t)a.n[0] + a.n[1] + a.n[2]); }
+
 hipError_t fill_guards(const GridDev& G, float* const* comps, int ncomp, int shear, double dys,
                        hipStream_t st)
 {
-    Comp6 A{};
-    for (int c = 0; c < ncomp; c++) A.p[c] = comps[c];
-    const double fl = floor(dys);
-    const int di = (int)fl;
-    const float w = (float)(dys - fl);
-    const int NYg = G.n[1] + 2 * G.g[1], NZg = G.n[2] + 2 * G.g[2];
-    fill_guards_kernel<<<dim3(nblocks((int64_t)2 * G.g[0] * NYg * NZg), ncomp), kBlock, 0, st>>>(
-        FillArgs{G, A, 0, shear, di, w});
-    fill_guards_kernel<<<dim3(nblocks((int64_t)G.n[0] * 2 * G.g[1] * NZg), ncomp), kBlock, 0, st>>>(
-        FillArgs{G, A, 1, shear, di, w});
-    if (G.g[2] > 0)
-        fill_guards_kernel<<<dim3(nblocks((int64_t)G.n[0] * G.n[1] * 2 * G.g[2]), ncomp), kBlock, 0,
-                             st>>>(FillArgs{G, A, 2, shear, di, w});
+    const FillArgs a = fill_args(G, comps, ncomp, shear, dys);
+    fill_guards_kernel<<<dim3(fill_blocks(a), ncomp), kBlock, 0, st>>>(a);
     return hipGetLastError();
 }
 

@@ -299,11 +299,12 @@ struct Comp6 {
 struct Comp3 {
     float* p[3];
 };
-struct FillArgs {  // guard fill of one slab kind (0: x, 1: y, 2: z) of ncomp = gridDim.y arrays
+struct FillArgs {  // guard fill of ncomp = gridDim.y arrays
     GridDev G;
     Comp6 A;
-    int slab, shear, dys_int;
+    int shear, dys_int;
     float dys_w;
+    uint32_t n[3];  // guard cells of the x, y and z slabs
 };
 struct FoldPArgs {  // periodic current fold along axis 1 (y) or 2 (z)
     GridDev G;
@@ -332,13 +333,13 @@ struct ZeroArgs {  // n 32-bit words set to zero
 // first sweep of a step (Fk = F^n) also writes C = F^n + dt/2 L(F^n) - 4 pi dt J'.
 struct KsbDev {
     GridDev G;
-    const float* Fk[6];  // iterate, Bx By Bz Ex Ey Ez (guard cells filled)
+    const float* Fk[6];  // iterate, Bx By Bz Ex Ey Ez (the interior is read)
     float* C[6];         // constant part of the step (written by the first sweep)
     float* Fo[6];        // next iterate (interior)
     const float* J[3];
     float dt, sO, half_nx;
     // shift of the iterate's shearing-periodic x images, Delta y_s = ydys_int + ydys_w with
-    // ydys_w in [0,1) (the 3D sweep reads its x halo there instead of from guard cells)
+    // ydys_w in [0,1): the sweeps read the cells beyond the x faces there, not from guard cells
     int ydys_int;
     float ydys_w;
     // tolerance mode (conv != nullptr): sweep k adds max|F^{k+1} - F^k| and max|F^{k+1}| (FP32
@@ -487,6 +488,8 @@ enum SortBatchKind { kBatchMigCount, kBatchMigOffsets, kBatchScan, kBatchMigScat
 hipError_t sort_batch(SortBatchKind k, const void* table, UnitMap m, int blocks, hipStream_t st);
 int sort_result_buffer(const Tiles& tl);  // sort buffer holding the sorted pairs
 
+FillArgs fill_args(const GridDev& G, float* const* comps, int ncomp, int shear, double dys);
+unsigned fill_blocks(const FillArgs& a);
 hipError_t fill_guards(const GridDev& G, float* const* comps, int ncomp, int shear, double dys,
                        hipStream_t st);
 // Fold the current guards (y, z periodic in place).  Shearing box: the J' transport and the
@@ -497,13 +500,12 @@ hipError_t fold_current(const GridDev& G, float* const* J, float* const* out, in
 hipError_t yee_b(const MaxwellDev& M, hipStream_t st);
 hipError_t yee_e(const MaxwellDev& M, hipStream_t st);
 // one sweep; 3D grids whose x size is a multiple of the staged kernel's column tile (128) take
-// the staged kernel, which reads its whole halo at the (shearing-)periodic images itself;
-// otherwise one thread per cell reads the guard cells, which must be filled between sweeps
+// the staged kernel, others one thread per cell; both read cells beyond the faces at their images
 bool ksb_staged(const GridDev& G);
 // the two-sweep pass applies: a staged grid whose arrays span less than 4 GiB (32-bit offsets)
 bool ksb_pass_fits(const GridDev& G);
 hipError_t ksb_sweep(const KsbDev& K, bool first, hipStream_t st);
-// the one-thread-per-cell sweep on any grid (reads the iterate's guard cells)
+// the one-thread-per-cell sweep on any grid
 hipError_t ksb_sweep_unstaged(const KsbDev& K, bool first, hipStream_t st);
 // two sweeps F^k -> F^{k+2} in one pass over memory (staged 3D grids only); first: F^k = F^n,
 // the pass also writes C
