@@ -69,8 +69,8 @@ enum pic_leaky_mode { PIC_LEAKY_DISPLACEMENT = 0, PIC_LEAKY_PROBABILISTIC = 1 };
 #define PIC_STEP_GRAPH 2u   /* the batched step as a captured HIP graph, replayed while the box
                                set and its launch shapes stay the same (implies BATCHED) */
 /* pic_tile_sort flags */
-#define PIC_SORT_OVERLAP 1u /* run the sort of each species on a stream of its own (the species'
-                               sorts side by side), after the work queued on the box stream so
+#define PIC_SORT_OVERLAP 1u /* run the sort on a stream of its own (the species side by side),
+                               after the work queued on the box stream so
                                far (the push that wrote the positions), so that it overlaps the
                                current fold and the Maxwell step queued after it; the next call that reads or writes particles or the sort
                                (push, deposit, sort, escape compaction, particle and sort copies,
@@ -319,9 +319,9 @@ int32_t pic_tile_candidates(int32_t dim, uint32_t flags, int32_t* shapes_out, in
 /* Tile counting sort (stable): key = tile of the particle's cell, dead particles go to a
    dead bin and are dropped.  Produces the permutation used by the next pic_gather_push and
    the per-tile offsets.  After a push the particles are still grouped by the tiles of the
-   previous sort and each moved less than a cell, so (on tile grids with whole tiles and one
-   or at least three tiles per axis) the sort only counts moves to the neighbouring tiles;
-   a particle found farther away sends that sort to the general radix sort on the device.
+   previous sort and each moved less than a cell, so (in the shearing box with at least three
+   tiles in x and no last y tile of one row) the sort only counts moves to the neighbouring tiles;
+   a particle found farther away sends that sort to a radix sort on the device.
    Both give the same permutation.  PIC_ESTATE while an unfused push awaits pic_deposit. */
 int32_t pic_tile_sort(pic_box* const* boxes, int32_t nb, uint32_t flags);
 

@@ -37,7 +37,7 @@ struct Species {
     int32_t* toff[2] = {};  // tile offsets (n_tiles + 2) of the last two sorts
     int toff_cur = 0;       // toff[toff_cur] belongs to the last sort
     bool grouped = false;   // particle arrays are in the slot order of toff[toff_cur] (a push ran)
-    bool counts_ready = false;  // that push also wrote the migration counts of the next sort
+    bool counts_ready = false;  // that push wrote the migration counts of the next sort
     int32_t* n_live = nullptr;
     int32_t* ws_cell = nullptr;
     float* ws_off[3] = {};
@@ -157,11 +157,10 @@ struct pic_box {
     bool sorted = false;
     bool deposit_pending = false;
     bool record_valid = false;  // the unfused-deposit workspace holds the last push's record
-    // PIC_SORT_OVERLAP: the sort of each species on a stream of its own beside the box stream,
-    // joined by the next call that touches particles or the sort (default priority, created
-    // on first use)
-    hipStream_t side[kMaxSpecies] = {};
-    hipEvent_t fork_ev = nullptr, side_ev[kMaxSpecies] = {};
+    // PIC_SORT_OVERLAP: the sort on a stream of its own beside the box stream, joined by the
+    // next call that touches particles or the sort (default priority, created on first use)
+    hipStream_t side = nullptr;
+    hipEvent_t fork_ev = nullptr, side_ev = nullptr;
     bool side_pending = false;
     bool track_ids = false;
     bool caller_mem = false;  // created on caller memory (pic_box_mem): never allocates
@@ -184,14 +183,12 @@ constexpr int kRowAlign = 32;  // floats per 128-byte line
 
 int32_t hip_fail(hipError_t e) { return e == hipSuccess ? PIC_OK : PIC_EDEVICE; }
 
-// make the box stream wait for the sorts queued on the side streams (PIC_SORT_OVERLAP)
+// make the box stream wait for the sort queued on the side stream (PIC_SORT_OVERLAP)
 int32_t side_join(pic_box* b)
 {
     if (!b->side_pending) return PIC_OK;
     b->side_pending = false;
-    for (int s = 0; s < b->nsp; s++)
-        if (hipStreamWaitEvent(b->st, b->side_ev[s], 0) != hipSuccess) return PIC_EDEVICE;
-    return PIC_OK;
+    return hip_fail(hipStreamWaitEvent(b->st, b->side_ev, 0));
 }
 
 // the leaky box's escape rule applies: always in the leaky frame, on request in the others
@@ -438,25 +435,26 @@ int32_t check_boxes(pic_box* const* boxes, int32_t nb)
     return PIC_OK;
 }
 
-// Tile decomposition of the box (power-of-two tile edges); the migration sort applies with whole
-// tiles and, on every axis, one tile or at least three (so that the steps -1, 0, +1 reach
-// distinct tiles); the shearing box needs the x crossings visible in the tile index.
+// Tile decomposition of the box (power-of-two tile edges).  The migration sort applies to any tile
+// grid, but in the shearing box only with at least three tiles in x (the x crossings are then visible
+// in the tile index) and no last y tile of a single row (a crossing could reach a fourth y tile).
 void set_tiling(pic_box* b, const int tile[3])
 {
+    MigGeo& g = b->mg;
+    g.general = 0;
     for (int k = 0; k < 3; k++) {
         b->tile[k] = tile[k];
         b->tl.lt[k] = ceil_log2(tile[k]);
         b->tl.nt[k] = (b->n[k] + tile[k] - 1) / tile[k];
+        g.nt[k] = b->tl.nt[k];
+        g.lt[k] = b->tl.lt[k];
+        if (b->n[k] % tile[k] != 0 || b->tl.nt[k] == 2) g.general = 1;
     }
     b->tl.n_tiles = b->tl.nt[0] * b->tl.nt[1] * b->tl.nt[2];
-    b->mig_ok = true;
-    for (int k = 0; k < 3; k++) {
-        b->mg.nt[k] = b->tl.nt[k];
-        b->mg.lt[k] = b->tl.lt[k];
-        if (b->n[k] % tile[k] != 0 || b->tl.nt[k] == 2) b->mig_ok = false;
-    }
-    if (sheared(&b->d) && b->tl.nt[0] < 3) b->mig_ok = false;
-    b->mg.n_tiles = b->tl.n_tiles;
+    g.n_tiles = b->tl.n_tiles;
+    g.shear = sheared(&b->d) ? 1 : 0;
+    g.ny = b->n[1];
+    b->mig_ok = !(g.shear && (g.nt[0] < 3 || (g.nt[1] > 2 && b->n[1] % tile[1] == 1)));
 }
 
 // the largest tile count over the supported shapes (tile-indexed workspace is sized for it)
@@ -473,25 +471,65 @@ int max_tiles(int dim, const int n[3])
     return m;
 }
 
-// the tile sort of species s, queued on stream st (the species' buffers only: the sorts of
-// different species may run at the same time)
-int32_t sort_species(pic_box* b, int s, hipStream_t st)
+// the migration sort of species s, whose offsets go to its other offset array
+MigArgs mig_args(const pic_box* b, const Species& S)
 {
-    Species& S = b->sp[s];
-    hipError_t e;
-    if (b->mig_ok && S.grouped) {
-        const int nxt = S.toff_cur ^ 1;
-        e = migrate_sort(S.cell[S.cur], S.toff[S.toff_cur], S.n_upper, b->cc, b->tl, b->mg, S.sb,
-                         S.toff[nxt], S.n_live, S.which, b->ctr + 2, S.counts_ready, st);
-        S.toff_cur = nxt;
-        b->n_migrations++;
-    } else {
-        e = tile_sort(S.cell[S.cur], S.n_live, S.n_upper, b->cc, b->tl, S.sb, S.toff[S.toff_cur],
-                      S.n_live, S.which, st);
+    MigArgs a{};
+    a.cell = S.cell[S.cur];
+    a.toff_prev = S.toff[S.toff_cur];
+    a.n_upper = S.n_upper;
+    a.which = sort_result_buffer(b->tl);
+    a.cc = b->cc;
+    a.g = b->mg;
+    a.mcnt = S.sb.mcnt;
+    a.mpre = S.sb.mpre;
+    a.tot = S.sb.tot;
+    a.dcnt = S.sb.dcnt;
+    a.start = S.sb.start;
+    a.dpre = S.sb.dpre;
+    for (int k = 0; k < 2; k++) {
+        a.keys[k] = S.sb.keys[k];
+        a.vals[k] = S.sb.vals[k];
     }
-    if (e != hipSuccess) return PIC_EDEVICE;
-    S.grouped = false;
-    S.counts_ready = false;
+    a.toff = S.toff[S.toff_cur ^ 1];
+    a.n_live = S.n_live;
+    a.fallback = S.sb.fallback;
+    a.n_fallback = b->ctr + 2;
+    return a;
+}
+bool can_migrate(const pic_box* b, const Species& S) { return b->mig_ok && S.grouped && S.counts_ready; }
+void migrated(pic_box* b, Species& S)
+{
+    S.which = sort_result_buffer(b->tl);
+    S.toff_cur ^= 1;
+    S.grouped = S.counts_ready = false;
+    b->n_migrations++;
+}
+
+// the tile sort of every species, queued on stream st
+int32_t sort_all(pic_box* b, hipStream_t st)
+{
+    MigPair mp{};
+    uint32_t* scratch[kMaxSpecies] = {};
+    int m = 0;
+    for (int s = 0; s < b->nsp; s++) {
+        Species& S = b->sp[s];
+        if (can_migrate(b, S)) {
+            scratch[m] = S.sb.mscratch;
+            mp.s[m++] = mig_args(b, S);
+            continue;
+        }
+        if (tile_sort(S.cell[S.cur], S.n_live, S.n_upper, b->cc, b->tl, S.sb, S.toff[S.toff_cur], S.n_live,
+                      S.which, st) != hipSuccess)
+            return PIC_EDEVICE;
+        S.grouped = false;
+        S.counts_ready = false;
+    }
+    if (m > 0) {
+        if (migrate_sort(mp, m, scratch, st) != hipSuccess) return PIC_EDEVICE;
+        for (int s = 0; s < b->nsp; s++)
+            if (can_migrate(b, b->sp[s])) migrated(b, b->sp[s]);
+    }
     return PIC_OK;
 }
 
@@ -499,26 +537,18 @@ int32_t sort_box(pic_box* b)
 {
     if (b->deposit_pending) return PIC_ESTATE;  // the unfused deposit reads this sort's slots
     if (side_join(b)) return PIC_EDEVICE;
-    for (int s = 0; s < b->nsp; s++)
-        if (sort_species(b, s, b->st)) return PIC_EDEVICE;
+    if (sort_all(b, b->st)) return PIC_EDEVICE;
     b->sorted = true;
     return PIC_OK;
 }
 
-int floor_div(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
-
-// Tile y shifts of particles crossing the x faces of the shearing box in the push that uses
-// dys_int = floor(Delta y_s(t^{n+1})): the new y tile is within one of (old tile + shift).
+// Rows that the particles of y tile 0 may reach through the x faces of the shearing box in the push
+// that uses dys_int = floor(Delta y_s(t^{n+1})): from these on (mig_center).
 void set_migration_shift(pic_box* b, int dys_int)
 {
-    if (!sheared(&b->d)) {
-        b->mg.cy_out = b->mg.cy_in = 0;
-        return;
-    }
-    const int TY = b->tile[1], nty = b->tl.nt[1];
-    auto wrap = [&](int v) { return ((v % nty) + nty) % nty; };
-    b->mg.cy_out = wrap(floor_div(dys_int - 1, TY) + 1);
-    b->mg.cy_in = wrap(floor_div(-dys_int - 2, TY) + 1);
+    auto wrap = [&](int v) { return ((v % b->n[1]) + b->n[1]) % b->n[1]; };
+    b->mg.first[1] = wrap(dys_int - 1);
+    b->mg.first[0] = wrap(-dys_int - 2);
 }
 
 int32_t zero_current(pic_box* b)
@@ -940,49 +970,29 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
 
     // ---- a1: tile sort (migration sort in the batch; radix per box where it does not apply)
     {
-        std::vector<ZeroArgs> zf;
-        std::vector<uint32_t> zfb;
-        std::vector<MigCountArgs> mc;
-        std::vector<MigOffArgs> mo;
-        std::vector<ScanArgs> sc;
-        std::vector<MigScatterArgs> ms;
-        std::vector<uint32_t> mcb, mob, scb, msb;
+        std::vector<MigArgs> mo, sc;
+        std::vector<uint32_t> mob, scb, msb;
         std::vector<int> radix_boxes;
         for (int i = 0; i < nb; i++) {
             pic_box* b = boxes[i];
-            bool all_grouped = b->mig_ok;
-            for (int s = 0; s < b->nsp; s++) all_grouped = all_grouped && b->sp[s].grouped;
-            if (!all_grouped) {
+            bool all = true;
+            for (int s = 0; s < b->nsp; s++) all = all && can_migrate(b, b->sp[s]);
+            if (!all) {
                 radix_boxes.push_back(i);
                 continue;
             }
             const int nt = b->tl.n_tiles;
             for (int s = 0; s < b->nsp; s++) {
-                Species& S = b->sp[s];
-                const int nxt = S.toff_cur ^ 1;
-                const Gate g{S.sb.fallback, 0};
-                S.which = sort_result_buffer(b->tl);
-                if (!S.counts_ready) {  // else the push wrote the counts and the flag
-                    zf.push_back(ZeroArgs{reinterpret_cast<uint32_t*>(S.sb.fallback), 1});
-                    zfb.push_back(1);
-                    mc.push_back(MigCountArgs{S.cell[S.cur], S.toff[S.toff_cur], b->cc, b->mg,
-                                              S.sb.mcnt, S.sb.fallback, b->err});
-                    mcb.push_back((uint32_t)nt);
+                MigArgs a = mig_args(b, b->sp[s]);
+                a.keys[0] = nullptr;  // the push has latched kErrSort
+                mo.push_back(a);
+                mob.push_back(mig_offset_blocks(nt));
+                if (mig_needs_scan(nt)) {
+                    sc.push_back(a);
+                    scb.push_back(2);
                 }
-                S.counts_ready = false;
-                mo.push_back(MigOffArgs{S.sb.mcnt, b->mg, S.sb.mpre, S.sb.tot, S.sb.dcnt, g});
-                mob.push_back((uint32_t)((nt + kBlock / 64 - 1) / (kBlock / 64)));
-                sc.push_back(ScanArgs{S.sb.tot, S.sb.start, nt + 1, g});
-                scb.push_back(1);
-                sc.push_back(ScanArgs{S.sb.dcnt, S.sb.dpre, nt + 1, g});
-                scb.push_back(1);
-                ms.push_back(MigScatterArgs{S.cell[S.cur], S.toff[S.toff_cur], S.n_upper, b->cc, b->mg,
-                                            S.sb.mpre, S.sb.start, S.sb.dpre, S.sb.vals[S.which],
-                                            S.toff[nxt], S.n_live, g});
                 msb.push_back((uint32_t)(nt + 1));
-                S.toff_cur = nxt;
-                S.grouped = false;
-                b->n_migrations++;
+                migrated(b, b->sp[s]);
             }
             b->sorted = true;
         }
@@ -997,11 +1007,9 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             }
             if (sort_box(boxes[i])) return undo(PIC_EDEVICE);
         }
-        plan.grid(kBatchZero, zf, zfb, 1);
-        plan.sort(kBatchMigCount, mc, mcb);
         plan.sort(kBatchMigOffsets, mo, mob);
-        plan.sort(kBatchScan, sc, scb);
-        plan.sort(kBatchMigScatter, ms, msb);
+        plan.sort(kBatchMigScan, sc, scb);
+        plan.sort(kBatchMigScatter, mo, msb);
     }
 
     // ---- current zeroing and the fused push (a2-a6, a8)
@@ -1585,13 +1593,11 @@ int32_t pic_box_destroy(pic_box* b)
 {
     if (!b) return PIC_OK;
     hipStreamSynchronize(b->st);
-    for (int s = 0; s < kMaxSpecies; s++) {
-        if (b->side[s]) {
-            hipStreamSynchronize(b->side[s]);
-            hipStreamDestroy(b->side[s]);
-        }
-        if (b->side_ev[s]) hipEventDestroy(b->side_ev[s]);
+    if (b->side) {
+        hipStreamSynchronize(b->side);
+        hipStreamDestroy(b->side);
     }
+    if (b->side_ev) hipEventDestroy(b->side_ev);
     if (b->fork_ev) hipEventDestroy(b->fork_ev);
     stager_release(b->stager);
     for (auto& a : b->allocs) lib_free(a.first, a.second);
@@ -1843,24 +1849,20 @@ int32_t pic_tile_sort(pic_box* const* boxes, int32_t nb, uint32_t flags)
             r = sort_box(b);
             continue;
         }
-        // fork: each species' side stream takes over after the work queued so far (the push
-        // that wrote the positions); the species' sorts run there, side by side; the join is
-        // left to the next call that touches particles or the sort
+        // fork: the side stream takes over after the work queued so far (the push that wrote the
+        // positions); the species' sorts run there, side by side; the join is left to the next
+        // call that touches particles or the sort
         if (b->deposit_pending) return PIC_ESTATE;
         if (side_join(b)) return PIC_EDEVICE;
         // created on first use (each that is still missing, so a failed creation is retried)
         if (!b->fork_ev && hipEventCreateWithFlags(&b->fork_ev, hipEventDisableTiming) != hipSuccess)
             return PIC_EDEVICE;
-        for (int s = 0; s < b->nsp; s++)
-            if ((!b->side[s] && hipStreamCreateWithFlags(&b->side[s], hipStreamNonBlocking) != hipSuccess) ||
-                (!b->side_ev[s] && hipEventCreateWithFlags(&b->side_ev[s], hipEventDisableTiming) != hipSuccess))
-                return PIC_EDEVICE;
-        if (hipEventRecord(b->fork_ev, b->st) != hipSuccess) return PIC_EDEVICE;
-        for (int s = 0; s < b->nsp; s++) {
-            if (hipStreamWaitEvent(b->side[s], b->fork_ev, 0) != hipSuccess ||
-                sort_species(b, s, b->side[s]) != PIC_OK || hipEventRecord(b->side_ev[s], b->side[s]) != hipSuccess)
-                return PIC_EDEVICE;
-        }
+        if ((!b->side && hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking) != hipSuccess) ||
+            (!b->side_ev && hipEventCreateWithFlags(&b->side_ev, hipEventDisableTiming) != hipSuccess))
+            return PIC_EDEVICE;
+        if (hipEventRecord(b->fork_ev, b->st) != hipSuccess || hipStreamWaitEvent(b->side, b->fork_ev, 0) != hipSuccess ||
+            sort_all(b, b->side) != PIC_OK || hipEventRecord(b->side_ev, b->side) != hipSuccess)
+            return PIC_EDEVICE;
         b->sorted = true;
         b->side_pending = true;
     }

@@ -544,6 +544,8 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
     // migration counts of the next sort (per species, direction)
     __shared__ uint32_t mc[kMaxSpecies * kMigDirs];
     const int tsy = t0[1] >> P.tl.lt[1];  // y index of this tile
+    const int mco = frame_sheared(FRAME) ? mig_center(P.mg, tsy, true) : tsy;
+    const int mci = frame_sheared(FRAME) ? mig_center(P.mg, tsy, false) : tsy;
 
     stage_fields<G, DIM, 0, NT>(Fl, P, t0, ext, tid);
     if (fuse)
@@ -737,27 +739,25 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
             }
 
             if (P.count_mig) {
-                // direction of the new tile from this one (the migration sort applies only to
-                // whole tiles): the cell step r + dc in [-1, edge] shifted right by log2(edge)
-                // is -1, 0 or +1, periodic wraps included; one tile on an axis means 0.  A
-                // shearing-box x-face crossing moves in y by the push's Delta y_s: its y step is
-                // taken against the tile shift of that face.
-                const int dx = P.mg.nt[0] == 1 ? 0 : (rx + dcx) >> P.tl.lt[0];
-                int dy = P.mg.nt[1] == 1 ? 0 : (ry + dcy) >> P.tl.lt[1];
-                const int dz = (DIM == 2 || P.mg.nt[2] == 1) ? 0 : (rz + dcz) >> P.tl.lt[2];
-                if (frame_sheared(FRAME) && xwrap && P.mg.nt[1] > 1) {
-                    int r = (ncy >> P.tl.lt[1]) - tsy - (dx > 0 ? P.mg.cy_out : P.mg.cy_in);
-                    const int n1 = P.mg.nt[1];  // r lies in (-2 n1, 2 n1)
-                    if (r < 0) r += n1;
-                    if (r < 0) r += n1;
-                    if (r >= n1) r -= n1;
-                    dy = r == 0 ? 0 : (r == 1 ? 1 : (r == n1 - 1 ? -1 : 2));
+                // direction of the new tile from this one.  Whole tiles: the cell step r + dc in
+                // [-1, edge] shifted right by log2(edge) is -1, 0 or +1, periodic wraps included;
+                // one tile on an axis means 0.  A shearing-box x-face crossing moves in y by the
+                // push's Delta y_s: its y step is taken from the face's centre.
+                int d;
+                if (P.mg.general) {
+                    d = mig_dir(P.mg, t0[0] >> P.tl.lt[0], tsy, t0[2] >> P.tl.lt[2], mco, mci, ncx, ncy, ncz);
+                } else {
+                    const int dx = P.mg.nt[0] == 1 ? 0 : (rx + dcx) >> P.tl.lt[0];
+                    int dy = P.mg.nt[1] == 1 ? 0 : (ry + dcy) >> P.tl.lt[1];
+                    const int dz = (DIM == 2 || P.mg.nt[2] == 1) ? 0 : (rz + dcz) >> P.tl.lt[2];
+                    if (frame_sheared(FRAME) && xwrap && P.mg.nt[1] > 1)
+                        dy = ring_step((ncy >> P.tl.lt[1]) - (dx > 0 ? mco : mci), P.mg.nt[1]);
+                    d = dy == 2 ? -1 : (dx + 1) + 3 * (dy + 1) + 9 * (dz + 1);
                 }
-                int d = dy == 2 ? -1 : (dx + 1) + 3 * (dy + 1) + 9 * (dz + 1);
                 if (ncell < 0) d = kMigDead;
-                // the particles that stay in the tile (the common direction, 13) are not counted
-                // here: they are the tile's particles less all the others (below)
-                if (d != 13) {
+                // the particles that stay in the tile (the common direction) are not counted: the
+                // sort takes them as the tile's particles less all the others
+                if (d != kMigStay) {
                     if (d >= 0)
                         atomicAdd(&mc[s * kMigDirs + d], 1u);
                     else
@@ -795,13 +795,7 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
     __syncthreads();
     if (P.count_mig && tid < P.nsp * kMigDirs) {
         const int s = tid / kMigDirs, d = tid - s * kMigDirs;
-        uint32_t v = mc[tid];
-        if (d == 13) {  // the stayers: every particle of the tile goes to exactly one direction
-            v = (uint32_t)(P.sp[s].toff[tile + 1] - P.sp[s].toff[tile]);
-            for (int e = 0; e < kMigDirs; e++)
-                if (e != 13) v -= mc[s * kMigDirs + e];
-        }
-        P.mcnt[s][(size_t)tile * kMigDirs + d] = v;
+        P.mcnt[s][(size_t)tile * kMigDirs + d] = mc[tid];
     }
     if (fuse) flush_current<G, DIM, NT>(Jl, P, t0, ext, tid);
 }

@@ -50,31 +50,41 @@ struct Tiles {
 
 // Directions of the migration sort: (dx, dy, dz) in {-1,0,1}^3 between the tile a particle
 // was sorted into and the tile of its new cell, index (dx+1) + 3 (dy+1) + 9 (dz+1); the last
-// direction is the dead bin.  Crossing the x faces of the shearing box shifts y by the tile
-// offset cy_out (leaving through the outer face) or cy_in (inner face) before dy is taken.
+// direction is the dead bin.  On an axis of two tiles the other tile is +1, whichever way.
+// Beyond the x faces of the shearing box the y step is taken from the tile mig_center.
 constexpr int kMigDirs = 28;
 constexpr uint32_t kErrSort = 16u;  // a batched sort met a particle beyond the neighbour tiles
 constexpr uint32_t kErrNoConverge = 32u;  // shearing-box sweeps missed their tolerance
-constexpr int kMigDead = 27;
+constexpr int kMigStay = 13, kMigDead = 27;
+constexpr int kMigSmall = 1024;  // tiles up to which the scatter scans the tile totals itself
 struct MigGeo {
     int nt[3], lt[3];
     int n_tiles;
-    int cy_out, cy_in;
+    int general;  // an axis of two tiles, or of a size that is no multiple of the tile
+    // shearing box: cells along y and, modulo them, the first row that the particles of tile 0 may
+    // reach through the outer (first[1]) and the inner (first[0]) x face
+    int shear, ny, first[2];
 };
 
-// d in (-2n, 2n) reduced on a ring of n tiles to -1, 0, +1, or 2 if it is farther (conditional
-// adds: no integer division)
+// The middle one of the (at most three) y tiles that the particles of y tile ty reach through an x
+// face: they are T + 3 rows from ty T + first on (the row, one down or up by the move, one up or
+// down by the fraction of Delta y_s).  On a ring of ny rows whose last tile has two rows or more,
+// T + 3 rows touch three consecutive tiles at most.
+__device__ inline int mig_center(const MigGeo& g, int ty, bool out)
+{
+    if (!g.shear || g.nt[1] <= 2) return ty;
+    int r = (ty << g.lt[1]) + g.first[out ? 1 : 0];
+    if (r >= g.ny) r -= g.ny;
+    r = (r >> g.lt[1]) + 1;
+    return r == g.nt[1] ? 0 : r;
+}
+
+// d in (-n, n) reduced on a ring of n tiles to -1, 0, +1, or 2 if it is farther
 __device__ inline int ring_step(int d, int n)
 {
-    if (n == 1) return 0;
-    int r = d;
-    if (r < 0) r += n;
-    if (r < 0) r += n;
-    if (r >= n) r -= n;
-    if (r == 0) return 0;
-    if (r == 1) return 1;
-    if (r == n - 1) return -1;
-    return 2;
+    if (n <= 2) return n == 1 ? 0 : d & 1;
+    const int r = d < 0 ? d + n : d;
+    return r <= 1 ? r : (r == n - 1 ? -1 : 2);
 }
 
 __device__ inline void tile_coords(const MigGeo& g, int t, int& x, int& y, int& z)
@@ -85,33 +95,24 @@ __device__ inline void tile_coords(const MigGeo& g, int t, int& x, int& y, int& 
     z = r / g.nt[1];
 }
 
-// direction of a particle of source tile (sx, sy, sz) with new cell c, or -1 if its new tile is
-// not a neighbour
-__device__ inline int mig_dir(const MigGeo& g, const CellCode& cc, int sx, int sy, int sz,
-                              int32_t c)
+// direction of a particle of source tile (sx, sy, sz) with new cell (x, y, z), or -1 if its new tile
+// is not a neighbour; co, ci: the centres of sy beyond the outer and the inner x face
+__device__ inline int mig_dir(const MigGeo& g, int sx, int sy, int sz, int co, int ci, int x, int y, int z)
+{
+    const int dx = ring_step((x >> g.lt[0]) - sx, g.nt[0]);
+    const int tx = sx + dx;  // beyond a face: through it (a sheared box has three tiles in x or more)
+    const int c = tx >= g.nt[0] ? co : (tx < 0 ? ci : sy);
+    const int dy = ring_step((y >> g.lt[1]) - c, g.nt[1]);
+    const int dz = ring_step((z >> g.lt[2]) - sz, g.nt[2]);
+    if (dx == 2 || dy == 2 || dz == 2) return -1;
+    return (dx + 1) + 3 * (dy + 1) + 9 * (dz + 1);
+}
+__device__ inline int mig_dir(const MigGeo& g, const CellCode& cc, int sx, int sy, int sz, int co, int ci, int32_t c)
 {
     if (c < 0) return kMigDead;
     int x, y, z;
     cc.decode(c, x, y, z);
-    const int tx = x >> g.lt[0], ty = y >> g.lt[1], tz = z >> g.lt[2];
-    int dx = tx - sx, wx = 0;
-    if (g.nt[0] == 1) {
-        dx = 0;
-    } else if (dx == g.nt[0] - 1 && dx > 1) {  // through the inner x face
-        dx = -1;
-        wx = -1;
-    } else if (dx == 1 - g.nt[0] && dx < -1) {  // through the outer x face
-        dx = 1;
-        wx = 1;
-    } else if (dx < -1 || dx > 1) {
-        return -1;
-    }
-    // tiles and the shifts lie in [0, nt): the differences below lie in (-2 nt, nt)
-    const int shift = wx > 0 ? g.cy_out : (wx < 0 ? g.cy_in : 0);
-    const int dy = ring_step(ty - sy - shift, g.nt[1]);
-    const int dz = ring_step(tz - sz, g.nt[2]);
-    if (dy == 2 || dz == 2) return -1;
-    return (dx + 1) + 3 * (dy + 1) + 9 * (dz + 1);
+    return mig_dir(g, sx, sy, sz, co, ci, x, y, z);
 }
 
 // One species as seen by a push launch: input arrays (read through perm), output arrays
@@ -397,47 +398,23 @@ struct SortBufs {
     int32_t* fallback; // set when a particle left the neighbourhood the migration sort covers
 };
 
-// A launch gated on a device flag runs only when *flag == want (flag == nullptr: always), so
-// that a fallback path can be queued behind a test without a host round trip.
-struct Gate {
-    const int32_t* flag;
-    int want;
-    __device__ inline bool off() const { return flag && *flag != want; }
-};
-
-
-struct MigCountArgs {
+// Migration sort of one species: its arrays, the push's counts, and the general sort's buffers for
+// a species that turns out to be beyond it (keys[0] null: none, the error is latched by the push)
+struct MigArgs {
     const int32_t* cell;
     const int32_t* toff_prev;
+    int n_upper, which;  // which: the vals buffer that takes the permutation
     CellCode cc;
     MigGeo g;
-    uint32_t* mcnt;
-    int32_t* fallback;
-    uint32_t* err;  // batched sorts (no radix fallback behind them) latch kErrSort here
-};
-struct MigOffArgs {
     const uint32_t* mcnt;
-    MigGeo g;
-    uint32_t *mpre, *tot, *dcnt;
-    Gate gate;
+    uint32_t *mpre, *tot, *dcnt, *start, *dpre;
+    uint32_t *keys[2], *vals[2];
+    int32_t *toff, *n_live;
+    const int32_t* fallback;
+    unsigned long long* n_fallback;
 };
-struct MigScatterArgs {
-    const int32_t* cell;
-    const int32_t* toff_prev;
-    int n_upper;
-    CellCode cc;
-    MigGeo g;
-    const uint32_t *mpre, *start, *dpre;
-    uint32_t* perm;
-    int32_t* toff;
-    int32_t* n_live;
-    Gate gate;
-};
-struct ScanArgs {  // exclusive scan of n words by one workgroup
-    const uint32_t* in;
-    uint32_t* out;
-    int n;
-    Gate gate;
+struct MigPair {
+    MigArgs s[kMaxSpecies];
 };
 
 // ---- launchers (gpd.hip, sort.hip, grid.hip, xfer.hip)
@@ -459,15 +436,12 @@ hipError_t tile_sort(const int32_t* cell, const int32_t* n_live_in, int n_upper,
                      hipStream_t st);
 
 // Migration sort: stable counting sort by tile of arrays still grouped by the tiles of the
-// previous sort (toff_prev), every particle within one tile of its old one.  Falls back to
-// tile_sort on the device when a particle is outside that neighbourhood.  Writes the
-// permutation to sb.vals[which] and the offsets to toff.
+// previous sort (toff_prev), every particle within one tile of its old one, the counts taken by the
+// push.  Writes the permutation to vals[which] and the offsets to toff.
 size_t migrate_scratch_words(int n_tiles);
-// counts_ready: the push already wrote sb.mcnt and the fallback flag (the count pass is skipped)
-hipError_t migrate_sort(const int32_t* cell, const int32_t* toff_prev, int n_upper, CellCode cc,
-                        Tiles tl, const MigGeo& mg, SortBufs& sb, int32_t* toff,
-                        int32_t* n_live_out, int& which, unsigned long long* n_fallback,
-                        bool counts_ready, hipStream_t st);
+hipError_t migrate_sort(const MigPair& a, int n_species, uint32_t* const* scratch, hipStream_t st);
+unsigned mig_offset_blocks(int n_tiles);
+bool mig_needs_scan(int n_tiles);
 
 // batched launches of the grid and sort kernels (tables of per-unit arguments on the device)
 // per-component factors of a field set (the combined frame's conversion to and from the
@@ -484,7 +458,7 @@ enum GridBatchKind {
 hipError_t grid_batch(GridBatchKind k, const void* table, UnitMap m, int blocks, int ydim,
                       hipStream_t st);
 unsigned grid_blocks(int64_t items);  // workgroups of kBlock threads for one item per thread
-enum SortBatchKind { kBatchMigCount, kBatchMigOffsets, kBatchScan, kBatchMigScatter };
+enum SortBatchKind { kBatchMigOffsets, kBatchMigScan, kBatchMigScatter };
 hipError_t sort_batch(SortBatchKind k, const void* table, UnitMap m, int blocks, hipStream_t st);
 int sort_result_buffer(const Tiles& tl);  // sort buffer holding the sorted pairs
 
