@@ -320,6 +320,9 @@ void build_mj_table(double theta, std::vector<float>& out)
 // ---------------------------------------------------------------- descriptor of one push
 void set_migration_shift(pic_box* b, int dys_int);
 
+int64_t slots_per_tile(const pic_box* b);
+int64_t rounds_of(const pic_box* b);
+
 StepDev make_step(pic_box* b)
 {
     StepDev P{};
@@ -356,6 +359,7 @@ StepDev make_step(pic_box* b)
     set_migration_shift(b, P.dys_int);
     P.count_mig = b->mig_ok ? 1 : 0;
     P.mig_latch = 0;
+    P.lsplit = tile_split(b->dim, rounds_of(b), slots_per_tile(b));
     P.mg = b->mg;
     for (int s = 0; s < b->nsp; s++) {
         P.mcnt[s] = b->sp[s].sb.mcnt;
@@ -551,21 +555,34 @@ void set_migration_shift(pic_box* b, int dys_int)
     b->mg.first[0] = wrap(-dys_int - 2);
 }
 
-int32_t zero_current(pic_box* b)
+// slots per tile of the fuller species, on average
+int64_t slots_per_tile(const pic_box* b)
 {
-    for (int c = 0; c < 3; c++)
-        if (zero_floats(b->J[c] - b->origin, b->comp_elems, b->st) != hipSuccess) return PIC_EDEVICE;
-    return PIC_OK;
+    int64_t m = 0;
+    for (int s = 0; s < b->nsp; s++) m = std::max(m, (int64_t)b->sp[s].n_upper);
+    return m / std::max(b->tl.n_tiles, 1);
+}
+int64_t rounds_of(const pic_box* b) { return tile_rounds(b->dim, b->tl.n_tiles, slots_per_tile(b)); }
+
+// clear what a launch with descriptor P adds to: the current (deposit) and its counts and flags (push)
+int32_t clear_box(pic_box* b, const StepDev& P, bool current, bool counts)
+{
+    ClearArgs a{};
+    for (int c = 0; c < 3; c++) a.J[c] = b->J[c] - b->origin;
+    a.n = current ? b->comp_elems : 0;
+    for (int s = 0; counts && P.count_mig && s < b->nsp; s++) {
+        a.flag[s] = b->sp[s].sb.fallback;
+        a.mcnt[s] = b->sp[s].sb.mcnt;
+    }
+    if (counts && P.count_mig && P.lsplit > 0) a.nm = (int64_t)b->tl.n_tiles * kMigDirs;
+    return hip_fail(clear_for_push(a, b->st));
 }
 
 int32_t push_box(pic_box* b, bool fuse)
 {
     if (side_join(b)) return PIC_EDEVICE;
     if (!b->sorted) return PIC_ESTATE;
-    if (fuse) {
-        int32_t r = zero_current(b);
-        if (r) return r;
-    } else {
+    if (!fuse) {
         // workspace of the unfused deposit (old position and deposit displacement per slot)
         for (int s = 0; s < b->nsp; s++) {
             Species& S = b->sp[s];
@@ -578,8 +595,7 @@ int32_t push_box(pic_box* b, bool fuse)
         }
     }
     StepDev P = make_step(b);
-    for (int s = 0; P.count_mig && s < b->nsp; s++)
-        if (set_i32(b->sp[s].sb.fallback, 0, b->st) != hipSuccess) return PIC_EDEVICE;
+    if (clear_box(b, P, fuse, true)) return PIC_EDEVICE;
     if (launch_gather_push(P, b->tile, fuse ? 1 : 0, b->st) != hipSuccess) return PIC_EDEVICE;
     for (int s = 0; s < b->nsp; s++) {
         b->sp[s].cur ^= 1;
@@ -596,10 +612,9 @@ int32_t deposit_box(pic_box* b)
 {
     if (side_join(b)) return PIC_EDEVICE;
     if (!b->deposit_pending) return PIC_ESTATE;
-    int32_t r = zero_current(b);
-    if (r) return r;
     // the saved slots and tile offsets belong to the sort before the push
     StepDev P = make_step(b);
+    if (clear_box(b, P, true, false)) return PIC_EDEVICE;
     if (launch_deposit(P, b->tile, b->st) != hipSuccess) return PIC_EDEVICE;
     b->deposit_pending = false;
     return PIC_OK;
@@ -1017,21 +1032,32 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
         std::vector<ZeroArgs> z;
         std::vector<uint32_t> zb;
         std::map<std::tuple<int, int, int, int, int>, std::pair<std::vector<StepDev>, std::vector<uint32_t>>> groups;
+        std::map<std::tuple<int, int, int, int, int>, int64_t> group_rounds;  // of each launch
+        auto group_of = [](const pic_box* b) {
+            return std::make_tuple(b->dim, b->tile[0], b->tile[1], b->tile[2], b->d.frame);
+        };
+        for (int i = 0; i < nb; i++) group_rounds[group_of(boxes[i])] += rounds_of(boxes[i]);
         for (int i = 0; i < nb; i++) {
             pic_box* b = boxes[i];
             for (int c = 0; c < 3; c++) {
                 z.push_back(ZeroArgs{reinterpret_cast<uint32_t*>(b->J[c] - b->origin), b->comp_elems});
                 zb.push_back(grid_blocks(b->comp_elems));
             }
-            auto& gr = groups[std::make_tuple(b->dim, b->tile[0], b->tile[1], b->tile[2], b->d.frame)];
+            auto& gr = groups[group_of(b)];
             StepDev P = make_step(b);
             P.mig_latch = 1;  // no radix fallback behind a batched sort
+            P.lsplit = tile_split(b->dim, group_rounds[group_of(b)], slots_per_tile(b));
             gr.first.push_back(P);
-            gr.second.push_back((uint32_t)b->tl.n_tiles);
+            gr.second.push_back((uint32_t)b->tl.n_tiles << P.lsplit);
             for (int s = 0; s < b->nsp; s++) {
                 if (P.count_mig) {  // cleared after this step's sort read it, set by the push
                     z.push_back(ZeroArgs{reinterpret_cast<uint32_t*>(b->sp[s].sb.fallback), 1});
                     zb.push_back(1);
+                    if (P.lsplit > 0) {
+                        const int64_t nm = (int64_t)b->tl.n_tiles * kMigDirs;
+                        z.push_back(ZeroArgs{b->sp[s].sb.mcnt, nm});
+                        zb.push_back(grid_blocks(nm));
+                    }
                 }
                 b->sp[s].cur ^= 1;
                 b->sp[s].grouped = true;
@@ -1963,9 +1989,10 @@ int32_t pic_autotune(pic_box* b, uint32_t flags, int32_t trials, int32_t* tile_o
         for (int t = 0; t <= trials && !r; t++) {
             for (int s = 0; s < b->nsp; s++) b->sp[s].grouped = false;
             r = sort_box(b);
-            if (!r) r = zero_current(b);
             if (r) break;
             const StepDev P = make_step(b);
+            r = clear_box(b, P, true, true);
+            if (r) break;
             if (hipEventRecord(e0, st) != hipSuccess ||
                 launch_gather_push(P, b->tile, 1, st) != hipSuccess ||
                 hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {

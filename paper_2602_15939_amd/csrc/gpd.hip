@@ -9,6 +9,8 @@
 // Particles are read through the sort permutation and written in sorted slot order, so the
 // tile sort's scatter is fused into this pass.  A particle found outside its tile (only
 // possible without a sort since the last push) takes the global-memory path.
+#include <algorithm>
+
 #include "pic_internal.h"
 
 namespace pic {
@@ -536,7 +538,8 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
     float* const Fl = reinterpret_cast<float*>(lds);                                      // E, B
     unsigned long long* const Jl = reinterpret_cast<unsigned long long*>(lds + G::FBYTES);  // J
 
-    const int tile = xcd_contiguous(blk, nblk);
+    const int unit = xcd_contiguous(blk, nblk);
+    const int tile = unit >> P.lsplit, part = unit & ((1 << P.lsplit) - 1);
     int t0[3], ext[3];
     tile_origin<DIM>(P, tile, t0, ext);
     const int tid = threadIdx.x;
@@ -563,7 +566,7 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
         // the waves take 64-slot groups aligned to 32 slots (the 128-byte lines of the 4-byte
         // particle arrays), so that their stores fill whole lines; the lanes before the tile's
         // first slot idle in the first round
-        for (uint32_t slot = (beg & ~31u) + tid; slot < end; slot += NT) {
+        for (uint32_t slot = (beg & ~31u) + part * NT + tid; slot < end; slot += (uint32_t)NT << P.lsplit) {
             if (slot < beg) continue;
             uint32_t so = slot;
             asm("" : "+v"(so));  // keeps the 32-bit offset form (scalar base) for the stores
@@ -795,7 +798,11 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
     __syncthreads();
     if (P.count_mig && tid < P.nsp * kMigDirs) {
         const int s = tid / kMigDirs, d = tid - s * kMigDirs;
-        P.mcnt[s][(size_t)tile * kMigDirs + d] = mc[tid];
+        uint32_t* const cnt = &P.mcnt[s][(size_t)tile * kMigDirs + d];
+        if (P.lsplit == 0)
+            *cnt = mc[tid];
+        else if (mc[tid])
+            atomicAdd(cnt, mc[tid]);
     }
     if (fuse) flush_current<G, DIM, NT>(Jl, P, t0, ext, tid);
 }
@@ -828,7 +835,8 @@ __global__ __launch_bounds__(NT) void deposit_kernel(StepDev P)
 {
     using G = Geo<DIM, TX, TY, TZ>;
     __shared__ unsigned long long Jl[G::JTOT];
-    const int tile = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int unit = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int tile = unit >> P.lsplit, part = unit & ((1 << P.lsplit) - 1);
     int t0[3], ext[3];
     tile_origin<DIM>(P, tile, t0, ext);
     const int tid = threadIdx.x;
@@ -837,7 +845,7 @@ __global__ __launch_bounds__(NT) void deposit_kernel(StepDev P)
     for (int s = 0; s < P.nsp; s++) {
         const SpeciesDev& S = P.sp[s];
         const uint32_t beg = (uint32_t)S.toff[tile], end = (uint32_t)S.toff[tile + 1];
-        for (uint32_t slot = beg + tid; slot < end; slot += NT) {
+        for (uint32_t slot = beg + part * NT + tid; slot < end; slot += (uint32_t)NT << P.lsplit) {
             int cx, cy, cz;
             P.cc.decode(ld_at(S.ws_cell, slot), cx, cy, cz);
             const float ox = ld_at(S.ws_off[0], slot), oy = ld_at(S.ws_off[1], slot);
@@ -872,11 +880,31 @@ __global__ __launch_bounds__(NT) void deposit_kernel(StepDev P)
 template <int DIM>
 constexpr int threads_for() { return DIM == 3 ? 512 : 256; }
 
+// A tile's workgroup walks its particles a round of NT slots after another, each round waiting for
+// its loads (3 to 5 us), so a launch of few or uneven tiles is bound by its longest chain on an idle
+// chip.  Tiles are split until a part's rounds of a species are no more than the launch's rounds
+// shared out to the workgroups that the chip holds (three a CU in 3D, eight in 2D), but not below
+// one round: more parts only add their staging and flush.  The 64^2 box of the parity tests (16 tiles
+// of 4096 slots a species): 84 us whole, 19 us in 256 workgroups; 20 x 12 x 16 cells: 32 -> 28 us.
+int tile_split(int dim, int64_t rounds, int64_t slots_per_tile)
+{
+    const int64_t nt = dim == 3 ? threads_for<3>() : threads_for<2>(), held = dim == 3 ? 3 * 256 : 8 * 256;
+    const int64_t most = std::max<int64_t>(1, rounds / held);
+    int l = 0;
+    while (l < 6 && (slots_per_tile >> l) > nt * most) l++;
+    return l;
+}
+int64_t tile_rounds(int dim, int64_t n_tiles, int64_t slots_per_tile)
+{
+    const int64_t nt = dim == 3 ? threads_for<3>() : threads_for<2>();
+    return n_tiles * ((slots_per_tile + nt - 1) / nt);
+}
+
 template <int DIM, int TX, int TY, int TZ>
 static hipError_t launch_shape(const StepDev& P, int fuse, hipStream_t st)
 {
     constexpr int NT = threads_for<DIM>();
-    const dim3 grid(P.tl.n_tiles), block(NT);
+    const dim3 grid((unsigned)P.tl.n_tiles << P.lsplit), block(NT);
     switch (P.frame) {
     case kShear:
         gpd_kernel<DIM, TX, TY, TZ, kShear, NT><<<grid, block, 0, st>>>(P, fuse);
@@ -901,7 +929,7 @@ template <int DIM, int TX, int TY, int TZ>
 static hipError_t launch_dep_shape(const StepDev& P, hipStream_t st)
 {
     constexpr int NT = threads_for<DIM>();
-    deposit_kernel<DIM, TX, TY, TZ, NT><<<dim3(P.tl.n_tiles), dim3(NT), 0, st>>>(P);
+    deposit_kernel<DIM, TX, TY, TZ, NT><<<dim3((unsigned)P.tl.n_tiles << P.lsplit), dim3(NT), 0, st>>>(P);
     return hipGetLastError();
 }
 

@@ -1184,7 +1184,7 @@ PIC_BATCHED_KERNEL(scale_fields, ScaleArgs, kBlock)
 
 // grid-stride, 16-byte stores where the array is 16-byte aligned (the batched launch gives
 // every word its own thread, so most of its threads find nothing to do)
-__device__ __attribute__((always_inline)) inline void zero_body(const ZeroArgs& a, int blk, int nblk, int)
+__device__ inline void zero_words(const ZeroArgs& a, int blk, int nblk)
 {
     const int64_t stride = (int64_t)nblk * kBlock, i = (int64_t)blk * kBlock + threadIdx.x;
     int64_t head = 0;
@@ -1196,7 +1196,22 @@ __device__ __attribute__((always_inline)) inline void zero_body(const ZeroArgs& 
     }
     for (int64_t j = head + i; j < a.n; j += stride) a.p[j] = 0u;
 }
+__device__ __attribute__((always_inline)) inline void zero_body(const ZeroArgs& a, int blk, int nblk, int)
+{
+    zero_words(a, blk, nblk);
+}
 PIC_BATCHED_KERNEL(zero, ZeroArgs, kBlock)
+
+// one launch (five before): y = 0 .. 2 the current arrays, beyond them the counts of a species
+__global__ __launch_bounds__(kBlock) void clear_kernel(ClearArgs a)
+{
+    const int y = (int)blockIdx.y, s = y - 3;
+    if (y < 3)
+        zero_words(ZeroArgs{reinterpret_cast<uint32_t*>(a.J[y]), a.n}, (int)blockIdx.x, (int)gridDim.x);
+    else
+        zero_words(ZeroArgs{a.mcnt[s], a.nm}, (int)blockIdx.x, (int)gridDim.x);
+    if (y == 0 && blockIdx.x == 0 && threadIdx.x < kMaxSpecies && a.flag[threadIdx.x]) *a.flag[threadIdx.x] = 0;
+}
 
 // interior <-> dense copies: dense index x + n0*(y + n1*z)
 __global__ __launch_bounds__(kBlock) void interior_copy_kernel(GridDev G, float* guarded,
@@ -1490,6 +1505,13 @@ hipError_t zero_floats(float* p, int64_t n, hipStream_t st)
     if (n > 0)
         zero_kernel<<<std::min(nblocks((n + 3) / 4), kStrideBlocks), kBlock, 0, st>>>(
             ZeroArgs{reinterpret_cast<uint32_t*>(p), n});
+    return hipGetLastError();
+}
+hipError_t clear_for_push(const ClearArgs& a, hipStream_t st)
+{
+    const int ns = a.nm == 0 ? 0 : (a.mcnt[1] ? 2 : 1);
+    const unsigned nb = std::min(nblocks((std::max(a.n, a.nm) + 3) / 4), kStrideBlocks / 4);
+    clear_kernel<<<dim3(std::max(nb, 1u), 3 + ns), kBlock, 0, st>>>(a);
     return hipGetLastError();
 }
 hipError_t interior_copy(const GridDev& G, float* guarded, float* dense, int to_dense, hipStream_t st)

@@ -171,8 +171,12 @@ struct StepDev {
     const float* mj;      // kMjBins + kMjTail values
     // fixed-point tile current: contribution * jscale -> integer units, units * junit -> J
     float jscale, junit;
+    // a tile's slots are shared out to 2^lsplit workgroups (part p takes every 2^lsplit-th round of
+    // them), where the tiles alone would leave the chip idle
+    int lsplit;
     // migration counts of the next sort, taken by the push: per species and source tile
-    // (= this launch's tile), the particles per direction (mcnt[tile * kMigDirs + d]); a
+    // (= this launch's tile), the particles per direction (mcnt[tile * kMigDirs + d], added to the
+    // cleared counts by the parts of a split tile); a
     // particle beyond the neighbouring tiles sets mfb (the radix fallback runs then)
     int count_mig;
     int mig_latch;  // batched steps (no radix fallback behind the sort): latch kErrSort too
@@ -325,6 +329,15 @@ struct FoldXArgs {  // x fold (periodic or shearing-periodic)
     int all, shear, dys_int;
     float dys_w;
 };
+// What a push starts from: the current arrays (n words each), the fallback flags and, for split
+// tiles, the migration counts (nm words) at zero.
+struct ClearArgs {
+    float* J[3];
+    int64_t n;
+    int32_t* flag[kMaxSpecies];
+    uint32_t* mcnt[kMaxSpecies];
+    int64_t nm;
+};
 struct ZeroArgs {  // n 32-bit words set to zero
     uint32_t* p;
     int64_t n;
@@ -419,6 +432,10 @@ struct MigPair {
 
 // ---- launchers (gpd.hip, sort.hip, grid.hip, xfer.hip)
 bool tile_shape_supported(int dim, const int t[3]);
+// log2 of the workgroups per tile of a box whose tiles hold slots_per_tile slots of the fuller species
+// on average, in a push or deposit launch over `rounds` rounds (tile_rounds of all its boxes)
+int tile_split(int dim, int64_t rounds, int64_t slots_per_tile);
+int64_t tile_rounds(int dim, int64_t n_tiles, int64_t slots_per_tile);
 // supported tile shapes (batched: those of the batched launch); the default shape comes first
 int tile_candidates(int dim, bool batched, int (*out)[3], int max);
 hipError_t launch_gather_push(const StepDev& P, const int t[3], int fuse, hipStream_t st);
@@ -490,6 +507,7 @@ hipError_t ksb_finalize(const KsbFin& F, hipStream_t st);
 hipError_t scale_fields(const GridDev& G, float* const* F, const float f[3], hipStream_t st);
 constexpr int kKsbFinBlocks = 512;  // workgroups per box of the finalize copy (grid stride)
 hipError_t zero_floats(float* p, int64_t n, hipStream_t st);
+hipError_t clear_for_push(const ClearArgs& a, hipStream_t st);
 hipError_t interior_copy(const GridDev& G, float* guarded, float* dense, int to_dense,
                          hipStream_t st);
 hipError_t field_energy(const GridDev& G, float* const* comps, int ncomp, double* part, int nblk,
