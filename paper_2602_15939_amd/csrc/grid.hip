@@ -638,8 +638,8 @@ __global__ __launch_bounds__(KX * KY) void ksb_sweep3_kernel(KsbDev K)
     const int nx = G.n[0], ny = G.n[1], nz = G.n[2];
     const int ntx = nx / KX, nty = (ny + KY - 1) / KY;
     const int tile = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int x0 = (tile % ntx) * KX, y0 = ((tile / ntx) % nty) * KY, z0 = (tile / (ntx * nty)) * KZ;
-    const int z1 = min(z0 + KZ, nz);
+    const int x0 = (tile % ntx) * KX, y0 = ((tile / ntx) % nty) * KY, z0 = (tile / (ntx * nty)) * K.zc;
+    const int z1 = min(z0 + K.zc, nz);
     const int x = x0 + tx, y = y0 + ty;
     const bool inside = y < ny;
     const float* const* F = K.Fk;
@@ -816,7 +816,7 @@ __global__ __launch_bounds__(PassTile<TX>::PN) __attribute__((amdgpu_waves_per_e
 void ksb_pass3_kernel(KsbDev K)
 {
     using T = PassTile<TX>;
-    constexpr int PX = T::PX, PY = T::PY, PZ = T::PZ, PN = T::PN;
+    constexpr int PX = T::PX, PY = T::PY, PN = T::PN;
     constexpr int W0X = T::W0X, W0Y = T::W0Y, W1X = T::W1X, W1Y = T::W1Y, XR0 = T::XR0, XR1 = T::XR1;
     static_assert(PX % 64 == 0 && W1Y * PX == 64 * T::WXB && T::WAUX < PN / 64 && T::WO1 < PN / 64,
                   "thread roles");
@@ -831,8 +831,8 @@ void ksb_pass3_kernel(KsbDev K)
     const int nx = G.n[0], ny = G.n[1], nz = G.n[2];
     const int ntx = nx / PX, nty = (ny + PY - 1) / PY;
     const int tile = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int x0 = (tile % ntx) * PX, y0 = ((tile / ntx) % nty) * PY, z0 = (tile / (ntx * nty)) * PZ;
-    const int z1 = min(z0 + PZ, nz);
+    const int x0 = (tile % ntx) * PX, y0 = ((tile / ntx) % nty) * PY, z0 = (tile / (ntx * nty)) * K.zc;
+    const int z1 = min(z0 + K.zc, nz);
     const float* const* F = K.Fk;
     const float h = 0.5f * K.dt;
     const float fpdt = 4.f * 3.14159265358979f * K.dt;
@@ -1416,15 +1416,26 @@ bool ksb_pass_fits(const GridDev& G)
     return G.dim == 3 && G.n[0] % kPassX == 0 && 4 * (int64_t)G.sz * G.n[2] < (int64_t(1) << 32);
 }
 
+// Planes per workgroup of the staged kernels and the workgroups of a launch over `columns` column
+// tiles: `most` planes on grids that fill the chip with them (two workgroups a CU), fewer on smaller
+// ones, down to 4 (a chunk reads two planes, a pass four, beyond its own).  On
+// 128 x 64 x 64 cells chunks of 64 planes are 16 workgroups: 61 us a sweep, 13 us in chunks of 4.
+static unsigned z_chunks(int columns, int nz, int most, int& zc)
+{
+    zc = most;
+    while (zc > 4 && (int64_t)columns * ((nz + zc - 1) / zc) < 2 * 256) zc /= 2;
+    return (unsigned)(columns * ((nz + zc - 1) / zc));
+}
+
 hipError_t ksb_sweep(const KsbDev& K, bool first, hipStream_t st)
 {
     if (ksb_staged(K.G)) {
-        const unsigned grid = (unsigned)((K.G.n[0] / KX) * ((K.G.n[1] + KY - 1) / KY) *
-                                         ((K.G.n[2] + KZ - 1) / KZ));
+        KsbDev Z = K;
+        const unsigned grid = z_chunks((K.G.n[0] / KX) * ((K.G.n[1] + KY - 1) / KY), K.G.n[2], KZ, Z.zc);
         if (first)
-            ksb_sweep3_kernel<true><<<grid, KX * KY, 0, st>>>(K);
+            ksb_sweep3_kernel<true><<<grid, KX * KY, 0, st>>>(Z);
         else
-            ksb_sweep3_kernel<false><<<grid, KX * KY, 0, st>>>(K);
+            ksb_sweep3_kernel<false><<<grid, KX * KY, 0, st>>>(Z);
     } else {
         const unsigned nb = nblocks((int64_t)K.G.n[0] * K.G.n[1] * K.G.n[2]);
         if (first)
@@ -1447,12 +1458,12 @@ hipError_t ksb_pass(const KsbDev& K, bool first, hipStream_t st)
 {
     if (!ksb_pass_fits(K.G) || K.conv) return hipErrorInvalidValue;
     using T = PassTile<kPassX>;
-    const unsigned grid = (unsigned)((K.G.n[0] / T::PX) * ((K.G.n[1] + T::PY - 1) / T::PY) *
-                                     ((K.G.n[2] + T::PZ - 1) / T::PZ));
+    KsbDev Z = K;
+    const unsigned grid = z_chunks((K.G.n[0] / T::PX) * ((K.G.n[1] + T::PY - 1) / T::PY), K.G.n[2], T::PZ, Z.zc);
     if (first)
-        ksb_pass3_kernel<kPassX, true><<<grid, T::PN, 0, st>>>(K);
+        ksb_pass3_kernel<kPassX, true><<<grid, T::PN, 0, st>>>(Z);
     else
-        ksb_pass3_kernel<kPassX, false><<<grid, T::PN, 0, st>>>(K);
+        ksb_pass3_kernel<kPassX, false><<<grid, T::PN, 0, st>>>(Z);
     return hipGetLastError();
 }
 hipError_t scale_fields(const GridDev& G, float* const* F, const float f[3], hipStream_t st)

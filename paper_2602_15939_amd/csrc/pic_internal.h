@@ -367,6 +367,7 @@ struct KsbDev {
     // intermediate iterate's x images, Delta y_s at t^{n+1} = y1_int + y1_w
     int y1_int;
     float y1_w;
+    int zc;  // planes per workgroup of the staged kernels (set by their launchers)
     // combined shearing and expanding frame (one-thread-per-cell sweeps only): the iterates are
     // the expanding-frame fields, the curls act on dfac[c] F_c and kz multiplies the z
     // transport of E'_y in dE'_z/dt

@@ -1,0 +1,26 @@
+"""The staged shearing-box sweeps cut z into chunks of 4 to 64 planes by the grid's column tiles.  The
+two-sweep pass equals single sweeps (tolerance mode with an unreachable tolerance) bit for bit where
+the two cut differently: one whole chunk against chunks of 4, a ragged last chunk, one plane more
+than a chunk, and one-thread-per-cell single sweeps (x size 64)."""
+import numpy as np
+import pytest
+
+from paper_2602_15939_amd import _lib as L
+from test_gpu_ksb_pass import _box, _current
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [(128, 1024, 6), (64, 256, 130), (128, 256, 65), (256, 12, 33)])
+def test_pass_equals_single_sweeps_for_any_chunks(n):
+    J = _current(n, 5)
+    boxes = [_box(n, 0.003, 13, J, maxwell_iters=4, maxwell_tol=t)[0] for t in (0.0, 1e-30)]
+    try:
+        for b in boxes:
+            b.maxwell()
+            assert b.info().errors & ~(L.DERR_ORDER | L.DERR_NOCONVERGE) == 0
+        for fa, fb in zip(boxes[0].get_fields(), boxes[1].get_fields()):
+            np.testing.assert_array_equal(fa.cpu().numpy(), fb.cpu().numpy())
+    finally:
+        for b in boxes:
+            b.close()
