@@ -321,7 +321,6 @@ void build_mj_table(double theta, std::vector<float>& out)
 void set_migration_shift(pic_box* b, int dys_int);
 
 int64_t slots_per_tile(const pic_box* b);
-int64_t rounds_of(const pic_box* b);
 
 StepDev make_step(pic_box* b)
 {
@@ -359,7 +358,7 @@ StepDev make_step(pic_box* b)
     set_migration_shift(b, P.dys_int);
     P.count_mig = b->mig_ok ? 1 : 0;
     P.mig_latch = 0;
-    P.lsplit = tile_split(b->dim, rounds_of(b), slots_per_tile(b));
+    P.lsplit = tile_split(b->dim, b->tl.n_tiles, slots_per_tile(b));
     P.mg = b->mg;
     for (int s = 0; s < b->nsp; s++) {
         P.mcnt[s] = b->sp[s].sb.mcnt;
@@ -562,7 +561,6 @@ int64_t slots_per_tile(const pic_box* b)
     for (int s = 0; s < b->nsp; s++) m = std::max(m, (int64_t)b->sp[s].n_upper);
     return m / std::max(b->tl.n_tiles, 1);
 }
-int64_t rounds_of(const pic_box* b) { return tile_rounds(b->dim, b->tl.n_tiles, slots_per_tile(b)); }
 
 // clear what a launch with descriptor P adds to: the current (deposit) and its counts and flags (push)
 int32_t clear_box(pic_box* b, const StepDev& P, bool current, bool counts)
@@ -1032,11 +1030,11 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
         std::vector<ZeroArgs> z;
         std::vector<uint32_t> zb;
         std::map<std::tuple<int, int, int, int, int>, std::pair<std::vector<StepDev>, std::vector<uint32_t>>> groups;
-        std::map<std::tuple<int, int, int, int, int>, int64_t> group_rounds;  // of each launch
+        std::map<std::tuple<int, int, int, int, int>, int64_t> group_tiles;  // tiles of each launch
         auto group_of = [](const pic_box* b) {
             return std::make_tuple(b->dim, b->tile[0], b->tile[1], b->tile[2], b->d.frame);
         };
-        for (int i = 0; i < nb; i++) group_rounds[group_of(boxes[i])] += rounds_of(boxes[i]);
+        for (int i = 0; i < nb; i++) group_tiles[group_of(boxes[i])] += boxes[i]->tl.n_tiles;
         for (int i = 0; i < nb; i++) {
             pic_box* b = boxes[i];
             for (int c = 0; c < 3; c++) {
@@ -1046,7 +1044,7 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             auto& gr = groups[group_of(b)];
             StepDev P = make_step(b);
             P.mig_latch = 1;  // no radix fallback behind a batched sort
-            P.lsplit = tile_split(b->dim, group_rounds[group_of(b)], slots_per_tile(b));
+            P.lsplit = tile_split(b->dim, group_tiles[group_of(b)], slots_per_tile(b));
             gr.first.push_back(P);
             gr.second.push_back((uint32_t)b->tl.n_tiles << P.lsplit);
             for (int s = 0; s < b->nsp; s++) {
@@ -1073,45 +1071,28 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
         }
     }
 
-    // ---- a7: current fold (z, y periodic; J' transport and shearing-periodic x, or periodic x)
+    // ---- a7: current fold (periodic; or with the J' transport and shearing-periodic in x)
     {
-        std::vector<FoldPArgs> fz, fy;
+        std::vector<FoldPArgs> fp;
         std::vector<ShearFoldArgs> adv;
-        std::vector<FoldXArgs> fx;
-        std::vector<uint32_t> fzb, fyb, advb, fxb;
+        std::vector<uint32_t> fpb, advb;
         for (int i = 0; i < nb; i++) {
             pic_box* b = boxes[i];
             const GridDev& G = b->G;
-            const Comp3 Jc{{b->J[0], b->J[1], b->J[2]}};
-            const int NXg = G.n[0] + 2 * G.g[0], NYg = G.n[1] + 2 * G.g[1];
-            if (G.g[2] > 0) {
-                const int nl = G.n[2] < 2 * G.g[2] ? G.n[2] : 2 * G.g[2];
-                fz.push_back(FoldPArgs{G, Jc, 2});
-                fzb.push_back(grid_blocks((int64_t)NXg * NYg * nl));
-            }
-            const int nly = G.n[1] < 2 * G.g[1] ? G.n[1] : 2 * G.g[1];
-            fy.push_back(FoldPArgs{G, Jc, 1});
-            fyb.push_back(grid_blocks((int64_t)NXg * nly * G.n[2]));
-            const double th = time_of(b, b->step) + 0.5 * b->d.dt;
-            if (sheared(&b->d)) {
-                // transport + x fold from J into the second array, which then becomes the
-                // current (the later stages of this step are planned with the swapped arrays)
-                const double dh = shear_offset(b, th), fl = std::floor(dh);
-                const Comp3 Tc{{b->Jt[0], b->Jt[1], b->Jt[2]}};
-                adv.push_back(ShearFoldArgs{G, Jc, Tc, (float)(b->d.shear_s * b->d.shear_omega0 * b->d.dt / 2.0),
-                                            0.5f * G.n[0], (int)fl, (float)(dh - fl)});
-                advb.push_back(grid_blocks((int64_t)G.n[0] * G.n[1] * G.n[2]));
-                for (int c = 0; c < 3; c++) std::swap(b->J[c], b->Jt[c]);
-            } else {
-                const int nlx = G.n[0] < 2 * G.g[0] ? G.n[0] : 2 * G.g[0];
-                fx.push_back(FoldXArgs{G, Jc, Jc, 0, 0, 0, 0.f});
-                fxb.push_back(grid_blocks((int64_t)nlx * G.n[1] * G.n[2]));
-            }
+            fp.push_back(fold_args(G, b->J, sheared(&b->d) ? 1 : 0));
+            fpb.push_back(fold_blocks(fp.back()));
+            if (!sheared(&b->d)) continue;
+            // transport + folds from J into the second array, which then becomes the current (the
+            // later stages of this step are planned with the swapped arrays)
+            const double th = time_of(b, b->step) + 0.5 * b->d.dt, dh = shear_offset(b, th), fl = std::floor(dh);
+            const Comp3 Jc{{b->J[0], b->J[1], b->J[2]}}, Tc{{b->Jt[0], b->Jt[1], b->Jt[2]}};
+            adv.push_back(ShearFoldArgs{G, Jc, Tc, (float)(b->d.shear_s * b->d.shear_omega0 * b->d.dt / 2.0),
+                                        0.5f * G.n[0], (int)fl, (float)(dh - fl)});
+            advb.push_back(grid_blocks((int64_t)G.n[0] * G.n[1] * G.n[2]));
+            for (int c = 0; c < 3; c++) std::swap(b->J[c], b->Jt[c]);
         }
-        plan.grid(kBatchFoldP, fz, fzb, 3);
-        plan.grid(kBatchFoldP, fy, fyb, 3);
+        plan.grid(kBatchFoldP, fp, fpb, 3);
         plan.grid(kBatchShearFold, adv, advb, 3);
-        plan.grid(kBatchFoldX, fx, fxb, 3);
     }
 
     // ---- a9: Maxwell (Yee with the expanding-box factors; shearing-box fixed-point sweeps)

@@ -9,8 +9,6 @@
 // Particles are read through the sort permutation and written in sorted slot order, so the
 // tile sort's scatter is fused into this pass.  A particle found outside its tile (only
 // possible without a sort since the last push) takes the global-memory path.
-#include <algorithm>
-
 #include "pic_internal.h"
 
 namespace pic {
@@ -881,23 +879,17 @@ template <int DIM>
 constexpr int threads_for() { return DIM == 3 ? 512 : 256; }
 
 // A tile's workgroup walks its particles a round of NT slots after another, each round waiting for
-// its loads (3 to 5 us), so a launch of few or uneven tiles is bound by its longest chain on an idle
-// chip.  Tiles are split until a part's rounds of a species are no more than the launch's rounds
-// shared out to the workgroups that the chip holds (three a CU in 3D, eight in 2D), but not below
-// one round: more parts only add their staging and flush.  The 64^2 box of the parity tests (16 tiles
-// of 4096 slots a species): 84 us whole, 19 us in 256 workgroups; 20 x 12 x 16 cells: 32 -> 28 us.
-int tile_split(int dim, int64_t rounds, int64_t slots_per_tile)
+// its loads (3 to 5 us), so a box of few tiles is bound by that chain on an idle chip.  Its tiles are
+// split until the launch has two (3D) or four (2D) workgroups a CU, as long as a part keeps a
+// whole round of a species: more parts only add their staging and flush (four parts a tile instead of
+// two made the 384^2 box's push slower, 75 -> 84 us).  The 64^2 box of the parity tests (16 tiles of 4096
+// slots a species): 84 us whole, 19 us in 256 workgroups; 20 x 12 x 16 cells: 32 -> 28 us.
+int tile_split(int dim, int64_t n_tiles, int64_t slots_per_tile)
 {
-    const int64_t nt = dim == 3 ? threads_for<3>() : threads_for<2>(), held = dim == 3 ? 3 * 256 : 8 * 256;
-    const int64_t most = std::max<int64_t>(1, rounds / held);
+    const int64_t want = dim == 3 ? 512 : 1024, nt = dim == 3 ? threads_for<3>() : threads_for<2>();
     int l = 0;
-    while (l < 6 && (slots_per_tile >> l) > nt * most) l++;
+    while (l < 6 && (n_tiles << l) < want && (slots_per_tile >> l) > nt) l++;
     return l;
-}
-int64_t tile_rounds(int dim, int64_t n_tiles, int64_t slots_per_tile)
-{
-    const int64_t nt = dim == 3 ? threads_for<3>() : threads_for<2>();
-    return n_tiles * ((slots_per_tile + nt - 1) / nt);
 }
 
 template <int DIM, int TX, int TY, int TZ>

@@ -110,47 +110,6 @@ PIC_BATCHED_KERNEL(fill_guards, FillArgs, kBlock)
 
 // ------------------------------------------------------------------ current fold
 
-// Periodic fold along axis a (1 = y, 2 = z) over the whole guarded extent of the axes before
-// it (x and, for z, y) and the interior of the others.
-__device__ __attribute__((always_inline)) inline void fold_periodic_body(const FoldPArgs& args, int blk, int, int c)
-{
-    const GridDev& G = args.G;
-    const int a = args.axis;
-    float* F = args.J.p[c];
-    const int64_t t = (int64_t)blk * kBlock + threadIdx.x;
-    const int gx = G.g[0], gy = G.g[1];
-    const int NXg = G.n[0] + 2 * gx, NYg = G.n[1] + 2 * gy;
-    const int na = G.n[a], ga = G.g[a];
-    const int nl = na < 2 * ga ? na : 2 * ga;  // boundary layers that receive
-    int x, y, z, m;
-    if (a == 2) {
-        const int64_t tot = (int64_t)NXg * NYg * nl;
-        if (t >= tot) return;
-        x = (int)(t % NXg) - gx;
-        int64_t r = t / NXg;
-        y = (int)(r % NYg) - gy;
-        m = (int)(r / NYg);
-        z = m < ga ? m : na - (m - ga) - 1;
-        if (m >= ga && z < ga) return;  // a small axis: layer already handled
-    } else {
-        const int64_t tot = (int64_t)NXg * nl * G.n[2];
-        if (t >= tot) return;
-        x = (int)(t % NXg) - gx;
-        int64_t r = t / NXg;
-        m = (int)(r % nl);
-        z = (int)(r / nl);
-        y = m < ga ? m : na - (m - ga) - 1;
-        if (m >= ga && y < ga) return;
-    }
-    const int i = a == 2 ? z : y;
-    float v = 0.f;
-    int64_t self = gidx(G, x, y, z);
-    if (i < ga) v += F[self + (int64_t)na * (a == 2 ? G.sz : G.sy)];
-    if (i >= na - ga) v += F[self - (int64_t)na * (a == 2 ? G.sz : G.sy)];
-    F[self] += v;
-}
-PIC_BATCHED_KERNEL(fold_periodic, FoldPArgs, kBlock)
-
 // interior coordinates of linear interior index t = x + n0 (y + n1 z) (below 2^31)
 __device__ inline void cell_of(const GridDev& G, int64_t t, int& x, int& y, int& z)
 {
@@ -214,61 +173,59 @@ __device__ __attribute__((always_inline)) inline void shear_fold_body(const Shea
 }
 PIC_BATCHED_KERNEL(shear_fold, ShearFoldArgs, kBlock)
 
-// x fold as a gather into interior cells: out(i) = in(i) plus the x guard columns that map
-// to i (periodic, or shearing-periodic at dys as the transpose of the guard interpolation).
-// Runs over all interior cells when in != out, else over the boundary layers only.
-__device__ __attribute__((always_inline)) inline void fold_x_body(const FoldXArgs& a, int blk, int, int c)
+// Periodic fold in place: the cells of the first and last two layers of each axis take the guard
+// cells that map onto them, in the order z, y, x.  A cell reads guards and itself and writes itself,
+// so the axes are one launch (two and three before).  With the x fold the cells are the interior's;
+// without it (the shearing box folds x with its transport) those of every guarded column.
+// An axis has at most one image of a cell (it has four cells or more): all images are loaded at
+// once, those that a cell has not at its own place, and the sums selected.
+__device__ __attribute__((always_inline)) inline void fold_periodic_body(const FoldPArgs& a, int blk, int, int c)
 {
     const GridDev& G = a.G;
-    const Comp3& Jin = a.in;
-    const Comp3& Jout = a.out;
-    const int all = a.all, shear = a.shear, dys_int = a.dys_int;
-    const float dys_w = a.dys_w;
-    const int64_t t = (int64_t)blk * kBlock + threadIdx.x;
-    const int nx = G.n[0], ga = G.g[0];
-    const int nl = all ? nx : (nx < 2 * ga ? nx : 2 * ga);
-    const int64_t tot = (int64_t)nl * G.n[1] * G.n[2];
-    if (t >= tot) return;
-    int m = (int)(t % nl);
-    const int64_t r = t / nl;
-    const int y = (int)(r % G.n[1]);
-    const int z = (int)(r / G.n[1]);
-    int x;
-    if (all) {
-        x = m;
+    float* F = a.J.p[c];
+    constexpr uint32_t g2 = 2 * kGuard;
+    const int nx = G.n[0], ny = G.n[1], nz = G.n[2];
+    uint32_t t = (uint32_t)blk * kBlock + threadIdx.x;
+    auto layer = [](uint32_t m, int n) { return m < kGuard ? (int)m : n - (int)g2 + (int)m; };
+    int x, y, z = 0;
+    if (t < a.n[0]) {  // x layers: every y, z
+        const uint32_t r = t / g2;
+        x = layer(t % g2, nx);
+        z = (int)G.div1.div(r);
+        y = (int)(r - (uint32_t)z * (uint32_t)ny);
     } else {
-        x = m < ga ? m : nx - (m - ga) - 1;
-        if (m >= ga && x < ga) return;
-    }
-    const float* F = Jin.p[c];
-    float v = F[gidx(G, x, y, z)];
-    if (x < ga) {  // receives guard column x + nx, the image of (x, y + dys)
-        if (shear) {
-            // guard (nx+x, j) adds (1-w) to (x, j + js) and w to (x, j + js + 1), js = dys_int
-            v += (1.f - dys_w) * F[gidx(G, x + nx, wrapn(y - dys_int, G.n[1]), z)] +
-                 dys_w * F[gidx(G, x + nx, wrapn(y - dys_int - 1, G.n[1]), z)];
+        t -= a.n[0];
+        const bool yl = t < a.n[1];
+        if (!yl && (t -= a.n[1]) >= a.n[2]) return;
+        const uint32_t r = t / a.wx;
+        x = a.x0 + (int)(t - r * a.wx);
+        if (yl) {
+            y = layer(r % g2, ny);
+            z = (int)(r / g2);
         } else {
-            v += F[gidx(G, x + nx, y, z)];
+            const uint32_t iny = (uint32_t)(ny - (int)g2), q = r / iny;
+            y = kGuard + (int)(r - q * iny);
+            z = layer(q, nz);
         }
     }
-    if (x >= nx - ga) {  // receives guard column x - nx, the image of (x, y - dys)
-        if (shear) {
-            // shift -dys = js' + w' with js' = -dys_int - 1, w' = 1 - w (w > 0), else -dys_int
-            int js = -dys_int;
-            float w = 0.f;
-            if (dys_w > 0.f) {
-                js = -dys_int - 1;
-                w = 1.f - dys_w;
-            }
-            v += (1.f - w) * F[gidx(G, x - nx, wrapn(y - js, G.n[1]), z)] +
-                 w * F[gidx(G, x - nx, wrapn(y - js - 1, G.n[1]), z)];
-        } else {
-            v += F[gidx(G, x - nx, y, z)];
+    auto image = [](int i, int n, int s) -> int64_t {
+        return i < kGuard ? (int64_t)n * s : (i >= n - kGuard ? -(int64_t)n * s : 0);
+    };
+    const int64_t i = gidx(G, x, y, z), iy = image(y, ny, G.sy);
+    const int64_t ix = a.n[0] ? image(x, nx, 1) : 0, iz = G.dim == 3 ? image(z, nz, G.sz) : 0;
+    float v[2][2];
+#pragma unroll
+    for (int k = 0; k < 2; k++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            const float* p = F + i + (k ? ix : 0) + (j ? iy : 0);
+            const float own = p[0], img = p[iz];
+            v[k][j] = iz ? own + img : own;
         }
-    }
-    Jout.p[c][gidx(G, x, y, z)] = v;
+    const float v0 = iy ? v[0][0] + v[0][1] : v[0][0], v1 = iy ? v[1][0] + v[1][1] : v[1][0];
+    F[i] = ix ? v0 + v1 : v0;
 }
-PIC_BATCHED_KERNEL(fold_x, FoldXArgs, kBlock)
+PIC_BATCHED_KERNEL(fold_periodic, FoldPArgs, kBlock)
 
 // ------------------------------------------------------------------ Maxwell
 // Yee curls (c = 1, dx = 1).  E_j and B_j enter multiplied by ge[j], gb[j] (the l_j of the
@@ -1367,35 +1324,34 @@ hipError_t fill_guards(const GridDev& G, float* const* comps, int ncomp, int she
     return hipGetLastError();
 }
 
-// Fold the deposited current.  For the shearing box tmp receives the transported current and
-// the fold writes every interior cell of J.
+FoldPArgs fold_args(const GridDev& G, float* const* J, int shear)
+{
+    FoldPArgs a{};
+    a.G = G;
+    for (int c = 0; c < 3; c++) a.J.p[c] = J[c];
+    const uint32_t g2 = 2 * kGuard, nx = G.n[0], ny = G.n[1], nz = G.n[2];
+    a.x0 = shear ? -kGuard : kGuard;
+    a.wx = shear ? nx + g2 : nx - g2;
+    a.n[0] = shear ? 0 : g2 * ny * nz;
+    a.n[1] = a.wx * g2 * nz;
+    a.n[2] = G.dim == 3 ? a.wx * (ny - g2) * g2 : 0;
+    return a;
+}
+unsigned fold_blocks(const FoldPArgs& a) { return nblocks((int64_t)a.n[0] + a.n[1] + a.n[2]); }
+
+// Fold the deposited current: in place, or for the shearing box into `out`, every interior cell.
 hipError_t fold_current(const GridDev& G, float* const* J, float* const* out, int shear,
                         double sO, double dt, double dys_half, hipStream_t st)
 {
-    Comp3 Jc{{J[0], J[1], J[2]}};
-    const int NXg = G.n[0] + 2 * G.g[0], NYg = G.n[1] + 2 * G.g[1];
-    if (G.g[2] > 0) {
-        const int nl = G.n[2] < 2 * G.g[2] ? G.n[2] : 2 * G.g[2];
-        fold_periodic_kernel<<<dim3(nblocks((int64_t)NXg * NYg * nl), 3), kBlock, 0, st>>>(
-            FoldPArgs{G, Jc, 2});
-    }
-    {
-        const int nl = G.n[1] < 2 * G.g[1] ? G.n[1] : 2 * G.g[1];
-        fold_periodic_kernel<<<dim3(nblocks((int64_t)NXg * nl * G.n[2]), 3), kBlock, 0, st>>>(
-            FoldPArgs{G, Jc, 1});
-    }
-    const double fl = floor(dys_half);
-    const int di = (int)fl;
-    const float w = (float)(dys_half - fl);
+    const Comp3 Jc{{J[0], J[1], J[2]}};
+    const FoldPArgs a = fold_args(G, J, shear);
+    fold_periodic_kernel<<<dim3(fold_blocks(a), 3), kBlock, 0, st>>>(a);
     if (shear) {
-        Comp3 Oc{{out[0], out[1], out[2]}};
+        const double fl = floor(dys_half);
+        const Comp3 Oc{{out[0], out[1], out[2]}};
         const unsigned nb = std::min(nblocks((int64_t)G.n[0] * G.n[1] * G.n[2]), kStrideBlocks);
         shear_fold_kernel<<<dim3(nb, 3), kBlock, 0, st>>>(
-            ShearFoldArgs{G, Jc, Oc, (float)(sO * dt / 2.0), 0.5f * G.n[0], di, w});
-    } else {
-        const int nl = G.n[0] < 2 * G.g[0] ? G.n[0] : 2 * G.g[0];
-        fold_x_kernel<<<dim3(nblocks((int64_t)nl * G.n[1] * G.n[2]), 3), kBlock, 0, st>>>(
-            FoldXArgs{G, Jc, Jc, 0, 0, 0, 0.f});
+            ShearFoldArgs{G, Jc, Oc, (float)(sO * dt / 2.0), 0.5f * G.n[0], (int)fl, (float)(dys_half - fl)});
     }
     return hipGetLastError();
 }
@@ -1496,7 +1452,6 @@ hipError_t grid_batch(GridBatchKind k, const void* table, UnitMap m, int blocks,
     case kBatchShearFold:
         shear_fold_batch<<<grid, kBlock, 0, st>>>(static_cast<const ShearFoldArgs*>(table), m);
         break;
-    case kBatchFoldX: fold_x_batch<<<grid, kBlock, 0, st>>>(static_cast<const FoldXArgs*>(table), m); break;
     case kBatchYeeB: yee_b_batch<<<grid, kBlock, 0, st>>>(static_cast<const MaxwellDev*>(table), m); break;
     case kBatchYeeE: yee_e_batch<<<grid, kBlock, 0, st>>>(static_cast<const MaxwellDev*>(table), m); break;
     case kBatchKsbFirst:

@@ -311,22 +311,18 @@ struct FillArgs {  // guard fill of ncomp = gridDim.y arrays
     float dys_w;
     uint32_t n[3];  // guard cells of the x, y and z slabs
 };
-struct FoldPArgs {  // periodic current fold along axis 1 (y) or 2 (z)
+struct FoldPArgs {  // periodic current fold, in place
     GridDev G;
     Comp3 J;
-    int axis;
+    uint32_t n[3];  // cells of the x layers, of the y layers and of the z layers, each without the former
+    int x0;         // columns x0 .. x0 + wx - 1 of the y and z layers
+    uint32_t wx;
 };
 struct ShearFoldArgs {  // J' transport along y and shearing-periodic x fold, in -> out
     GridDev G;
     Comp3 in, out;
     float sO_hdt, half_nx;
     int dys_int;
-    float dys_w;
-};
-struct FoldXArgs {  // x fold (periodic or shearing-periodic)
-    GridDev G;
-    Comp3 in, out;
-    int all, shear, dys_int;
     float dys_w;
 };
 // What a push starts from: the current arrays (n words each), the fallback flags and, for split
@@ -433,10 +429,9 @@ struct MigPair {
 
 // ---- launchers (gpd.hip, sort.hip, grid.hip, xfer.hip)
 bool tile_shape_supported(int dim, const int t[3]);
-// log2 of the workgroups per tile of a box whose tiles hold slots_per_tile slots of the fuller species
-// on average, in a push or deposit launch over `rounds` rounds (tile_rounds of all its boxes)
-int tile_split(int dim, int64_t rounds, int64_t slots_per_tile);
-int64_t tile_rounds(int dim, int64_t n_tiles, int64_t slots_per_tile);
+// log2 of the workgroups per tile of a push or deposit launch over n_tiles tiles (of all its boxes),
+// for a box with slots_per_tile slots of the fuller species a tile on average
+int tile_split(int dim, int64_t n_tiles, int64_t slots_per_tile);
 // supported tile shapes (batched: those of the batched launch); the default shape comes first
 int tile_candidates(int dim, bool batched, int (*out)[3], int max);
 hipError_t launch_gather_push(const StepDev& P, const int t[3], int fuse, hipStream_t st);
@@ -470,7 +465,7 @@ struct ScaleArgs {
     float f[3];
 };
 enum GridBatchKind {
-    kBatchZero, kBatchFill, kBatchFoldP, kBatchShearFold, kBatchFoldX, kBatchYeeB, kBatchYeeE,
+    kBatchZero, kBatchFill, kBatchFoldP, kBatchShearFold, kBatchYeeB, kBatchYeeE,
     kBatchKsbFirst, kBatchKsbNext, kBatchKsbFinal, kBatchScale
 };
 hipError_t grid_batch(GridBatchKind k, const void* table, UnitMap m, int blocks, int ydim,
@@ -484,9 +479,11 @@ FillArgs fill_args(const GridDev& G, float* const* comps, int ncomp, int shear, 
 unsigned fill_blocks(const FillArgs& a);
 hipError_t fill_guards(const GridDev& G, float* const* comps, int ncomp, int shear, double dys,
                        hipStream_t st);
-// Fold the current guards (y, z periodic in place).  Shearing box: the J' transport and the
+// Fold the current guards (y, z periodic).  Shearing box: with the J' transport and the
 // shearing-periodic x fold in one pass from J into `out` (the caller then swaps the two arrays);
-// otherwise the periodic x fold in place.
+// otherwise periodic in place.
+FoldPArgs fold_args(const GridDev& G, float* const* J, int shear);
+unsigned fold_blocks(const FoldPArgs& a);
 hipError_t fold_current(const GridDev& G, float* const* J, float* const* out, int shear,
                         double sO, double dt, double dys_half, hipStream_t st);
 hipError_t yee_b(const MaxwellDev& M, hipStream_t st);

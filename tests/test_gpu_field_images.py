@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import oracle
-from _cases import FRAMES, random_fields
+from _cases import FRAMES, Case, random_fields
 from paper_2602_15939_amd.box import Box, step_many
 
 pytestmark = pytest.mark.gpu
@@ -48,3 +48,19 @@ def test_field_step_against_oracle(frame, n, batched):
             assert np.abs(g.cpu().numpy() - o).max() <= 1e-5 * np.abs(o).max()
     finally:
         b.close()
+
+
+@pytest.mark.parametrize("frame", ["plain", "shear"])
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("batched", [False, True])
+def test_folded_current_against_oracle(frame, n, batched):
+    """Grids whose cells are boundary layers of every axis, some of both ends of a wave: the current of
+    a step after the fold of the guards along the three axes."""
+    c = Case(len(n), n, frame, ppc=6, seed=8, omega0=0.02, maxwell_iters=2)
+    try:
+        step_many([c.gpu], batched=batched)
+        c.oracle_step()
+        J = c.gpu.get_current().cpu().numpy()
+        assert np.abs(J - c.J).max() <= 1e-5 * np.abs(c.J).max()
+    finally:
+        c.close()
