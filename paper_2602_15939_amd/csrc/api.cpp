@@ -145,7 +145,7 @@ struct pic_box {
     uint32_t* conv = nullptr;  // shearing box: convergence record of the tolerance-mode sweeps
     int last_sweeps = 0;       // sweeps of the last Maxwell step (-1: the device record has it)
     double* red_part = nullptr;
-    double* red_out = nullptr;
+    BoxRecord* record = nullptr;
     double* hist_edges = nullptr;               // energy histogram: edges ...
     unsigned long long* hist_counts = nullptr;  // ... and counts
     int64_t step = 0;
@@ -616,6 +616,21 @@ int32_t deposit_box(pic_box* b)
     if (launch_deposit(P, b->tile, b->st) != hipSuccess) return PIC_EDEVICE;
     b->deposit_pending = false;
     return PIC_OK;
+}
+
+// a species' current arrays (ids and displacements where carried)
+Particles particles_of(const pic_box* b, const Species& S)
+{
+    const int k = S.cur;
+    Particles p{};
+    p.cell = S.cell[k];
+    for (int c = 0; c < 3; c++) {
+        p.off[c] = S.off[k][c];
+        p.u[c] = S.u[k][c];
+        p.dr[c] = S.dr[k][c];
+    }
+    p.id = b->track_ids ? S.id[k] : nullptr;
+    return p;
 }
 
 float* const* field_ptrs(pic_box* b) { return b->set[b->cur_set]; }
@@ -1537,8 +1552,8 @@ int32_t alloc_all(pic_box* b, const pic_box_mem* m)
     if (!r) r = dalloc(b, b->err, 4);
     if (!r) r = dalloc(b, b->ctr, 4);
     if (!r && sheared(d)) r = dalloc(b, b->conv, kKsbConvWords);
-    if (!r) r = dalloc(b, b->red_part, (size_t)10 * kRedBlocks);
-    if (!r) r = dalloc(b, b->red_out, 16);
+    if (!r) r = dalloc(b, b->red_part, (size_t)(6 + kPartSums * kMaxSpecies) * kRedBlocks);
+    if (!r) r = dalloc(b, b->record, 1);
     if (!r) r = dalloc(b, b->hist_edges, kHistMaxBins + 1);
     if (!r) r = dalloc(b, b->hist_counts, kHistMaxBins + 2);
     if (!r && escapes(d) && d->leaky_mode == PIC_LEAKY_DISPLACEMENT)
@@ -1697,12 +1712,14 @@ int32_t pic_set_fields(pic_box* b, const float* E, const float* B)
 {
     if (!b || !E || !B) return PIC_EINVAL;
     const int64_t nc = (int64_t)b->n[0] * b->n[1] * b->n[2];
+    float *own[6], *dense[6];
     for (int c = 0; c < 3; c++) {
-        if (interior_copy(b->G, b->E(c), const_cast<float*>(E) + c * nc, 0, b->st) != hipSuccess)
-            return PIC_EDEVICE;
-        if (interior_copy(b->G, b->B(c), const_cast<float*>(B) + c * nc, 0, b->st) != hipSuccess)
-            return PIC_EDEVICE;
+        own[c] = b->B(c);
+        own[3 + c] = b->E(c);
+        dense[c] = const_cast<float*>(B) + c * nc;
+        dense[3 + c] = const_cast<float*>(E) + c * nc;
     }
+    if (interior_copy(b->G, own, dense, 6, 0, b->st) != hipSuccess) return PIC_EDEVICE;
     return fill_field_guards(b, time_of(b, b->step));
 }
 
@@ -1710,10 +1727,19 @@ int32_t pic_get_fields(pic_box* b, float* E, float* B)
 {
     if (!b) return PIC_EINVAL;
     const int64_t nc = (int64_t)b->n[0] * b->n[1] * b->n[2];
+    float *own[6], *dense[6];
+    int m = 0;
     for (int c = 0; c < 3; c++) {
-        if (E && interior_copy(b->G, b->E(c), E + c * nc, 1, b->st) != hipSuccess) return PIC_EDEVICE;
-        if (B && interior_copy(b->G, b->B(c), B + c * nc, 1, b->st) != hipSuccess) return PIC_EDEVICE;
+        if (E) {
+            own[m] = b->E(c);
+            dense[m++] = E + c * nc;
+        }
+        if (B) {
+            own[m] = b->B(c);
+            dense[m++] = B + c * nc;
+        }
     }
+    if (interior_copy(b->G, own, dense, m, 1, b->st) != hipSuccess) return PIC_EDEVICE;
     return hip_fail(hipStreamSynchronize(b->st));
 }
 
@@ -1721,8 +1747,8 @@ int32_t pic_get_current(pic_box* b, float* J)
 {
     if (!b || !J) return PIC_EINVAL;
     const int64_t nc = (int64_t)b->n[0] * b->n[1] * b->n[2];
-    for (int c = 0; c < 3; c++)
-        if (interior_copy(b->G, b->J[c], J + c * nc, 1, b->st) != hipSuccess) return PIC_EDEVICE;
+    float* dense[3] = {J, J + nc, J + 2 * nc};
+    if (interior_copy(b->G, b->J, dense, 3, 1, b->st) != hipSuccess) return PIC_EDEVICE;
     return hip_fail(hipStreamSynchronize(b->st));
 }
 
@@ -1733,35 +1759,9 @@ int32_t pic_set_particles(pic_box* b, int32_t s, int64_t n, const int32_t* cell,
     if (side_join(b)) return PIC_EDEVICE;
     Species& S = b->sp[s];
     if (n > S.cap) return PIC_ECAP;
-    hipStream_t st = b->st;
-    const int k = S.cur;
-    if (cells_linear_to_packed(cell, S.cell[k], n, b->n, b->cc, b->err, st) != hipSuccess) return PIC_EDEVICE;
-    const size_t fb = sizeof(float) * (size_t)n;
-    for (int c = 0; c < b->dim; c++)
-        if (n && hipMemcpyAsync(S.off[k][c], off + c * n, fb, hipMemcpyDeviceToDevice, st) != hipSuccess)
-            return PIC_EDEVICE;
-    for (int c = 0; c < 3; c++)
-        if (n && hipMemcpyAsync(S.u[k][c], u + c * n, fb, hipMemcpyDeviceToDevice, st) != hipSuccess)
-            return PIC_EDEVICE;
-    if (b->track_ids) {
-        if (id) {
-            if (n && hipMemcpyAsync(S.id[k], id, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, st) != hipSuccess)
-                return PIC_EDEVICE;
-        } else if (iota_u32(S.id[k], n, st) != hipSuccess) {
-            return PIC_EDEVICE;
-        }
-    }
-    if (S.dr[k][0]) {
-        for (int c = 0; c < 3; c++) {
-            if (dr) {
-                if (n && hipMemcpyAsync(S.dr[k][c], dr + c * n, fb, hipMemcpyDeviceToDevice, st) != hipSuccess)
-                    return PIC_EDEVICE;
-            } else if (zero_floats(S.dr[k][c], n, st) != hipSuccess) {
-                return PIC_EDEVICE;
-            }
-        }
-    }
-    if (set_i32(S.n_live, (int32_t)n, st) != hipSuccess) return PIC_EDEVICE;
+    if (particles_in(particles_of(b, S), n, cell, off, u, id, dr, b->dim, b->G, b->cc, S.n_live, b->err, b->st) !=
+        hipSuccess)
+        return PIC_EDEVICE;
     b->record_valid = false;
     S.n_upper = (int)n;
     S.grouped = false;
@@ -1776,31 +1776,16 @@ int32_t pic_get_particles(pic_box* b, int32_t s, int64_t* n_out, int32_t* cell, 
     if (!b || s < 0 || s >= b->nsp) return PIC_EINVAL;
     if (side_join(b)) return PIC_EDEVICE;
     Species& S = b->sp[s];
+    // the z displacement is tracked only with the 3-vector escape test: 0 otherwise
+    const Particles from = particles_of(b, S);
     int32_t n = 0;
-    if (hipMemcpyAsync(&n, S.n_live, sizeof(int32_t), hipMemcpyDeviceToHost, b->st) != hipSuccess ||
+    if (particles_out(from, S.n_live, S.n_upper, cell, off, u, from.id ? id : nullptr, from.dr[0] ? dr : nullptr, b->dim,
+                      b->d.leaky_use_3vec ? 3 : 2, b->G, b->cc, b->st) != hipSuccess ||
+        hipMemcpyAsync(&n, S.n_live, sizeof(int32_t), hipMemcpyDeviceToHost, b->st) != hipSuccess ||
         hipStreamSynchronize(b->st) != hipSuccess)
         return PIC_EDEVICE;
     if (n_out) *n_out = n;
-    const int k = S.cur;
-    hipStream_t st = b->st;
-    const size_t fb = sizeof(float) * (size_t)n;
-    if (cell && cells_packed_to_linear(S.cell[k], cell, n, b->n, b->cc, st) != hipSuccess) return PIC_EDEVICE;
-    for (int c = 0; c < b->dim && off; c++)
-        if (n && hipMemcpyAsync(off + c * n, S.off[k][c], fb, hipMemcpyDeviceToDevice, st) != hipSuccess)
-            return PIC_EDEVICE;
-    for (int c = 0; c < 3 && u; c++)
-        if (n && hipMemcpyAsync(u + c * n, S.u[k][c], fb, hipMemcpyDeviceToDevice, st) != hipSuccess)
-            return PIC_EDEVICE;
-    if (id && b->track_ids && n &&
-        hipMemcpyAsync(id, S.id[k], sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, st) != hipSuccess)
-        return PIC_EDEVICE;
-    // the z displacement is tracked only with the 3-vector escape test: 0 otherwise
-    const int ndr = b->d.leaky_use_3vec ? 3 : 2;
-    for (int c = 0; c < ndr && dr && S.dr[k][0]; c++)
-        if (n && hipMemcpyAsync(dr + c * n, S.dr[k][c], fb, hipMemcpyDeviceToDevice, st) != hipSuccess)
-            return PIC_EDEVICE;
-    if (dr && S.dr[k][0] && ndr == 2 && zero_floats(dr + 2 * n, n, st) != hipSuccess) return PIC_EDEVICE;
-    return hip_fail(hipStreamSynchronize(st));
+    return PIC_OK;
 }
 
 int32_t pic_get_sort(pic_box* b, int32_t s, int32_t* perm, int32_t* offsets, int32_t* n_tiles_out)
@@ -1830,21 +1815,20 @@ int32_t pic_get_push_record(pic_box* b, int32_t s, int64_t* n_out, int32_t* cell
     if (side_join(b)) return PIC_EDEVICE;
     if (!b->record_valid) return PIC_ESTATE;
     Species& S = b->sp[s];
+    Particles from{};
+    from.cell = S.ws_cell;
+    for (int c = 0; c < 3; c++) {
+        from.off[c] = S.ws_off[c];
+        from.u[c] = S.ws_disp[c];
+    }
     int32_t n = 0;
-    if (hipMemcpyAsync(&n, S.n_live, sizeof(int32_t), hipMemcpyDeviceToHost, b->st) != hipSuccess ||
+    if (particles_out(from, S.n_live, S.n_upper, cell, off, disp, nullptr, nullptr, b->dim, 0, b->G, b->cc, b->st) !=
+            hipSuccess ||
+        hipMemcpyAsync(&n, S.n_live, sizeof(int32_t), hipMemcpyDeviceToHost, b->st) != hipSuccess ||
         hipStreamSynchronize(b->st) != hipSuccess)
         return PIC_EDEVICE;
     if (n_out) *n_out = n;
-    hipStream_t st = b->st;
-    const size_t fb = sizeof(float) * (size_t)n;
-    if (cell && cells_packed_to_linear(S.ws_cell, cell, n, b->n, b->cc, st) != hipSuccess) return PIC_EDEVICE;
-    for (int c = 0; c < b->dim && off; c++)
-        if (n && hipMemcpyAsync(off + c * n, S.ws_off[c], fb, hipMemcpyDeviceToDevice, st) != hipSuccess)
-            return PIC_EDEVICE;
-    for (int c = 0; c < 3 && disp; c++)
-        if (n && hipMemcpyAsync(disp + c * n, S.ws_disp[c], fb, hipMemcpyDeviceToDevice, st) != hipSuccess)
-            return PIC_EDEVICE;
-    return hip_fail(hipStreamSynchronize(st));
+    return PIC_OK;
 }
 
 int32_t pic_tile_sort(pic_box* const* boxes, int32_t nb, uint32_t flags)
@@ -2108,8 +2092,8 @@ int32_t pic_energy_histogram(pic_box* b, int32_t s, const double* edges, int32_t
     const int k = S.cur;
     if (hipMemcpyAsync(b->hist_edges, edges, sizeof(double) * (nbins + 1), hipMemcpyHostToDevice, st) !=
             hipSuccess ||
-        energy_histogram(S.cell[k], S.u[k][0], S.u[k][1], S.u[k][2], S.n_live, b->hist_edges, nbins,
-                         b->hist_counts, kRedBlocks, st) != hipSuccess ||
+        energy_histogram(escapes(&b->d) ? S.cell[k] : nullptr, S.u[k][0], S.u[k][1], S.u[k][2], S.n_live, b->hist_edges, nbins,
+                         b->hist_counts, st) != hipSuccess ||
         hipMemcpyAsync(counts, b->hist_counts, sizeof(uint64_t) * (nbins + 2), hipMemcpyDeviceToHost, st) !=
             hipSuccess)
         return PIC_EDEVICE;
@@ -2138,8 +2122,8 @@ int32_t pic_energy_histogram_static(pic_box* b, int32_t s, const double* edges, 
     // scratch keeps the last call's contents)
     if (hipMemcpyAsync(dev_edges, edges, sizeof(double) * (nbins + 1), hipMemcpyHostToDevice, st) !=
             hipSuccess ||
-        energy_histogram(S.cell[k], S.u[k][0], S.u[k][1], S.u[k][2], S.n_live, dev_edges, nbins,
-                         dev_counts, kRedBlocks, st) != hipSuccess ||
+        energy_histogram(escapes(&b->d) ? S.cell[k] : nullptr, S.u[k][0], S.u[k][1], S.u[k][2], S.n_live, dev_edges, nbins,
+                         dev_counts, st) != hipSuccess ||
         hipMemcpyAsync(counts, dev_counts, sizeof(uint64_t) * (nbins + 2), hipMemcpyDeviceToHost, st) !=
             hipSuccess)
         return PIC_EDEVICE;
@@ -2152,50 +2136,43 @@ int32_t pic_box_get(pic_box* b, pic_box_info* info)
     if (side_join(b)) return PIC_EDEVICE;
     std::memset(info, 0, sizeof(*info));
     hipStream_t st = b->st;
-    if (field_energy(b->G, field_ptrs(b), 6, b->red_part, kRedBlocks, b->red_out, st) != hipSuccess)
-        return PIC_EDEVICE;
-    double fe[6];
-    if (hipMemcpyAsync(fe, b->red_out, sizeof(fe), hipMemcpyDeviceToHost, st) != hipSuccess ||
+    // one record for all: its sums, counters and counts come back in one copy
+    SumArgs P{};
+    P.nsp = b->nsp;
+    for (int s = 0; s < b->nsp; s++) {
+        const Species& S = b->sp[s];
+        P.s[s].cell = escapes(&b->d) ? S.cell[S.cur] : nullptr;
+        for (int c = 0; c < 3; c++) P.s[s].u[c] = S.u[S.cur][c];
+        P.s[s].n_live = S.n_live;
+    }
+    P.ctr = b->ctr;
+    P.err = b->err;
+    P.sweeps = b->last_sweeps < 0 ? reinterpret_cast<const int32_t*>(b->conv + 2 * kKsbMaxSweeps) : nullptr;
+    BoxRecord R{};
+    if (box_record(b->G, field_ptrs(b), P, b->red_part, kRedBlocks, b->record, st) != hipSuccess ||
+        hipMemcpyAsync(&R, b->record, sizeof(R), hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
         return PIC_EDEVICE;
     for (int c = 0; c < 3; c++) {
-        info->field_energy_B[c] = fe[c] / (8.0 * kPi);  // set order: B then E
-        info->field_energy_E[c] = fe[3 + c] / (8.0 * kPi);
+        info->field_energy_B[c] = R.row[c] / (8.0 * kPi);  // set order: B then E
+        info->field_energy_E[c] = R.row[3 + c] / (8.0 * kPi);
     }
     for (int s = 0; s < b->nsp; s++) {
-        Species& S = b->sp[s];
-        const int k = S.cur;
-        if (particle_sums(S.cell[k], S.u[k][0], S.u[k][1], S.u[k][2], S.n_live, b->red_part, kRedBlocks,
-                          b->red_out, st) != hipSuccess)
-            return PIC_EDEVICE;
-        double ps[kPartSums];
-        int32_t n = 0;
-        if (hipMemcpyAsync(ps, b->red_out, sizeof(ps), hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipMemcpyAsync(&n, S.n_live, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess)
-            return PIC_EDEVICE;
+        const Species& S = b->sp[s];
+        const double* ps = R.row + 6 + kPartSums * s;
         const double m = S.qm != 0 ? std::fabs(S.q / S.qm) : 0.0;
         info->kinetic_energy += m * ps[0];
         for (int c = 0; c < 3; c++) info->momentum[c] += m * ps[1 + c];
         for (int c = 0; c < 3; c++) info->pressure[c] += m * ps[4 + c];
-        info->n_particles[s] = n;
+        info->n_particles[s] = R.live[s];
     }
-    uint32_t err = 0;
-    unsigned long long ctr[4] = {0, 0, 0, 0};
-    if (hipMemcpy(&err, b->err, sizeof(err), hipMemcpyDeviceToHost) != hipSuccess ||
-        hipMemcpy(ctr, b->ctr, sizeof(ctr), hipMemcpyDeviceToHost) != hipSuccess)
-        return PIC_EDEVICE;
-    info->maxwell_sweeps = b->last_sweeps;
-    if (b->last_sweeps < 0 &&
-        hipMemcpy(&info->maxwell_sweeps, b->conv + 2 * kKsbMaxSweeps, sizeof(int32_t), hipMemcpyDeviceToHost) !=
-            hipSuccess)
-        return PIC_EDEVICE;
+    info->maxwell_sweeps = b->last_sweeps < 0 ? R.sweeps : b->last_sweeps;
     info->n_sort_migrations = b->n_migrations;
-    info->n_sort_fallbacks = (int64_t)ctr[2];
-    info->errors = err;
-    info->n_slow = (int64_t)ctr[0];
-    info->n_escaped = (int64_t)ctr[1];
-    info->n_superluminal = (int64_t)ctr[3];
+    info->n_sort_fallbacks = (int64_t)R.ctr[2];
+    info->errors = R.err;
+    info->n_slow = (int64_t)R.ctr[0];
+    info->n_escaped = (int64_t)R.ctr[1];
+    info->n_superluminal = (int64_t)R.ctr[3];
     info->field_set = b->cur_set;
     info->current_array = b->J[0] == b->J0 ? 0 : 1;
     for (int s = 0; s < b->nsp; s++) info->particle_copy[s] = b->sp[s].cur;

@@ -1170,22 +1170,37 @@ __global__ __launch_bounds__(kBlock) void clear_kernel(ClearArgs a)
     if (y == 0 && blockIdx.x == 0 && threadIdx.x < kMaxSpecies && a.flag[threadIdx.x]) *a.flag[threadIdx.x] = 0;
 }
 
-// interior <-> dense copies: dense index x + n0*(y + n1*z)
-__global__ __launch_bounds__(kBlock) void interior_copy_kernel(GridDev G, float* guarded,
-                                                               float* dense, int to_dense)
+// interior <-> dense copies of gridDim.y arrays: dense index x + n0*(y + n1*z)
+__global__ __launch_bounds__(kBlock) void interior_copy_kernel(GridDev G, Comp6 guarded, Comp6 dense, int to_dense)
 {
-    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (t >= (int64_t)G.n[0] * G.n[1] * G.n[2]) return;
-    int x, y, z;
-    cell_of(G, t, x, y, z);
-    const int64_t i = gidx(G, x, y, z);
-    if (to_dense)
-        dense[t] = guarded[i];
-    else
-        guarded[i] = dense[t];
+    const int c = (int)blockIdx.y;
+    const int64_t n = (int64_t)G.n[0] * G.n[1] * G.n[2];
+    for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < n; t += (int64_t)gridDim.x * kBlock) {
+        int x, y, z;
+        cell_of(G, t, x, y, z);
+        const int64_t i = gidx(G, x, y, z);
+        if (to_dense)
+            dense.p[c][t] = guarded.p[c][i];
+        else
+            guarded.p[c][i] = dense.p[c][t];
+    }
 }
 
-// FP64 block partial sums of squares of up to 6 interior component arrays
+// FP64 sum of a workgroup's values in a fixed order, on thread 0
+__device__ inline double block_sum(double v, double* sh)
+{
+    sh[threadIdx.x] = v;
+    __syncthreads();
+    for (int s = kBlock / 2; s > 0; s >>= 1) {
+        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
+        __syncthreads();
+    }
+    const double r = sh[0];
+    __syncthreads();
+    return r;
+}
+
+// FP64 block partial sums of squares of 6 interior component arrays
 __global__ __launch_bounds__(kBlock) void field_energy_kernel(GridDev G, Comp6 A, double* part)
 {
     __shared__ double sh[kBlock];
@@ -1199,96 +1214,113 @@ __global__ __launch_bounds__(kBlock) void field_energy_kernel(GridDev G, Comp6 A
         const double v = A.p[c][gidx(G, x, y, z)];
         acc += v * v;
     }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = kBlock / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[c * gridDim.x + blockIdx.x] = sh[0];
+    const double r = block_sum(acc, sh);
+    if (threadIdx.x == 0) part[c * gridDim.x + blockIdx.x] = r;
 }
 
-// FP64 block partial sums of (gamma-1), u_x, u_y, u_z over the live particles
-// sums over the particles that have not escaped (an escape marks the cell -1 until the next
-// sort drops the particle)
-__global__ __launch_bounds__(kBlock) void particle_sums_kernel(const int32_t* cell, const float* ux,
-                                                               const float* uy, const float* uz,
-                                                               const int32_t* n_live,
-                                                               double* part)
+// FP64 block partial sums of (gamma-1), u and the kinetic stress diagonal u_c^2/gamma over the particles
+// that have not escaped (an escape marks the cell -1 until the next sort drops the particle; cell null:
+// a box without escapes), one species per blockIdx.y
+__global__ __launch_bounds__(kBlock) void particle_sums_kernel(SumArgs P, double* part)
 {
-    __shared__ double sh[kPartSums][kBlock];
+    __shared__ double sh[kBlock];
+    const SumArgs::Species& S = P.s[blockIdx.y];
     double a[kPartSums] = {};
-    const int n = *n_live;
+    const int n = *S.n_live;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * kBlock) {
-        if (cell[i] < 0) continue;
-        const double x = ux[i], y = uy[i], z = uz[i];
+        if (S.cell && S.cell[i] < 0) continue;
+        const double x = S.u[0][i], y = S.u[1][i], z = S.u[2][i];
         const double uu = x * x + y * y + z * z;
-        const double g = sqrt(1.0 + uu);
+        const double g = sqrt(1.0 + uu), rg = 1.0 / g;
         a[0] += uu / (g + 1.0);  // gamma - 1 without cancellation
         a[1] += x;
         a[2] += y;
         a[3] += z;
-        a[4] += x * x / g;  // kinetic stress diagonal u_c^2 / gamma
-        a[5] += y * y / g;
-        a[6] += z * z / g;
+        a[4] += x * x * rg;
+        a[5] += y * y * rg;
+        a[6] += z * z * rg;
     }
-    for (int k = 0; k < kPartSums; k++) sh[k][threadIdx.x] = a[k];
-    __syncthreads();
-    for (int s = kBlock / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s)
-            for (int k = 0; k < kPartSums; k++) sh[k][threadIdx.x] += sh[k][threadIdx.x + s];
-        __syncthreads();
+    for (int k = 0; k < kPartSums; k++) {
+        const double r = block_sum(a[k], sh);
+        if (threadIdx.x == 0) part[(blockIdx.y * kPartSums + k) * gridDim.x + blockIdx.x] = r;
     }
-    if (threadIdx.x == 0)
-        for (int k = 0; k < kPartSums; k++) part[k * gridDim.x + blockIdx.x] = sh[k][0];
 }
 
 // Energy distribution (Sec. 4.2) of the particles that have not escaped: slot = number of
 // edges <= gamma - 1 (0: below the first edge, nbins + 1: at or above the last; non-finite
-// energies go to the last slot).  Edges and the workgroup's counts sit in LDS; each workgroup
-// adds its non-zero counts once.
-__global__ __launch_bounds__(kBlock) void energy_hist_kernel(const int32_t* cell, const float* ux,
+// energies go to the last slot).  Edges and the workgroup's counts sit in LDS, sized by the bins, so
+// that a histogram of 200 bins leaves a CU full (three workgroups with the space for the most bins);
+// each workgroup adds its non-zero counts once.  The chip is filled by two workgroups of sixteen waves
+// a CU: the counts of 1024 smaller ones meet at the same few words of memory.  A thread searches for two
+// particles at a time.
+// 9.6M particles, 200 bins: 127 us with the fixed space and 1024 small workgroups, 50 us (2.3 TB/s).  (Several count words a slot, and a
+// search by FP32 energies with the FP64 one where an edge is near, did not change that.)
+constexpr int kHistBlock = 1024, kHistBlocks = 512;
+__global__ __launch_bounds__(kHistBlock) void energy_hist_kernel(const int32_t* cell, const float* ux,
                                                              const float* uy, const float* uz,
                                                              const int32_t* n_live,
                                                              const double* edges, int nbins,
                                                              unsigned long long* counts)
 {
-    __shared__ double e[kHistMaxBins + 1];
-    __shared__ uint32_t h[kHistMaxBins + 2];
-    for (int b = threadIdx.x; b < nbins + 2; b += kBlock) h[b] = 0u;
-    for (int b = threadIdx.x; b <= nbins; b += kBlock) e[b] = edges[b];
+    extern __shared__ double e[];
+    uint32_t* const h = reinterpret_cast<uint32_t*>(e + nbins + 1);
+    for (int b = threadIdx.x; b < nbins + 2; b += kHistBlock) h[b] = 0u;
+    for (int b = threadIdx.x; b <= nbins; b += kHistBlock) e[b] = edges[b];
     __syncthreads();
     const int n = *n_live;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * kBlock) {
-        if (cell[i] < 0) continue;
-        const double x = ux[i], y = uy[i], z = uz[i];
-        const double uu = x * x + y * y + z * z;  // FP32 inputs: the products are exact
-        const double k = uu / (sqrt(1.0 + uu) + 1.0);
-        int lo = 0, hi = nbins + 1;  // edges[0..lo) <= k, edges[hi..] > k
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (e[mid] <= k)
-                lo = mid + 1;
-            else
-                hi = mid;
+    int steps = 1;  // halvings that bring nbins + 1 edges down to none
+    while ((nbins + 1) >> steps) steps++;
+    const int64_t stride = (int64_t)gridDim.x * kHistBlock;
+    for (int64_t i = (int64_t)blockIdx.x * kHistBlock + threadIdx.x; i < n; i += 2 * stride) {
+        double k[2];
+        int lo[2] = {0, 0}, len[2];
+        bool on[2];
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            const int64_t p = i + j * stride, q = p < n ? p : i;
+            on[j] = p < n && !(cell && cell[q] < 0);
+            const double x = ux[q], y = uy[q], z = uz[q];
+            const double uu = x * x + y * y + z * z;  // FP32 inputs: the products are exact
+            k[j] = uu / (sqrt(1.0 + uu) + 1.0);
+            len[j] = nbins + 1;  // edges[0 .. lo) <= k, edges[lo + len ..] > k
         }
-        atomicAdd(&h[k == k ? lo : nbins + 1], 1u);
+        for (int s = 0; s < steps; s++)
+#pragma unroll
+            for (int j = 0; j < 2; j++) {
+                const int half = len[j] >> 1, mid = lo[j] + half;
+                const bool below = len[j] > 0 && e[mid < nbins ? mid : nbins] <= k[j];
+                lo[j] = below ? mid + 1 : lo[j];
+                len[j] = below ? len[j] - half - 1 : half;
+            }
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+            if (on[j]) atomicAdd(&h[k[j] == k[j] ? lo[j] : nbins + 1], 1u);
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < nbins + 2; b += kBlock)
+    for (int b = threadIdx.x; b < nbins + 2; b += kHistBlock)
         if (h[b]) atomicAdd(&counts[b], (unsigned long long)h[b]);
 }
 
-// fixed-order final sum of nrow rows of ncol partials (one thread per row)
-__global__ void sum_rows_kernel(const double* part, int nrow, int ncol, double* out)
+// The record of a box: workgroup r < rows sums the row r of ncol partials in a fixed order, the one
+// beyond them collects the counters.  (One thread per row took 82 us.)
+__global__ __launch_bounds__(kBlock) void box_record_kernel(SumArgs P, const double* part, int rows, int ncol, BoxRecord* out)
 {
-    const int r = threadIdx.x;
-    if (r >= nrow) return;
-    double s = 0.0;
-    for (int k = 0; k < ncol; k++) s += part[r * ncol + k];
-    out[r] = s;
+    __shared__ double sh[kBlock];
+    const int r = (int)blockIdx.x;
+    if (r == rows) {
+        if (threadIdx.x == 0) {
+            for (int s = 0; s < P.nsp; s++) out->live[s] = *P.s[s].n_live;
+            for (int k = 0; k < 4; k++) out->ctr[k] = P.ctr[k];
+            out->err = *P.err;
+            out->sweeps = P.sweeps ? *P.sweeps : 0;
+        }
+        return;
+    }
+    double v = 0.0;
+    for (int k = threadIdx.x; k < ncol; k += kBlock) v += part[r * ncol + k];
+    v = block_sum(v, sh);
+    if (threadIdx.x == 0) out->row[r] = v;
 }
 
 // ------------------------------------------------------------------ host launchers
@@ -1480,35 +1512,38 @@ hipError_t clear_for_push(const ClearArgs& a, hipStream_t st)
     clear_kernel<<<dim3(std::max(nb, 1u), 3 + ns), kBlock, 0, st>>>(a);
     return hipGetLastError();
 }
-hipError_t interior_copy(const GridDev& G, float* guarded, float* dense, int to_dense, hipStream_t st)
+hipError_t interior_copy(const GridDev& G, float* const* guarded, float* const* dense, int ncomp, int to_dense,
+                         hipStream_t st)
 {
-    interior_copy_kernel<<<nblocks((int64_t)G.n[0] * G.n[1] * G.n[2]), kBlock, 0, st>>>(G, guarded,
-                                                                                      dense, to_dense);
+    if (ncomp == 0) return hipSuccess;
+    Comp6 A{}, D{};
+    for (int c = 0; c < ncomp; c++) {
+        A.p[c] = guarded[c];
+        D.p[c] = dense[c];
+    }
+    const unsigned nb = std::min(nblocks((int64_t)G.n[0] * G.n[1] * G.n[2]), kStrideBlocks);
+    interior_copy_kernel<<<dim3(nb, (unsigned)ncomp), kBlock, 0, st>>>(G, A, D, to_dense);
     return hipGetLastError();
 }
-hipError_t field_energy(const GridDev& G, float* const* comps, int ncomp, double* part, int nblk,
-                        double* out, hipStream_t st)
+hipError_t box_record(const GridDev& G, float* const* comps, const SumArgs& P, double* part, int nblk, BoxRecord* out,
+                      hipStream_t st)
 {
     Comp6 A{};
-    for (int c = 0; c < ncomp; c++) A.p[c] = comps[c];
-    field_energy_kernel<<<dim3(nblk, ncomp), kBlock, 0, st>>>(G, A, part);
-    sum_rows_kernel<<<1, 64, 0, st>>>(part, ncomp, nblk, out);
-    return hipGetLastError();
-}
-hipError_t particle_sums(const int32_t* cell, const float* ux, const float* uy, const float* uz,
-                         const int32_t* n_live, double* part, int nblk, double* out, hipStream_t st)
-{
-    particle_sums_kernel<<<nblk, kBlock, 0, st>>>(cell, ux, uy, uz, n_live, part);
-    sum_rows_kernel<<<1, 64, 0, st>>>(part, kPartSums, nblk, out);
+    for (int c = 0; c < 6; c++) A.p[c] = comps[c];
+    const int rows = 6 + kPartSums * P.nsp;
+    field_energy_kernel<<<dim3(nblk, 6), kBlock, 0, st>>>(G, A, part);
+    particle_sums_kernel<<<dim3(nblk, (unsigned)P.nsp), kBlock, 0, st>>>(P, part + 6 * nblk);
+    box_record_kernel<<<rows + 1, kBlock, 0, st>>>(P, part, rows, nblk, out);
     return hipGetLastError();
 }
 hipError_t energy_histogram(const int32_t* cell, const float* ux, const float* uy, const float* uz,
                             const int32_t* n_live, const double* edges, int nbins,
-                            unsigned long long* counts, int nblk, hipStream_t st)
+                            unsigned long long* counts, hipStream_t st)
 {
     zero_kernel<<<nblocks(2 * (nbins + 2)), kBlock, 0, st>>>(
         ZeroArgs{reinterpret_cast<uint32_t*>(counts), (int64_t)2 * (nbins + 2)});
-    energy_hist_kernel<<<nblk, kBlock, 0, st>>>(cell, ux, uy, uz, n_live, edges, nbins, counts);
+    const size_t lds = (size_t)(nbins + 1) * sizeof(double) + (size_t)(nbins + 2) * sizeof(uint32_t);
+    energy_hist_kernel<<<kHistBlocks, kHistBlock, lds, st>>>(cell, ux, uy, uz, n_live, edges, nbins, counts);
     return hipGetLastError();
 }
 

@@ -506,17 +506,35 @@ hipError_t scale_fields(const GridDev& G, float* const* F, const float f[3], hip
 constexpr int kKsbFinBlocks = 512;  // workgroups per box of the finalize copy (grid stride)
 hipError_t zero_floats(float* p, int64_t n, hipStream_t st);
 hipError_t clear_for_push(const ClearArgs& a, hipStream_t st);
-hipError_t interior_copy(const GridDev& G, float* guarded, float* dense, int to_dense,
+hipError_t interior_copy(const GridDev& G, float* const* guarded, float* const* dense, int ncomp, int to_dense,
                          hipStream_t st);
-hipError_t field_energy(const GridDev& G, float* const* comps, int ncomp, double* part, int nblk,
-                        double* out, hipStream_t st);
-hipError_t particle_sums(const int32_t* cell, const float* ux, const float* uy, const float* uz,
-                         const int32_t* n_live, double* part, int nblk, double* out, hipStream_t st);
-constexpr int kPartSums = 7;       // particle_sums rows: gamma-1, u (3), u_c^2/gamma (3)
+constexpr int kPartSums = 7;       // rows per species: gamma-1, u (3), u_c^2/gamma (3)
+// the particles and counters that a box's record is taken from, and the record
+struct SumArgs {
+    struct Species {
+        const int32_t* cell;  // null: a box without escapes
+        const float* u[3];
+        const int32_t* n_live;
+    } s[kMaxSpecies];
+    int nsp;
+    const unsigned long long* ctr;
+    const uint32_t* err;
+    const int32_t* sweeps;  // null: known to the host
+};
+struct BoxRecord {
+    double row[6 + kPartSums * kMaxSpecies];  // squares of B, E; then per species kPartSums sums
+    unsigned long long ctr[4];
+    int32_t live[kMaxSpecies];
+    uint32_t err;
+    int32_t sweeps;
+};
+// part: one row of nblk partials for every row of the record
+hipError_t box_record(const GridDev& G, float* const* comps, const SumArgs& P, double* part, int nblk, BoxRecord* out,
+                      hipStream_t st);
 constexpr int kHistMaxBins = 4096;  // energy_histogram
 hipError_t energy_histogram(const int32_t* cell, const float* ux, const float* uy, const float* uz,
                             const int32_t* n_live, const double* edges, int nbins,
-                            unsigned long long* counts, int nblk, hipStream_t st);
+                            unsigned long long* counts, hipStream_t st);
 
 // Static device scratch of the entry points that allocate nothing (noalloc.hip): the current
 // device's copy of one file-scope array of kStaticScratchBytes, its address taken once per
@@ -527,12 +545,22 @@ constexpr size_t kStaticScratchBytes =
     (kStaticHistCountsOffset + (size_t)(kHistMaxBins + 2) * 8 + 255) & ~(size_t)255;
 hipError_t static_scratch(void** ptr, size_t* bytes);
 
-hipError_t cells_linear_to_packed(const int32_t* lin, int32_t* packed, int64_t n, const int nn[3],
-                                  CellCode cc, uint32_t* err, hipStream_t st);
-hipError_t cells_packed_to_linear(const int32_t* packed, int32_t* lin, int64_t n, const int nn[3],
-                                  CellCode cc, hipStream_t st);
+// particles between the boundary layout (dense arrays: off[c * n + i], u, dr likewise; linear cells)
+// and a species' arrays; null pointers are left out
+struct Particles {
+    int32_t* cell;
+    float* off[3];
+    float* u[3];
+    uint32_t* id;
+    float* dr[3];
+};
+hipError_t particles_in(const Particles& to, int64_t n, const int32_t* cell, const float* off, const float* u,
+                        const uint32_t* id, const float* dr, int dim, const GridDev& G, CellCode cc, int32_t* n_live,
+                        uint32_t* err, hipStream_t st);
+// the *n_live particles (at most n_upper) out; dr: ndr components, the others 0
+hipError_t particles_out(const Particles& from, const int32_t* n_live, int64_t n_upper, int32_t* cell, float* off,
+                         float* u, uint32_t* id, float* dr, int dim, int ndr, const GridDev& G, CellCode cc,
+                         hipStream_t st);
 hipError_t device_copy16(void* dst, const void* src, int64_t nwords, hipStream_t st);
-hipError_t iota_u32(uint32_t* p, int64_t n, hipStream_t st);
-hipError_t set_i32(int32_t* p, int32_t v, hipStream_t st);
 
 }  // namespace pic

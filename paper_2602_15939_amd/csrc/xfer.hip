@@ -4,43 +4,118 @@
 
 namespace pic {
 
-__global__ __launch_bounds__(kBlock) void lin_to_packed_kernel(const int32_t* lin, int32_t* packed,
-                                                               int64_t n, int nx, int ny, int nz,
-                                                               CellCode cc, uint32_t* err)
+// All arrays of a species in one launch, four consecutive particles a thread and round: bound by
+// memory (a copy per array was five to nine launches, on small boxes 4 us each).  A species' arrays
+// start at 16-byte boundaries; a row of a dense array of n particles (off, u, dr) may start at any
+// 4-byte one, and its 16-byte accesses carry that alignment.
+template <class T>
+struct Vec4 {
+    typedef T type __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <class T>
+__device__ inline void copy4(T* dst, const T* src, int64_t i, int m)
 {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const int32_t c = lin[i];
-    if (c < 0 || (int64_t)c >= (int64_t)nx * ny * nz) {
-        packed[i] = cc.encode(0, 0, 0);
-        atomicOr(err, 8u);
-        return;
+    using V = typename Vec4<T>::type;
+    if (m == 4)
+        *reinterpret_cast<V*>(dst + i) = *reinterpret_cast<const V*>(src + i);
+    else
+        for (int k = 0; k < m; k++) dst[i + k] = src[i + k];
+}
+template <class T>
+__device__ inline void load4(T v[4], const T* src, int64_t i, int m)
+{
+    using V = typename Vec4<T>::type;
+    if (m == 4) {
+        const V q = *reinterpret_cast<const V*>(src + i);
+#pragma unroll
+        for (int k = 0; k < 4; k++) v[k] = q[k];
+    } else {
+        for (int k = 0; k < m; k++) v[k] = src[i + k];
     }
-    const int x = c % nx;
-    const int r = c / nx;
-    packed[i] = cc.encode(x, r % ny, r / ny);
+}
+template <class T>
+__device__ inline void store4(T* dst, const T v[4], int64_t i, int m)
+{
+    using V = typename Vec4<T>::type;
+    if (m == 4)
+        *reinterpret_cast<V*>(dst + i) = V{v[0], v[1], v[2], v[3]};
+    else
+        for (int k = 0; k < m; k++) dst[i + k] = v[k];
 }
 
-__global__ __launch_bounds__(kBlock) void packed_to_lin_kernel(const int32_t* packed, int32_t* lin,
-                                                               int64_t n, int nx, int ny,
-                                                               CellCode cc)
+__global__ __launch_bounds__(kBlock) void particles_in_kernel(Particles to, int64_t n, const int32_t* cell, const float* off,
+                                                              const float* u, const uint32_t* id, const float* dr, int dim,
+                                                              GridDev G, CellCode cc, int32_t* n_live, uint32_t* err)
 {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const int32_t c = packed[i];
-    if (c < 0) {
-        lin[i] = -1;
-        return;
+    const int64_t first = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (first == 0) *n_live = (int32_t)n;
+    const int64_t ncell = (int64_t)G.n[0] * G.n[1] * G.n[2];
+    const float zero[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int64_t i = 4 * first; i < n; i += (int64_t)gridDim.x * kBlock * 4) {
+        const int m = n - i < 4 ? (int)(n - i) : 4;
+        int32_t c[4] = {};
+        load4(c, cell, i, m);
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            if (k < m && (c[k] < 0 || (int64_t)c[k] >= ncell)) {
+                c[k] = 0;
+                atomicOr(err, 8u);
+            }
+            const uint32_t r = G.div0.div((uint32_t)c[k]), z = G.div1.div(r);
+            c[k] = cc.encode((int)((uint32_t)c[k] - r * (uint32_t)G.n[0]), (int)(r - z * (uint32_t)G.n[1]), (int)z);
+        }
+        store4(to.cell, c, i, m);
+#pragma unroll
+        for (int d = 0; d < 3; d++) {
+            if (d < dim) copy4(to.off[d], off + d * n, i, m);
+            copy4(to.u[d], u + d * n, i, m);
+            if (to.dr[d]) {
+                if (dr)
+                    copy4(to.dr[d], dr + d * n, i, m);
+                else
+                    store4(to.dr[d], zero, i, m);
+            }
+        }
+        if (to.id) {
+            uint32_t q[4] = {(uint32_t)i, (uint32_t)i + 1u, (uint32_t)i + 2u, (uint32_t)i + 3u};
+            if (id) load4(q, id, i, m);
+            store4(to.id, q, i, m);
+        }
     }
-    int x, y, z;
-    cc.decode(c, x, y, z);
-    lin[i] = x + nx * (y + ny * z);
 }
 
-__global__ __launch_bounds__(kBlock) void iota_kernel(uint32_t* p, int64_t n)
+__global__ __launch_bounds__(kBlock) void particles_out_kernel(Particles from, const int32_t* n_live, int32_t* cell, float* off,
+                                                               float* u, uint32_t* id, float* dr, int dim, int ndr,
+                                                               GridDev G, CellCode cc)
 {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) p[i] = (uint32_t)i;
+    const int64_t n = *n_live;
+    const float zero[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int64_t i = 4 * ((int64_t)blockIdx.x * kBlock + threadIdx.x); i < n; i += (int64_t)gridDim.x * kBlock * 4) {
+        const int m = n - i < 4 ? (int)(n - i) : 4;
+        if (cell) {
+            int32_t c[4] = {};
+            load4(c, from.cell, i, m);
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                int x, y, z;
+                cc.decode(c[k], x, y, z);
+                c[k] = c[k] < 0 ? -1 : x + G.n[0] * (y + G.n[1] * z);
+            }
+            store4(cell, c, i, m);
+        }
+#pragma unroll
+        for (int d = 0; d < 3; d++) {
+            if (off && d < dim) copy4(off + d * n, from.off[d], i, m);
+            if (u) copy4(u + d * n, from.u[d], i, m);
+            if (dr) {
+                if (d < ndr)
+                    copy4(dr + d * n, from.dr[d], i, m);
+                else
+                    store4(dr + d * n, zero, i, m);
+            }
+        }
+        if (id) copy4(id, from.id, i, m);
+    }
 }
 
 // Plain streaming copy in 16-byte words (the reference kernel of known traffic used to scale
@@ -52,22 +127,25 @@ __global__ __launch_bounds__(kBlock) void copy_kernel(uint4* __restrict__ dst,
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) dst[i] = src[i];
 }
 
-__global__ void set_i32_kernel(int32_t* p, int32_t v) { *p = v; }
-
-static inline unsigned nblk(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
-
-hipError_t cells_linear_to_packed(const int32_t* lin, int32_t* packed, int64_t n, const int nn[3],
-                                  CellCode cc, uint32_t* err, hipStream_t st)
+static inline unsigned capped(int64_t n)
 {
-    if (n > 0)
-        lin_to_packed_kernel<<<nblk(n), kBlock, 0, st>>>(lin, packed, n, nn[0], nn[1], nn[2], cc, err);
+    const int64_t want = (n + 4 * kBlock - 1) / (4 * kBlock);
+    return (unsigned)(want < 1 ? 1 : (want < 8192 ? want : 8192));
+}
+
+hipError_t particles_in(const Particles& to, int64_t n, const int32_t* cell, const float* off, const float* u,
+                        const uint32_t* id, const float* dr, int dim, const GridDev& G, CellCode cc, int32_t* n_live,
+                        uint32_t* err, hipStream_t st)
+{
+    particles_in_kernel<<<capped(n), kBlock, 0, st>>>(to, n, cell, off, u, id, dr, dim, G, cc, n_live, err);
     return hipGetLastError();
 }
 
-hipError_t cells_packed_to_linear(const int32_t* packed, int32_t* lin, int64_t n, const int nn[3],
-                                  CellCode cc, hipStream_t st)
+hipError_t particles_out(const Particles& from, const int32_t* n_live, int64_t n_upper, int32_t* cell, float* off,
+                         float* u, uint32_t* id, float* dr, int dim, int ndr, const GridDev& G, CellCode cc,
+                         hipStream_t st)
 {
-    if (n > 0) packed_to_lin_kernel<<<nblk(n), kBlock, 0, st>>>(packed, lin, n, nn[0], nn[1], cc);
+    particles_out_kernel<<<capped(n_upper), kBlock, 0, st>>>(from, n_live, cell, off, u, id, dr, dim, ndr, G, cc);
     return hipGetLastError();
 }
 
@@ -79,18 +157,6 @@ hipError_t device_copy16(void* dst, const void* src, int64_t nwords, hipStream_t
         copy_kernel<<<grid, kBlock, 0, st>>>(static_cast<uint4*>(dst), static_cast<const uint4*>(src),
                                              nwords);
     }
-    return hipGetLastError();
-}
-
-hipError_t set_i32(int32_t* p, int32_t v, hipStream_t st)
-{
-    set_i32_kernel<<<1, 1, 0, st>>>(p, v);
-    return hipGetLastError();
-}
-
-hipError_t iota_u32(uint32_t* p, int64_t n, hipStream_t st)
-{
-    if (n > 0) iota_kernel<<<nblk(n), kBlock, 0, st>>>(p, n);
     return hipGetLastError();
 }
 
