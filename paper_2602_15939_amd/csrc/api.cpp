@@ -451,6 +451,7 @@ void set_tiling(pic_box* b, const int tile[3])
         b->tl.nt[k] = (b->n[k] + tile[k] - 1) / tile[k];
         g.nt[k] = b->tl.nt[k];
         g.lt[k] = b->tl.lt[k];
+        g.many[k] = g.nt[k] > 1 ? -1 : 0;
         if (b->n[k] % tile[k] != 0 || b->tl.nt[k] == 2) g.general = 1;
     }
     b->tl.n_tiles = b->tl.nt[0] * b->tl.nt[1] * b->tl.nt[2];

@@ -60,6 +60,7 @@ constexpr int kMigSmall = 1024;  // tiles up to which the scatter scans the tile
 struct MigGeo {
     int nt[3], lt[3];
     int n_tiles;
+    int many[3];  // -1 on an axis of several tiles, 0 on one of a single tile
     int general;  // an axis of two tiles, or of a size that is no multiple of the tile
     // shearing box: cells along y and, modulo them, the first row that the particles of tile 0 may
     // reach through the outer (first[1]) and the inner (first[0]) x face
