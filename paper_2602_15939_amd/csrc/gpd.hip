@@ -380,27 +380,30 @@ __host__ __device__ constexpr bool yee_half(int f, int a) { return f < 3 ? f == 
 template <int DIM, int TX, int TY, int TZ>
 struct Geo {
     static constexpr int T(int a) { return a == 0 ? TX : (a == 1 ? TY : TZ); }
-    // Staged field component f: along a half-lattice axis the values at global indices
-    // t0-1 .. t0+T (T+2), along an integer axis t0 .. t0+T (T+1): what CIC needs for a
-    // particle in the tile.
+    // Staged field component f: per lower corner along x the value there and the step to the next one
+    // (8 bytes): along a half-lattice axis the values at global indices t0-1 .. t0+T, along an integer
+    // axis t0 .. t0+T, what CIC needs for a particle in the tile.  All components have the pitches of
+    // the half lattices, so that one place and the three half-cell choices give every address.
+    static constexpr int FX = TX + 1, FY = TY + 2, FXY = FX * FY;
     static constexpr int fdim(int f, int a)
     {
         return (DIM == 2 && a == 2) ? 1 : T(a) + (yee_half(f, a) ? 2 : 1);
     }
-    static constexpr int fsize(int f) { return fdim(f, 0) * fdim(f, 1) * fdim(f, 2); }
+    static constexpr int fsize(int f) { return FXY * (fdim(f, 2) - 1) + FX * fdim(f, 1); }
     static constexpr int foff(int f) { return f == 0 ? 0 : foff(f - 1) + fsize(f - 1); }
     // Current component c, origin at global index t0-1 on every axis: along its own axis the
     // edges t0-1 .. t0+T (T+2), across it the nodes t0-1 .. t0+T+1 (T+3); the deposit of a
-    // particle of the tile stays inside.  2D: J_z has nodes along x and y.
+    // particle of the tile stays inside.  2D: J_z has nodes along x and y.  Pitches of the nodes.
+    static constexpr int JX = TX + 3, JY = TY + 3;
     static constexpr int jdim(int c, int a)
     {
         return (DIM == 2 && a == 2) ? 1 : T(a) + (a == c ? 2 : 3);
     }
-    static constexpr int jsize(int c) { return jdim(c, 0) * jdim(c, 1) * jdim(c, 2); }
+    static constexpr int jsize(int c) { return JX * (JY * (jdim(c, 2) - 1) + jdim(c, 1)); }
     static constexpr int joff(int c) { return c == 0 ? 0 : joff(c - 1) + jsize(c - 1); }
     static constexpr int JTOT = joff(2) + jsize(2);
     static constexpr int FTOT = foff(5) + fsize(5);
-    static constexpr int FBYTES = (4 * FTOT + 15) & ~15;   // E, B first, then J (8-byte words)
+    static constexpr int FBYTES = (8 * FTOT + 15) & ~15;   // E, B first, then J (8-byte words)
     static constexpr int LDS_BYTES = FBYTES + 8 * JTOT;
 };
 
@@ -414,8 +417,8 @@ struct LdsAcc {
     char* J;
     int at[3];  // places in bytes
     static constexpr int kX = 8;
-    static __device__ constexpr int sy(int c) { return 8 * G::jdim(c, 0); }
-    static __device__ constexpr int sz(int c) { return 8 * G::jdim(c, 0) * G::jdim(c, 1); }
+    static __device__ constexpr int sy(int) { return 8 * G::JX; }
+    static __device__ constexpr int sz(int) { return 8 * G::JX * G::JY; }
     __device__ inline void add(int, int i, float v)
     {
         // v_cvt_i32_f32: truncates, saturates
@@ -442,29 +445,32 @@ __device__ inline GlobalAcc global_acc(const StepDev& P, int x, int y, int z)
     return GlobalAcc{P.J, {i, i, i}, P.sy, P.sz};
 }
 
-// CIC interpolation of staged component F: (ia, ib, ic) is the region index of the lower
-// corner, (wa, wb, wc) the weights of the upper corner.  The eight corners are fixed offsets
-// from one LDS address.
-template <class G, int DIM, int F>
-__device__ inline float interp_lds(const float* __restrict__ Fl, int ia, int ib, int ic, float wa,
-                                   float wb, float wc)
+// CIC interpolation of staged component F: ad is the place of the lower corner in bytes, (wa, wb, wc) the
+// weights of the upper corner.  One 8-byte read per x row: for scattered lanes it costs the 6.3 cycles of a
+// 4-byte one, two 4-byte values (ds_read2_b32) 12.5 and two rows in one instruction (ds_read2_b64) 22, which
+// the atomic form of the load keeps the compiler from making.  LDS was active 81-86 % of a 3D push's cycles,
+// now 64-70 %: 256^3 shear 6.35 -> 6.05 ms, 128 x 128 x 512 expand 5.30 -> 5.04 ms (2 x 134 M particles).
+template <class G, int F>
+__device__ inline float2 field_row(const char* Fl, unsigned ad, int row)
 {
-    constexpr unsigned X = G::fdim(F, 0), XY = X * G::fdim(F, 1);
-    // 24-bit multiply-adds (full rate); the index is non-negative and below 2^16
-    const unsigned idx = (unsigned)G::foff(F) + (unsigned)ia + __umul24((unsigned)ib, X) +
-                         (DIM == 3 ? __umul24((unsigned)ic, XY) : 0u);
-    unsigned ad = idx;
-    // opaque to constant reassociation: the corner offsets then fold into the ds_read2
-    // immediates of one address register
-    asm("" : "+v"(ad));
-    const float* p = Fl + ad;
-    const float a = p[0] + wa * (p[1] - p[0]);
-    const float b = p[X] + wa * (p[X + 1] - p[X]);
+    const unsigned long long v = __hip_atomic_load(
+        reinterpret_cast<const unsigned long long*>(Fl + ad + 8 * (G::foff(F) + row)), __ATOMIC_RELAXED,
+        __HIP_MEMORY_SCOPE_SINGLETHREAD);
+    return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+}
+template <class G, int DIM, int F>
+__device__ inline float interp_lds(const char* Fl, unsigned ad, float wa, float wb, float wc)
+{
+    const float2 p = field_row<G, F>(Fl, ad, 0), q = field_row<G, F>(Fl, ad, G::FX);
+    float2 s, t;
+    if (DIM == 3) {
+        s = field_row<G, F>(Fl, ad, G::FXY);
+        t = field_row<G, F>(Fl, ad, G::FXY + G::FX);
+    }
+    const float a = p.x + wa * p.y, b = q.x + wa * q.y;
     float r = a + wb * (b - a);
     if (DIM == 3) {
-        const float* q = p + XY;
-        const float c = q[0] + wa * (q[1] - q[0]);
-        const float d = q[X] + wa * (q[X + 1] - q[X]);
+        const float c = s.x + wa * s.y, d = t.x + wa * t.y;
         const float r2 = c + wb * (d - c);
         r = r + wc * (r2 - r);
     }
@@ -474,40 +480,54 @@ __device__ inline float interp_lds(const float* __restrict__ Fl, int ia, int ib,
 // Gather from the staged tile: (rx, ry, rz) = cell - tile origin.  On a half-shifted axis the
 // lower node is the one at cell - 1/2 below the cell centre and cell + 1/2 above it.
 template <class G, int DIM>
-__device__ inline void gather_lds(const float* __restrict__ Fl, int rx, int ry, int rz, float ox,
-                                  float oy, float oz, f3& E, f3& B)
+__device__ inline void gather_lds(const char* Fl, int rx, int ry, int rz, float ox, float oy, float oz, f3& E,
+                                  f3& B)
 {
     const bool lx = ox < 0.5f, ly = oy < 0.5f, lz = oz < 0.5f;
     const float hx = ox + (lx ? 0.5f : -0.5f), hy = oy + (ly ? 0.5f : -0.5f);
     const float hz = oz + (lz ? 0.5f : -0.5f);
-    const int ix = rx + (lx ? 0 : 1), iy = ry + (ly ? 0 : 1), iz = rz + (lz ? 0 : 1);
-    E.x = interp_lds<G, DIM, 0>(Fl, ix, ry, rz, hx, oy, oz);
-    E.y = interp_lds<G, DIM, 1>(Fl, rx, iy, rz, ox, hy, oz);
-    E.z = interp_lds<G, DIM, 2>(Fl, rx, ry, iz, ox, oy, hz);
-    B.x = interp_lds<G, DIM, 3>(Fl, rx, iy, iz, ox, hy, hz);
-    B.y = interp_lds<G, DIM, 4>(Fl, ix, ry, iz, hx, oy, hz);
-    B.z = interp_lds<G, DIM, 5>(Fl, ix, iy, rz, hx, hy, oz);
+    // 24-bit multiply-adds (full rate); places are non-negative
+    const unsigned ad = 8u * (unsigned)rx + __umul24((unsigned)ry, 8u * G::FX) +
+                        (DIM == 3 ? __umul24((unsigned)rz, 8u * G::FXY) : 0u);
+    const unsigned ax = lx ? 0u : 8u, ay = ly ? 0u : 8u * G::FX, az = DIM == 2 || lz ? 0u : 8u * G::FXY;
+    E.x = interp_lds<G, DIM, 0>(Fl, ad + ax, hx, oy, oz);
+    E.y = interp_lds<G, DIM, 1>(Fl, ad + ay, ox, hy, oz);
+    E.z = interp_lds<G, DIM, 2>(Fl, ad + az, ox, oy, hz);
+    B.x = interp_lds<G, DIM, 3>(Fl, ad + ay + az, ox, hy, hz);
+    B.y = interp_lds<G, DIM, 4>(Fl, ad + ax + az, hx, oy, hz);
+    B.z = interp_lds<G, DIM, 5>(Fl, ad + ax + ay, hx, hy, oz);
 }
 
-// Stage field component F (and the ones after it) of the tile into its LDS region.
+// Stage field component F (and the ones after it) of the tile into its LDS region.  All components'
+// loads are in flight before the first store where a thread has few of them: a box of one round of
+// workgroups waits for memory once instead of for each component.
 template <class G, int DIM, int F, int NT>
-__device__ inline void stage_fields(float* __restrict__ Fl, const StepDev& P, const int t0[3],
+__device__ inline void stage_fields(float2* __restrict__ Fl, const StepDev& P, const int t0[3],
                                     const int ext[3], int tid)
 {
-    constexpr int X = G::fdim(F, 0), Y = G::fdim(F, 1), Z = G::fdim(F, 2);
+    constexpr int N = G::fsize(F), ROUNDS = (N + NT - 1) / NT;
     constexpr int hx = yee_half(F, 0), hy = yee_half(F, 1), hz = DIM == 3 && yee_half(F, 2);
     const float* src = F < 3 ? P.E[F] : P.B[F - 3];
-    for (int e = tid; e < X * Y * Z; e += NT) {
-        const int lx = e % X, ly = (e / X) % Y, lz = e / (X * Y);
-        float v = 0.f;
-        if (lx < ext[0] + 1 + hx && ly < ext[1] + 1 + hy && (DIM == 2 || lz < ext[2] + 1 + hz)) {
+    float a[ROUNDS], b[ROUNDS];
+#pragma unroll
+    for (int k = 0; k < ROUNDS; k++) {
+        const int e = tid + k * NT;
+        const int lx = e % G::FX, ly = (e / G::FX) % G::FY, lz = e / G::FXY;
+        a[k] = b[k] = 0.f;
+        if (lx < ext[0] + hx && ly < ext[1] + 1 + hy && lz < (DIM == 2 ? 1 : ext[2] + 1 + hz)) {
             const int64_t g = (int64_t)(t0[0] - hx + lx) + (int64_t)P.sy * (t0[1] - hy + ly) +
                               (DIM == 3 ? (int64_t)P.sz * (t0[2] - hz + lz) : 0);
-            v = src[g];
+            a[k] = src[g];
+            b[k] = src[g + 1];
         }
-        Fl[G::foff(F) + e] = v;
     }
-    if constexpr (F < 5) stage_fields<G, DIM, F + 1, NT>(Fl, P, t0, ext, tid);
+    if constexpr (F < 5 && ROUNDS <= 2) stage_fields<G, DIM, F + 1, NT>(Fl, P, t0, ext, tid);
+#pragma unroll
+    for (int k = 0; k < ROUNDS; k++) {
+        const int e = tid + k * NT;
+        if (e < N) Fl[G::foff(F) + e] = make_float2(a[k], b[k] - a[k]);
+    }
+    if constexpr (F < 5 && ROUNDS > 2) stage_fields<G, DIM, F + 1, NT>(Fl, P, t0, ext, tid);
 }
 
 // ------------------------------------------------------------------ the fused kernel
@@ -552,9 +572,7 @@ __device__ inline void flush_current(const unsigned long long* __restrict__ Jl, 
         if (a == 0ull) continue;
         const int c = (e >= G::joff(1)) + (e >= G::joff(2));
         const int r = e - (c == 0 ? 0 : (c == 1 ? G::joff(1) : G::joff(2)));
-        const int X = c == 0 ? G::jdim(0, 0) : (c == 1 ? G::jdim(1, 0) : G::jdim(2, 0));
-        const int Y = c == 0 ? G::jdim(0, 1) : (c == 1 ? G::jdim(1, 1) : G::jdim(2, 1));
-        const int lx = r % X, ly = (r / X) % Y, lz = r / (X * Y);
+        const int lx = r % G::JX, ly = (r / G::JX) % G::JY, lz = r / (G::JX * G::JY);
         if (lx < ext[0] + (c == 0 ? 2 : 3) && ly < ext[1] + (c == 1 ? 2 : 3) &&
             (DIM == 2 || lz < ext[2] + (c == 2 ? 2 : 3))) {
             const int64_t g = (int64_t)(t0[0] - 1 + lx) + (int64_t)P.sy * (t0[1] - 1 + ly) +
@@ -570,13 +588,12 @@ __device__ inline LdsAcc<G> lds_acc(unsigned long long* Jl, int nx, int ny, int 
 {
     LdsAcc<G> acc;
     acc.J = reinterpret_cast<char*>(Jl);
+    // 24-bit multiply-adds; region places are non-negative
+    const unsigned b = 8u * (unsigned)nx + __umul24((unsigned)acc.sy(0), (unsigned)ny) +
+                       (DIM == 3 ? __umul24((unsigned)acc.sz(0), (unsigned)nz) : 0u);
 #pragma unroll
-    for (int c = 0; c < 3; c++) {
-        // 24-bit multiply-adds; region indices are non-negative
-        const unsigned b = 8u * (unsigned)nx + __umul24((unsigned)acc.sy(c), (unsigned)ny) +
-                           (DIM == 3 ? __umul24((unsigned)acc.sz(c), (unsigned)nz) : 0u);
+    for (int c = 0; c < 3; c++)
         acc.at[c] = 8 * G::joff(c) + 8 + acc.sy(c) + (DIM == 3 ? acc.sz(c) : 0) + (int)b;
-    }
     return acc;
 }
 
@@ -586,7 +603,7 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
 {
     using G = Geo<DIM, TX, TY, TZ>;
     __shared__ __attribute__((aligned(16))) unsigned char lds[G::LDS_BYTES];
-    float* const Fl = reinterpret_cast<float*>(lds);                                      // E, B
+    const char* const Fl = reinterpret_cast<const char*>(lds);                            // E, B
     unsigned long long* const Jl = reinterpret_cast<unsigned long long*>(lds + G::FBYTES);  // J
 
     const int unit = xcd_contiguous(blk, nblk);
@@ -601,7 +618,7 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
     const int mco = frame_sheared(FRAME) ? mig_center(P.mg, tsy, true) : tsy;
     const int mci = frame_sheared(FRAME) ? mig_center(P.mg, tsy, false) : tsy;
 
-    stage_fields<G, DIM, 0, NT>(Fl, P, t0, ext, tid);
+    stage_fields<G, DIM, 0, NT>(reinterpret_cast<float2*>(lds), P, t0, ext, tid);
     if (fuse)
         for (int e = tid; e < G::JTOT; e += NT) Jl[e] = 0ull;
     if (tid < kMaxSpecies * kMigDirs) mc[tid] = 0u;
@@ -855,10 +872,8 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
     if (fuse) flush_current<G, DIM, NT>(Jl, P, t0, ext, tid);
 }
 
-// 3D tiles: compact regions (48.4 KB of LDS for 8^3) let three workgroups share a CU, so the
-// register budget is set for 6 waves per SIMD.  2D tiles of 16x16 and 8x8 (16 KB and less) fit
-// eight waves per SIMD in 64 VGPRs (a few spilled: 2-4 % faster for the leaky box than at the
-// 81-93 VGPRs of no budget); the larger 2D tiles are bound by their LDS first.
+// Register budgets: 3D for the 6 waves per SIMD of two 12-wave workgroups a CU; 2D tiles of 8x8 (7 KB of
+// LDS) fit eight waves per SIMD in 64 VGPRs, the larger 2D tiles are bound by their LDS first.
 template <int DIM, int TX, int TY, int TZ, int FRAME, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIM == 3 ? 6 : 8)))
 void gpd_kernel(StepDev P, int fuse)
@@ -920,10 +935,14 @@ __global__ __launch_bounds__(NT) void deposit_kernel(StepDev P)
 }
 
 // ------------------------------------------------------------------ launchers
-// threads per workgroup: 3D tiles hold a 56 KB LDS footprint (2 workgroups per CU), so they
-// use 8 waves per workgroup to keep 16 waves per CU
-template <int DIM>
-constexpr int threads_for() { return DIM == 3 ? 512 : 256; }
+// Threads per workgroup: the paired field regions leave LDS for two workgroups a CU at 8^3 tiles (72 KB each;
+// three of 48 KB before), and twelve waves in each keep the CU's 24; the larger 2D tiles have as many more
+// threads as cells.  Ten waves did not pair up on the four SIMDs (push at 256^3 7.8 ms against 6.1), eight
+// with more registers were slower too (6.3).
+constexpr int threads_for(int dim, int cells)
+{
+    return dim == 3 ? (cells == 512 ? 768 : 512) : (cells <= 256 ? 256 : cells);
+}
 
 // A tile's workgroup walks its particles a round of NT slots after another, each round waiting for
 // its loads (3 to 5 us), so a box of few tiles is bound by that chain on an idle chip.  Its tiles are
@@ -931,9 +950,9 @@ constexpr int threads_for() { return DIM == 3 ? 512 : 256; }
 // whole round of a species: more parts only add their staging and flush (four parts a tile instead of
 // two made the 384^2 box's push slower, 75 -> 84 us).  The 64^2 box of the parity tests (16 tiles of 4096
 // slots a species): 84 us whole, 19 us in 256 workgroups; 20 x 12 x 16 cells: 32 -> 28 us.
-int tile_split(int dim, int64_t n_tiles, int64_t slots_per_tile)
+int tile_split(int dim, const int t[3], int64_t n_tiles, int64_t slots_per_tile)
 {
-    const int64_t want = dim == 3 ? 512 : 1024, nt = dim == 3 ? threads_for<3>() : threads_for<2>();
+    const int64_t want = dim == 3 ? 512 : 1024, nt = threads_for(dim, t[0] * t[1] * t[2]);
     int l = 0;
     while (l < 6 && (n_tiles << l) < want && (slots_per_tile >> l) > nt) l++;
     return l;
@@ -942,7 +961,7 @@ int tile_split(int dim, int64_t n_tiles, int64_t slots_per_tile)
 template <int DIM, int TX, int TY, int TZ>
 static hipError_t launch_shape(const StepDev& P, int fuse, hipStream_t st)
 {
-    constexpr int NT = threads_for<DIM>();
+    constexpr int NT = threads_for(DIM, TX * TY * TZ);
     const dim3 grid((unsigned)P.tl.n_tiles << P.lsplit), block(NT);
     switch (P.frame) {
     case kShear:
@@ -967,7 +986,7 @@ static hipError_t launch_shape(const StepDev& P, int fuse, hipStream_t st)
 template <int DIM, int TX, int TY, int TZ>
 static hipError_t launch_dep_shape(const StepDev& P, hipStream_t st)
 {
-    constexpr int NT = threads_for<DIM>();
+    constexpr int NT = threads_for(DIM, TX * TY * TZ);
     deposit_kernel<DIM, TX, TY, TZ, NT><<<dim3((unsigned)P.tl.n_tiles << P.lsplit), dim3(NT), 0, st>>>(P);
     return hipGetLastError();
 }
@@ -1001,7 +1020,7 @@ template <int DIM, int TX, int TY, int TZ>
 static hipError_t launch_batch_shape(const StepDev* table, UnitMap m, int blocks, int frame,
                                      hipStream_t st)
 {
-    constexpr int NT = threads_for<DIM>();
+    constexpr int NT = threads_for(DIM, TX * TY * TZ);
     switch (frame) {
     case kShear: gpd_batch<DIM, TX, TY, TZ, kShear, NT><<<blocks, NT, 0, st>>>(table, m); break;
     case kExpand: gpd_batch<DIM, TX, TY, TZ, kExpand, NT><<<blocks, NT, 0, st>>>(table, m); break;

@@ -432,7 +432,7 @@ struct MigPair {
 bool tile_shape_supported(int dim, const int t[3]);
 // log2 of the workgroups per tile of a push or deposit launch over n_tiles tiles (of all its boxes),
 // for a box with slots_per_tile slots of the fuller species a tile on average
-int tile_split(int dim, int64_t n_tiles, int64_t slots_per_tile);
+int tile_split(int dim, const int t[3], int64_t n_tiles, int64_t slots_per_tile);
 // supported tile shapes (batched: those of the batched launch); the default shape comes first
 int tile_candidates(int dim, bool batched, int (*out)[3], int max);
 hipError_t launch_gather_push(const StepDev& P, const int t[3], int fuse, hipStream_t st);
