@@ -224,150 +224,183 @@ __device__ inline float renorm(float s, int& dc)
 }
 
 // ------------------------------------------------------------------ Esirkepov deposit
-// CIC shape along one axis about the nearest node C of the old position (xi0, xi1: old and new position
-// relative to it): S is the neighbour on the old position's side, X the other one, which only a particle
-// that crosses C reaches.  Weights before the move on C and S (none on X) and their changes.
+// CIC shape along one axis: L and U are the nodes around the old position (offset o from L, then o + D); a
+// particle that leaves [0, 1] also reaches the node beyond, X (below L or above U).
 struct Shape {
-    float c0, s0;      // weights on C and S
-    float dc, ds, dx;  // changes on C, S and X
-    uint32_t sign;     // sign bit of the old position: S below C
-    bool cross;
+    float l, u;        // weights on L and U before the move
+    float dl, du, dx;  // their changes and X's
+    float e, x;        // what flows through the edge L-U, and through the one to X (towards +)
 };
-__device__ inline float flip(float v, uint32_t sign) { return __uint_as_float(__float_as_uint(v) ^ sign); }
-__device__ inline Shape shape(float xi0, float xi1)
+__device__ inline Shape shape(float o, float D)
 {
     Shape A;
-    A.sign = __float_as_uint(xi0) & 0x80000000u;
-    const float t1 = flip(xi1, A.sign);  // the new position counted towards S
-    A.s0 = fabsf(xi0);
-    A.c0 = 1.f - A.s0;
-    A.dc = (1.f - fabsf(xi1)) - A.c0;
-    A.ds = fmaxf(0.f, t1) - A.s0;
-    A.dx = fmaxf(0.f, -t1);
-    A.cross = t1 < 0.f;
+    A.l = 1.f - o;
+    A.u = o;
+    // each way's excess from the node that it crosses: no rounding at the size of o + D
+    const float below = fminf(D + A.u, 0.f), above = fmaxf(D - A.l, 0.f);
+    A.x = below + above;
+    A.e = D - A.x;
+    A.dl = below - A.e;
+    A.du = A.e - above;
+    A.dx = fabsf(A.x);
     return A;
 }
 // transverse factors of an axis with the charge factor q/dt folded in: node weight w gives
 // (w0 + dw/2) and (w0/2 + dw/3)
 struct Factor {
-    float c1, c2, s1, s2, x1, x2;
+    float l1, l2, u1, u2, x1, x2;
 };
 __device__ inline Factor factor(const Shape& A, float q, float qh, float qt)
 {
-    return Factor{q * A.c0 + qh * A.dc, qh * A.c0 + qt * A.dc, q * A.s0 + qh * A.ds,
-                  qh * A.s0 + qt * A.ds, qh * A.dx, qt * A.dx};
+    return Factor{q * A.l + qh * A.dl, qh * A.l + qt * A.dl, q * A.u + qh * A.du,
+                  qh * A.u + qt * A.du, qh * A.dx, qt * A.dx};
 }
 
 // Esirkepov decomposition of the density change into currents (CIC):
-//   J_x on the two edges around the nearest node: -q/dt DS_x[-1] P and +q/dt DS_x[+1] P,
+//   J_x on an edge: q/dt times what flows through it times P of its node across,
 //   P = S0_y (S0_z + DS_z/2) + DS_y (S0_z/2 + DS_z/3) (cyclic for y and z);
 //   2D: P = S0_y + DS_y/2, and J_z = q dz/dt (S0_x (S0_y + DS_y/2) + DS_x (S0_y/2 + DS_y/3)).
-// A particle that crosses its nearest node on no axis (61 % of them at theta = 0.3, 80 % at 0.05) has 12
-// (3D) / 8 (2D) terms of the 54 / 21: those on C and S, which every lane adds at addresses of its own.
-// The terms on X and on its edge stand in one branch for every combination of crossed axes (seven in 3D).
-// With a mask for each term about C instead, a wave ran all 54 on a quarter of its lanes.  The push of
-// 2 x 134 M particles at 256^3: shear 6.56 -> 6.35 ms; 128 x 128 x 512, expand: 5.67 -> 5.30 ms; 2048^2,
-// leaky: 4.39 -> 4.34 ms.  What bounds it now is LDS: its units are active 81-86 % of the cycles in 3D, half
-// of that on bank conflicts of scattered particles.
+// A particle that crosses a node on no axis (61 % of them at theta = 0.3, 80 % at 0.05) has the 12
+// (3D) / 8 (2D) terms of the cell's own edges out of 54 / 21, all at fixed ways from one place.  The terms on
+// X nodes and edges stand in a branch per combination of crossed axes (seven in 3D) for all components.
+// With a mask for each term about the nearest node instead, a wave ran all 54 on a quarter of its lanes.
+// Fixed ways from one place keep the dense terms at one address register: 256^3 shear 6.05 -> 5.96 ms,
+// 128 x 128 x 512 expand 5.04 -> 4.96 ms, 2048^2 leaky 4.38 -> 4.33 ms.
 //
-// One component along axis E, nodes over the axes F and S (its Factor): i is the place of the edge between
-// C and S of E at the C nodes of the others; oE, oF, oS: the way from C to S of each axis.
-template <class Acc>
-__device__ inline void deposit3(Acc& acc, int c, int i, int oE, int oF, int oS, const Shape& E, const Shape& F,
-                                const Factor& W, const Shape& S)
-{
-    const float e = flip(E.ds, E.sign), x = flip(E.dx, E.sign ^ 0x80000000u);
-    const float cc = F.c0 * W.c1 + F.dc * W.c2, cs = F.c0 * W.s1 + F.dc * W.s2;
-    const float sc = F.s0 * W.c1 + F.ds * W.c2, ss = F.s0 * W.s1 + F.ds * W.s2;
-    acc.add(c, i, e * cc);
-    acc.add(c, i + oS, e * cs);
-    acc.add(c, i + oF, e * sc);
-    acc.add(c, i + oF + oS, e * ss);
-    if (E.cross) {
-        const int k = i - oE;
-        acc.add(c, k, x * cc);
-        acc.add(c, k + oS, x * cs);
-        acc.add(c, k + oF, x * sc);
-        acc.add(c, k + oF + oS, x * ss);
-    }
-    if (F.cross) {
-        const int k = i - oF;
-        const float xc = F.dx * W.c2, xs = F.dx * W.s2;
-        acc.add(c, k, e * xc);
-        acc.add(c, k + oS, e * xs);
-        if (E.cross) {
-            acc.add(c, k - oE, x * xc);
-            acc.add(c, k - oE + oS, x * xs);
-        }
-    }
-    if (S.cross) {
-        const int k = i - oS;
-        const float cx = F.c0 * W.x1 + F.dc * W.x2, sx = F.s0 * W.x1 + F.ds * W.x2;
-        acc.add(c, k, e * cx);
-        acc.add(c, k + oF, e * sx);
-        if (E.cross) {
-            acc.add(c, k - oE, x * cx);
-            acc.add(c, k - oE + oF, x * sx);
-        }
-        if (F.cross) {
-            const float xx = F.dx * W.x2;
-            acc.add(c, k - oF, e * xx);
-            if (E.cross) acc.add(c, k - oF - oE, x * xx);
-        }
-    }
-}
-
-// the same in 2D for J_x and J_y: nodes over F alone
-template <class Acc>
-__device__ inline void deposit2(Acc& acc, int c, int i, int oE, int oF, const Shape& E, const Shape& F, float q)
-{
-    const float e = q * flip(E.ds, E.sign), x = q * flip(E.dx, E.sign ^ 0x80000000u);
-    const float pc = F.c0 + 0.5f * F.dc, ps = F.s0 + 0.5f * F.ds, px = 0.5f * F.dx;
-    acc.add(c, i, e * pc);
-    acc.add(c, i + oF, e * ps);
-    if (E.cross) {
-        acc.add(c, i - oE, x * pc);
-        acc.add(c, i - oE + oF, x * ps);
-    }
-    if (F.cross) {
-        acc.add(c, i - oF, e * px);
-        if (E.cross) acc.add(c, i - oE - oF, x * px);
-    }
-}
-
-// Acc: place at[c] of the C node on every axis in component c's array, strides kX, sy(c), sz(c)
+// Acc: add<C, IX, IY, IZ>(way, v) adds to component C at the particle's cell + (IX, IY, IZ) + way;
+// node<A>(x), edge<A>(x): the way from L (from the edge L-U) along axis A to X by the sign of x.
 template <int DIM, class Acc>
 __device__ inline void esirkepov(Acc& acc, const Shape& X, const Shape& Y, const Shape& Z, float q_dt, float dz)
 {
-    // the edge between C and S lies at C's index above it and at the one below
-    const int bx = X.sign ? -Acc::kX : 0, ox = X.sign ? -Acc::kX : Acc::kX;
-    const int by = Y.sign ? -1 : 0, bz = Z.sign ? -1 : 0, gy = Y.sign ? -1 : 1, gz = Z.sign ? -1 : 1;
-    if (DIM == 3) {
+    const bool crx = X.x != 0.f, cry = Y.x != 0.f, crz = DIM == 3 && Z.x != 0.f;
+    if constexpr (DIM == 3) {
         const float qh = 0.5f * q_dt, qt = (1.f / 3.f) * q_dt;
         const Factor FZ = factor(Z, q_dt, qh, qt), FY = factor(Y, q_dt, qh, qt);
-        deposit3(acc, 0, acc.at[0] + bx, ox, gy * acc.sy(0), gz * acc.sz(0), X, Y, FZ, Z);
-        deposit3(acc, 1, acc.at[1] + by * acc.sy(1), gy * acc.sy(1), ox, gz * acc.sz(1), Y, X, FZ, Z);
-        deposit3(acc, 2, acc.at[2] + bz * acc.sz(2), gz * acc.sz(2), ox, gy * acc.sy(2), Z, X, FY, Y);
-    } else {
-        deposit2(acc, 0, acc.at[0] + bx, ox, gy * acc.sy(0), X, Y, q_dt);
-        deposit2(acc, 1, acc.at[1] + by * acc.sy(1), gy * acc.sy(1), ox, Y, X, q_dt);
-        const float jz = q_dt * dz;
-        const int i = acc.at[2], oy = gy * acc.sy(2);
-        const float c1 = Y.c0 + 0.5f * Y.dc, c2 = 0.5f * Y.c0 + (1.f / 3.f) * Y.dc;
-        const float s1 = Y.s0 + 0.5f * Y.ds, s2 = 0.5f * Y.s0 + (1.f / 3.f) * Y.ds;
-        acc.add(2, i, jz * (X.c0 * c1 + X.dc * c2));
-        acc.add(2, i + oy, jz * (X.c0 * s1 + X.dc * s2));
-        acc.add(2, i + ox, jz * (X.s0 * c1 + X.ds * c2));
-        acc.add(2, i + ox + oy, jz * (X.s0 * s1 + X.ds * s2));
-        if (X.cross) {
-            acc.add(2, i - ox, jz * (X.dx * c2));
-            acc.add(2, i - ox + oy, jz * (X.dx * s2));
+        // products over two axes: nodes L and U of the first, then of the second
+        const float yz00 = Y.l * FZ.l1 + Y.dl * FZ.l2, yz01 = Y.l * FZ.u1 + Y.dl * FZ.u2;
+        const float yz10 = Y.u * FZ.l1 + Y.du * FZ.l2, yz11 = Y.u * FZ.u1 + Y.du * FZ.u2;
+        const float xz00 = X.l * FZ.l1 + X.dl * FZ.l2, xz01 = X.l * FZ.u1 + X.dl * FZ.u2;
+        const float xz10 = X.u * FZ.l1 + X.du * FZ.l2, xz11 = X.u * FZ.u1 + X.du * FZ.u2;
+        const float xy00 = X.l * FY.l1 + X.dl * FY.l2, xy01 = X.l * FY.u1 + X.dl * FY.u2;
+        const float xy10 = X.u * FY.l1 + X.du * FY.l2, xy11 = X.u * FY.u1 + X.du * FY.u2;
+        acc.template add<0, 0, 0, 0>(0, X.e * yz00);
+        acc.template add<0, 0, 0, 1>(0, X.e * yz01);
+        acc.template add<0, 0, 1, 0>(0, X.e * yz10);
+        acc.template add<0, 0, 1, 1>(0, X.e * yz11);
+        acc.template add<1, 0, 0, 0>(0, Y.e * xz00);
+        acc.template add<1, 0, 0, 1>(0, Y.e * xz01);
+        acc.template add<1, 1, 0, 0>(0, Y.e * xz10);
+        acc.template add<1, 1, 0, 1>(0, Y.e * xz11);
+        acc.template add<2, 0, 0, 0>(0, Z.e * xy00);
+        acc.template add<2, 0, 1, 0>(0, Z.e * xy01);
+        acc.template add<2, 1, 0, 0>(0, Z.e * xy10);
+        acc.template add<2, 1, 1, 0>(0, Z.e * xy11);
+        if (crx) {
+            const int d = acc.template edge<0>(X.x), k = acc.template node<0>(X.x);
+            acc.template add<0, 0, 0, 0>(d, X.x * yz00);
+            acc.template add<0, 0, 0, 1>(d, X.x * yz01);
+            acc.template add<0, 0, 1, 0>(d, X.x * yz10);
+            acc.template add<0, 0, 1, 1>(d, X.x * yz11);
+            const float ey = Y.e * X.dx, ez = Z.e * X.dx;
+            acc.template add<1, 0, 0, 0>(k, ey * FZ.l2);
+            acc.template add<1, 0, 0, 1>(k, ey * FZ.u2);
+            acc.template add<2, 0, 0, 0>(k, ez * FY.l2);
+            acc.template add<2, 0, 1, 0>(k, ez * FY.u2);
         }
-        if (Y.cross) {
-            const float x1 = 0.5f * Y.dx, x2 = (1.f / 3.f) * Y.dx;
-            acc.add(2, i - oy, jz * (X.c0 * x1 + X.dc * x2));
-            acc.add(2, i + ox - oy, jz * (X.s0 * x1 + X.ds * x2));
-            if (X.cross) acc.add(2, i - ox - oy, jz * (X.dx * x2));
+        if (cry) {
+            const int d = acc.template edge<1>(Y.x), k = acc.template node<1>(Y.x);
+            acc.template add<1, 0, 0, 0>(d, Y.x * xz00);
+            acc.template add<1, 0, 0, 1>(d, Y.x * xz01);
+            acc.template add<1, 1, 0, 0>(d, Y.x * xz10);
+            acc.template add<1, 1, 0, 1>(d, Y.x * xz11);
+            const float ex = X.e * Y.dx;
+            acc.template add<0, 0, 0, 0>(k, ex * FZ.l2);
+            acc.template add<0, 0, 0, 1>(k, ex * FZ.u2);
+            acc.template add<2, 0, 0, 0>(k, Z.e * (X.l * FY.x1 + X.dl * FY.x2));
+            acc.template add<2, 1, 0, 0>(k, Z.e * (X.u * FY.x1 + X.du * FY.x2));
+        }
+        if (crz) {
+            const int d = acc.template edge<2>(Z.x), k = acc.template node<2>(Z.x);
+            acc.template add<2, 0, 0, 0>(d, Z.x * xy00);
+            acc.template add<2, 0, 1, 0>(d, Z.x * xy01);
+            acc.template add<2, 1, 0, 0>(d, Z.x * xy10);
+            acc.template add<2, 1, 1, 0>(d, Z.x * xy11);
+            acc.template add<0, 0, 0, 0>(k, X.e * (Y.l * FZ.x1 + Y.dl * FZ.x2));
+            acc.template add<0, 0, 1, 0>(k, X.e * (Y.u * FZ.x1 + Y.du * FZ.x2));
+            acc.template add<1, 0, 0, 0>(k, Y.e * (X.l * FZ.x1 + X.dl * FZ.x2));
+            acc.template add<1, 1, 0, 0>(k, Y.e * (X.u * FZ.x1 + X.du * FZ.x2));
+        }
+        if (crx && cry) {
+            const int kx = acc.template node<0>(X.x), ky = acc.template node<1>(Y.x);
+            const int ax = acc.template edge<0>(X.x) + ky, ay = kx + acc.template edge<1>(Y.x);
+            const float fx = X.x * Y.dx, fy = Y.x * X.dx;
+            acc.template add<0, 0, 0, 0>(ax, fx * FZ.l2);
+            acc.template add<0, 0, 0, 1>(ax, fx * FZ.u2);
+            acc.template add<1, 0, 0, 0>(ay, fy * FZ.l2);
+            acc.template add<1, 0, 0, 1>(ay, fy * FZ.u2);
+            acc.template add<2, 0, 0, 0>(kx + ky, Z.e * X.dx * FY.x2);
+        }
+        if (crx && crz) {
+            const int kx = acc.template node<0>(X.x), kz = acc.template node<2>(Z.x);
+            const int ax = acc.template edge<0>(X.x) + kz, az = kx + acc.template edge<2>(Z.x);
+            const float fz = Z.x * X.dx;
+            acc.template add<0, 0, 0, 0>(ax, X.x * (Y.l * FZ.x1 + Y.dl * FZ.x2));
+            acc.template add<0, 0, 1, 0>(ax, X.x * (Y.u * FZ.x1 + Y.du * FZ.x2));
+            acc.template add<2, 0, 0, 0>(az, fz * FY.l2);
+            acc.template add<2, 0, 1, 0>(az, fz * FY.u2);
+            acc.template add<1, 0, 0, 0>(kx + kz, Y.e * X.dx * FZ.x2);
+        }
+        if (cry && crz) {
+            const int ky = acc.template node<1>(Y.x), kz = acc.template node<2>(Z.x);
+            const int ay = acc.template edge<1>(Y.x) + kz, az = ky + acc.template edge<2>(Z.x);
+            acc.template add<1, 0, 0, 0>(ay, Y.x * (X.l * FZ.x1 + X.dl * FZ.x2));
+            acc.template add<1, 1, 0, 0>(ay, Y.x * (X.u * FZ.x1 + X.du * FZ.x2));
+            acc.template add<2, 0, 0, 0>(az, Z.x * (X.l * FY.x1 + X.dl * FY.x2));
+            acc.template add<2, 1, 0, 0>(az, Z.x * (X.u * FY.x1 + X.du * FY.x2));
+            acc.template add<0, 0, 0, 0>(ky + kz, X.e * Y.dx * FZ.x2);
+            if (crx) {
+                const int kx = acc.template node<0>(X.x);
+                acc.template add<0, 0, 0, 0>(acc.template edge<0>(X.x) + ky + kz, X.x * Y.dx * FZ.x2);
+                acc.template add<1, 0, 0, 0>(kx + ay, Y.x * X.dx * FZ.x2);
+                acc.template add<2, 0, 0, 0>(kx + az, Z.x * X.dx * FY.x2);
+            }
+        }
+    } else {
+        const float ex = q_dt * X.e, ey = q_dt * Y.e, jz = q_dt * dz;
+        const float xl = X.l + 0.5f * X.dl, xu = X.u + 0.5f * X.du;
+        const float yl = Y.l + 0.5f * Y.dl, yu = Y.u + 0.5f * Y.du;
+        const float yl2 = 0.5f * Y.l + (1.f / 3.f) * Y.dl, yu2 = 0.5f * Y.u + (1.f / 3.f) * Y.du;
+        acc.template add<0, 0, 0, 0>(0, ex * yl);
+        acc.template add<0, 0, 1, 0>(0, ex * yu);
+        acc.template add<1, 0, 0, 0>(0, ey * xl);
+        acc.template add<1, 1, 0, 0>(0, ey * xu);
+        acc.template add<2, 0, 0, 0>(0, jz * (X.l * yl + X.dl * yl2));
+        acc.template add<2, 0, 1, 0>(0, jz * (X.l * yu + X.dl * yu2));
+        acc.template add<2, 1, 0, 0>(0, jz * (X.u * yl + X.du * yl2));
+        acc.template add<2, 1, 1, 0>(0, jz * (X.u * yu + X.du * yu2));
+        if (crx) {
+            const int d = acc.template edge<0>(X.x), k = acc.template node<0>(X.x);
+            const float fx = q_dt * X.x, jx = jz * X.dx;
+            acc.template add<0, 0, 0, 0>(d, fx * yl);
+            acc.template add<0, 0, 1, 0>(d, fx * yu);
+            acc.template add<1, 0, 0, 0>(k, ey * (0.5f * X.dx));
+            acc.template add<2, 0, 0, 0>(k, jx * yl2);
+            acc.template add<2, 0, 1, 0>(k, jx * yu2);
+        }
+        if (cry) {
+            const int d = acc.template edge<1>(Y.x), k = acc.template node<1>(Y.x);
+            const float fy = q_dt * Y.x, x1 = 0.5f * Y.dx, x2 = (1.f / 3.f) * Y.dx;
+            acc.template add<1, 0, 0, 0>(d, fy * xl);
+            acc.template add<1, 1, 0, 0>(d, fy * xu);
+            acc.template add<0, 0, 0, 0>(k, ex * x1);
+            acc.template add<2, 0, 0, 0>(k, jz * (X.l * x1 + X.dl * x2));
+            acc.template add<2, 1, 0, 0>(k, jz * (X.u * x1 + X.du * x2));
+            if (crx) {
+                const int kx = acc.template node<0>(X.x);
+                acc.template add<0, 0, 0, 0>(acc.template edge<0>(X.x) + k, q_dt * X.x * x1);
+                acc.template add<1, 0, 0, 0>(kx + d, fy * (0.5f * X.dx));
+                acc.template add<2, 0, 0, 0>(kx + k, jz * X.dx * x2);
+            }
         }
     }
 }
@@ -412,37 +445,50 @@ struct Geo {
 // contribution is 2^30 units, is truncated to int32 and added with ds_add_u64 (integer LDS
 // atomics cost a few cycles per wave instruction, while FP32 LDS atomics are serialised per
 // lane).  Integer sums are exact and independent of the order.
-template <class G>
+template <class G, int DIM>
 struct LdsAcc {
     char* J;
-    int at[3];  // places in bytes
-    static constexpr int kX = 8;
-    static __device__ constexpr int sy(int) { return 8 * G::JX; }
-    static __device__ constexpr int sz(int) { return 8 * G::JX * G::JY; }
-    __device__ inline void add(int, int i, float v)
+    unsigned at;  // place in bytes of the particle's cell, counted from the tile's first
+    static constexpr int pitch(int a) { return 8 * (a == 0 ? 1 : (a == 1 ? G::JX : G::JX * G::JY)); }
+    template <int C, int IX, int IY, int IZ>
+    __device__ inline void add(int way, float v)
     {
+        constexpr int place = 8 * G::joff(C) + (1 + IX) * pitch(0) + (1 + IY) * pitch(1) + (DIM == 3 ? (1 + IZ) * pitch(2) : 0);
         // v_cvt_i32_f32: truncates, saturates
-        atomicAdd(reinterpret_cast<unsigned long long*>(J + i), (unsigned long long)(long long)(int)v);
+        atomicAdd(reinterpret_cast<unsigned long long*>(J + (at + way) + place), (unsigned long long)(long long)(int)v);
     }
+    template <int A>
+    __device__ inline int edge(float x) const { return x < 0.f ? -pitch(A) : pitch(A); }
+    template <int A>
+    __device__ inline int node(float x) const { return x < 0.f ? -pitch(A) : 2 * pitch(A); }
 };
+template <class G, int DIM>
+__device__ inline LdsAcc<G, DIM> lds_acc(unsigned long long* Jl, int rx, int ry, int rz)
+{
+    using A = LdsAcc<G, DIM>;
+    // 24-bit multiply-adds; region places are non-negative
+    return A{reinterpret_cast<char*>(Jl), 8u * (unsigned)rx + __umul24((unsigned)A::pitch(1), (unsigned)ry) +
+                                              (DIM == 3 ? __umul24((unsigned)A::pitch(2), (unsigned)rz) : 0u)};
+}
 
 // Global accumulator on the guarded current arrays (slow path).
 struct GlobalAcc {
     float* const* J;
-    int at[3];  // places in elements
-    int stride_y, stride_z;
-    static constexpr int kX = 1;
-    __device__ inline int sy(int) const { return stride_y; }
-    __device__ inline int sz(int) const { return stride_z; }
-    __device__ inline void add(int c, int i, float v)
+    int at;  // the particle's cell; a guarded array holds less than 2^31 floats
+    int sy, sz;
+    template <int C, int IX, int IY, int IZ>
+    __device__ inline void add(int way, float v)
     {
-        if (v != 0.f) unsafeAtomicAdd(&J[c][i], v);
+        if (v != 0.f) unsafeAtomicAdd(&J[C][at + IX + sy * IY + sz * IZ + way], v);
     }
+    template <int A>
+    __device__ inline int edge(float x) const { return (x < 0.f ? -1 : 1) * (A == 0 ? 1 : (A == 1 ? sy : sz)); }
+    template <int A>
+    __device__ inline int node(float x) const { return (x < 0.f ? -1 : 2) * (A == 0 ? 1 : (A == 1 ? sy : sz)); }
 };
 __device__ inline GlobalAcc global_acc(const StepDev& P, int x, int y, int z)
 {
-    const int i = x + P.sy * y + P.sz * z;  // a guarded array holds less than 2^31 floats
-    return GlobalAcc{P.J, {i, i, i}, P.sy, P.sz};
+    return GlobalAcc{P.J, x + P.sy * y + P.sz * z, P.sy, P.sz};
 }
 
 // CIC interpolation of staged component F: ad is the place of the lower corner in bytes, (wa, wb, wc) the
@@ -582,21 +628,6 @@ __device__ inline void flush_current(const unsigned long long* __restrict__ Jl, 
     }
 }
 
-// (nx, ny, nz): the nearest node counted from the tile's origin; a region starts one before it
-template <class G, int DIM>
-__device__ inline LdsAcc<G> lds_acc(unsigned long long* Jl, int nx, int ny, int nz)
-{
-    LdsAcc<G> acc;
-    acc.J = reinterpret_cast<char*>(Jl);
-    // 24-bit multiply-adds; region places are non-negative
-    const unsigned b = 8u * (unsigned)nx + __umul24((unsigned)acc.sy(0), (unsigned)ny) +
-                       (DIM == 3 ? __umul24((unsigned)acc.sz(0), (unsigned)nz) : 0u);
-#pragma unroll
-    for (int c = 0; c < 3; c++)
-        acc.at[c] = 8 * G::joff(c) + 8 + acc.sy(c) + (DIM == 3 ? acc.sz(c) : 0) + (int)b;
-    return acc;
-}
-
 template <int DIM, int TX, int TY, int TZ, int FRAME, int NT>
 __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P, int blk, int nblk,
                                                                 int fuse)
@@ -694,14 +725,12 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
 
             // ---- deposit xn -> xn + D
             if (fuse) {
-                const int hx = ox >= 0.5f, hy = oy >= 0.5f, hz = DIM == 3 ? (oz >= 0.5f) : 0;
-                const float x0 = ox - (float)hx, y0 = oy - (float)hy, z0 = oz - (float)hz;
-                const Shape SX = shape(x0, x0 + D.x), SY = shape(y0, y0 + D.y), SZ = shape(z0, z0 + D.z);
+                const Shape SX = shape(ox, D.x), SY = shape(oy, D.y), SZ = shape(oz, D.z);
                 if (in_tile) {
-                    LdsAcc<G> acc = lds_acc<G, DIM>(Jl, rx + hx, ry + hy, rz + hz);
+                    LdsAcc<G, DIM> acc = lds_acc<G, DIM>(Jl, rx, ry, rz);
                     esirkepov<DIM>(acc, SX, SY, SZ, S.q_dt * P.jscale, D.z);
                 } else {
-                    GlobalAcc acc = global_acc(P, cx + hx, cy + hy, DIM == 3 ? cz + hz : 0);
+                    GlobalAcc acc = global_acc(P, cx, cy, DIM == 3 ? cz : 0);
                     esirkepov<DIM>(acc, SX, SY, SZ, S.q_dt, D.z);
                 }
             } else {
@@ -918,14 +947,12 @@ __global__ __launch_bounds__(NT) void deposit_kernel(StepDev P)
             const int rx = cx - t0[0], ry = cy - t0[1], rz = DIM == 3 ? cz - t0[2] : 0;
             const bool in_tile = (unsigned)rx < (unsigned)ext[0] && (unsigned)ry < (unsigned)ext[1] &&
                                  (DIM == 2 || (unsigned)rz < (unsigned)ext[2]);
-            const int hx = ox >= 0.5f, hy = oy >= 0.5f, hz = DIM == 3 ? (oz >= 0.5f) : 0;
-            const float x0 = ox - (float)hx, y0 = oy - (float)hy, z0 = oz - (float)hz;
-            const Shape SX = shape(x0, x0 + D.x), SY = shape(y0, y0 + D.y), SZ = shape(z0, z0 + D.z);
+            const Shape SX = shape(ox, D.x), SY = shape(oy, D.y), SZ = shape(oz, D.z);
             if (in_tile) {
-                LdsAcc<G> acc = lds_acc<G, DIM>(Jl, rx + hx, ry + hy, rz + hz);
+                LdsAcc<G, DIM> acc = lds_acc<G, DIM>(Jl, rx, ry, rz);
                 esirkepov<DIM>(acc, SX, SY, SZ, S.q_dt * P.jscale, D.z);
             } else {
-                GlobalAcc acc = global_acc(P, cx + hx, cy + hy, DIM == 3 ? cz + hz : 0);
+                GlobalAcc acc = global_acc(P, cx, cy, DIM == 3 ? cz : 0);
                 esirkepov<DIM>(acc, SX, SY, SZ, S.q_dt, D.z);
             }
         }
