@@ -628,6 +628,33 @@ __device__ inline void flush_current(const unsigned long long* __restrict__ Jl, 
     }
 }
 
+// a particle as it is read through the sort permutation; in the leaky box with what its escape needs
+template <int DIM, int FRAME>
+struct Particle {
+    int32_t cell;
+    float o[DIM];
+    f3 u;
+    float dr[3];
+    uint32_t id;
+    __device__ inline void load(const StepDev& P, const SpeciesDev& S, uint32_t src)
+    {
+        cell = ld_at(S.cell_in, src);
+#pragma unroll
+        for (int d = 0; d < DIM; d++) o[d] = ld_at(S.off_in[d], src);
+        u = mk(ld_at(S.u_in[0], src), ld_at(S.u_in[1], src), ld_at(S.u_in[2], src));
+        if (FRAME == kLeaky) load_escape(P, S, src);
+    }
+    __device__ inline void load_escape(const StepDev& P, const SpeciesDev& S, uint32_t src)
+    {
+        id = ld_at(S.id_in, src);
+        if (P.leaky_mode == 0) {
+            dr[0] = ld_at(S.dr_in[0], src);
+            dr[1] = ld_at(S.dr_in[1], src);
+            if (P.use_3vec) dr[2] = ld_at(S.dr_in[2], src);
+        }
+    }
+};
+
 template <int DIM, int TX, int TY, int TZ, int FRAME, int NT>
 __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P, int blk, int nblk,
                                                                 int fuse)
@@ -662,19 +689,33 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
         uint32_t nesc = 0;  // probabilistic escapes (one counter add per wave, at the end)
         uint32_t nsl = 0;   // shearing box: superluminal effective velocities (likewise)
         const uint32_t beg = (uint32_t)S.toff[tile], end = (uint32_t)S.toff[tile + 1];
-        // the waves take 64-slot groups aligned to 32 slots (the 128-byte lines of the 4-byte
-        // particle arrays), so that their stores fill whole lines; the lanes before the tile's
-        // first slot idle in the first round
-        for (uint32_t slot = (beg & ~31u) + part * NT + tid; slot < end; slot += (uint32_t)NT << P.lsplit) {
-            if (slot < beg) continue;
-            uint32_t so = slot;
+        // The threads take the tile's slots from the first multiple of 32 on (the 128-byte lines of the
+        // 4-byte particle arrays, so that a wave's stores fill whole lines) and those before it last.
+        // A round's particle is read during the deposit of the round before, at an index read one round
+        // earlier still; past the last round both stay on the last slot.  The kernel without gather, push
+        // and deposit still takes 80-97 % of its time, so what counts is that every wave always has loads
+        // on their way, and that it waits for its stores no earlier than after a deposit: 256^3 shear
+        // 5.96 -> 5.84 ms, 128 x 128 x 512 expand 4.96 -> 4.80 ms, 1024^2 leaky 0.716 -> 0.675 ms.
+        const uint32_t count = end - beg, head = min(-beg & 31u, count);
+        auto slot_of = [&](uint32_t v) {
+            const uint32_t r = min(v, count - 1) + head;
+            return beg + (r < count ? r : r - count);
+        };
+        const uint32_t stride = (uint32_t)NT << P.lsplit;
+        uint32_t v = part * NT + tid, src = 0, src_next = 0;
+        Particle<DIM, FRAME> p;
+        if (v < count) {
+            src = (uint32_t)ld_at(S.perm, slot_of(v));
+            src_next = (uint32_t)ld_at(S.perm, slot_of(v + stride));
+            p.load(P, S, src);
+        }
+        for (; v < count; v += stride) {
+            uint32_t so = slot_of(v);
             asm("" : "+v"(so));  // keeps the 32-bit offset form (scalar base) for the stores
-            const uint32_t src = (uint32_t)ld_at(S.perm, slot);
             int cx, cy, cz;
-            P.cc.decode(ld_at(S.cell_in, src), cx, cy, cz);
-            const float ox = ld_at(S.off_in[0], src), oy = ld_at(S.off_in[1], src);
-            const float oz = DIM == 3 ? ld_at(S.off_in[2], src) : 0.f;
-            f3 u = mk(ld_at(S.u_in[0], src), ld_at(S.u_in[1], src), ld_at(S.u_in[2], src));
+            P.cc.decode(p.cell, cx, cy, cz);
+            const float ox = p.o[0], oy = p.o[1], oz = DIM == 3 ? p.o[2] : 0.f;
+            f3 u = p.u;
 
             const int rx = cx - t0[0], ry = cy - t0[1], rz = DIM == 3 ? cz - t0[2] : 0;
             const bool in_tile = (unsigned)rx < (unsigned)ext[0] && (unsigned)ry < (unsigned)ext[1] &&
@@ -723,26 +764,6 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
                   fabsf(dyt) < 1.f))
                 latch(P.err, (isfinite(u.x) && isfinite(u.y) && isfinite(u.z)) ? 1u : 2u);
 
-            // ---- deposit xn -> xn + D
-            if (fuse) {
-                const Shape SX = shape(ox, D.x), SY = shape(oy, D.y), SZ = shape(oz, D.z);
-                if (in_tile) {
-                    LdsAcc<G, DIM> acc = lds_acc<G, DIM>(Jl, rx, ry, rz);
-                    esirkepov<DIM>(acc, SX, SY, SZ, S.q_dt * P.jscale, D.z);
-                } else {
-                    GlobalAcc acc = global_acc(P, cx, cy, DIM == 3 ? cz : 0);
-                    esirkepov<DIM>(acc, SX, SY, SZ, S.q_dt, D.z);
-                }
-            } else {
-                st_at(S.ws_cell, so, P.cc.encode(cx, cy, cz));
-                st_at(S.ws_off[0], so, ox);
-                st_at(S.ws_off[1], so, oy);
-                if (DIM == 3) st_at(S.ws_off[2], so, oz);
-                st_at(S.ws_disp[0], so, D.x);
-                st_at(S.ws_disp[1], so, D.y);
-                st_at(S.ws_disp[2], so, D.z);
-            }
-
             // ---- new position: x' = x^n + D, then (shearing box) the shear move
             // y -= s Omega0 (x' + x^n)/2 dt (Sec. 2.2)
             if (frame_sheared(FRAME)) {
@@ -782,14 +803,15 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
             // ---- leaky box (Sec. 4.1); in the shearing and expanding frames on request, with the
             // displacement D of the deposit: comoving (relative to the shear flow), or primed
             if (FRAME == kLeaky || (FRAME != kPlain && P.escape)) {
-                const uint32_t pid = ld_at(S.id_in, src);
+                if (FRAME != kLeaky) p.load_escape(P, S, src);
+                const uint32_t pid = p.id;
                 if (P.leaky_mode == 0) {
                     // the z displacement is tracked only for the 3-vector test
-                    float rx = ld_at(S.dr_in[0], src) + D.x, ry = ld_at(S.dr_in[1], src) + D.y;
+                    float rx = p.dr[0] + D.x, ry = p.dr[1] + D.y;
                     float rz = 0.f;
                     float m = fmaxf(fabsf(rx), fabsf(ry));
                     if (P.use_3vec) {
-                        rz = ld_at(S.dr_in[2], src) + D.z;
+                        rz = p.dr[2] + D.z;
                         m = fmaxf(m, fabsf(rz));
                     }
                     if (m >= P.l_esc) {
@@ -868,7 +890,31 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
             st_at(S.u_out[0], so, u.x);
             st_at(S.u_out[1], so, u.y);
             st_at(S.u_out[2], so, u.z);
-            if (P.track_ids) st_at(S.id_out, so, ld_at(S.id_in, src));
+            if (P.track_ids) st_at(S.id_out, so, FRAME == kLeaky ? p.id : ld_at(S.id_in, src));
+
+            src = src_next;
+            p.load(P, S, src);
+            src_next = (uint32_t)ld_at(S.perm, slot_of(v + 2 * stride));
+
+            // ---- deposit xn -> xn + D
+            if (fuse) {
+                const Shape SX = shape(ox, D.x), SY = shape(oy, D.y), SZ = shape(oz, D.z);
+                if (in_tile) {
+                    LdsAcc<G, DIM> acc = lds_acc<G, DIM>(Jl, rx, ry, rz);
+                    esirkepov<DIM>(acc, SX, SY, SZ, S.q_dt * P.jscale, D.z);
+                } else {
+                    GlobalAcc acc = global_acc(P, cx, cy, DIM == 3 ? cz : 0);
+                    esirkepov<DIM>(acc, SX, SY, SZ, S.q_dt, D.z);
+                }
+            } else {
+                st_at(S.ws_cell, so, P.cc.encode(cx, cy, cz));
+                st_at(S.ws_off[0], so, ox);
+                st_at(S.ws_off[1], so, oy);
+                if (DIM == 3) st_at(S.ws_off[2], so, oz);
+                st_at(S.ws_disp[0], so, D.x);
+                st_at(S.ws_disp[1], so, D.y);
+                st_at(S.ws_disp[2], so, D.z);
+            }
         }
         if (FRAME == kLeaky || (FRAME != kPlain && P.escape)) {
 #pragma unroll
@@ -902,9 +948,9 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
 }
 
 // Register budgets: 3D for the 6 waves per SIMD of two 12-wave workgroups a CU; 2D tiles of 8x8 (7 KB of
-// LDS) fit eight waves per SIMD in 64 VGPRs, the larger 2D tiles are bound by their LDS first.
+// LDS) fit eight waves per SIMD in 64 VGPRs, tiles of 16x16 (23 KB) seven in 72.
 template <int DIM, int TX, int TY, int TZ, int FRAME, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIM == 3 ? 6 : 8)))
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIM == 3 ? 6 : (TX == 8 ? 8 : 7))))
 void gpd_kernel(StepDev P, int fuse)
 {
     gpd_body<DIM, TX, TY, TZ, FRAME, NT>(P, (int)blockIdx.x, (int)gridDim.x, fuse);
@@ -912,7 +958,7 @@ void gpd_kernel(StepDev P, int fuse)
 
 // Many boxes in one launch: the blocks of unit u (one box's tiles) take its descriptor.
 template <int DIM, int TX, int TY, int TZ, int FRAME, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIM == 3 ? 6 : 8)))
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIM == 3 ? 6 : (TX == 8 ? 8 : 7))))
 void gpd_batch(const StepDev* __restrict__ t, UnitMap m)
 {
     const int u = unit_of(m, (int)blockIdx.x);
