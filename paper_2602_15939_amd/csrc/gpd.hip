@@ -41,10 +41,13 @@ __device__ inline T ld_at(const T* __restrict__ base, uint32_t i)
     return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) +
                                        (size_t)(i * (uint32_t)sizeof(T)));
 }
+// Non-temporal: what a push writes is read by the next one at the earliest, and the caches are better kept for
+// the reads, whose lines neighbouring tiles share (256^3 shear 5.84 -> 5.70 ms, 2048^2 leaky 4.27 -> 4.12 ms,
+// 1024^2 leaky 0.675 -> 0.643 ms, a step of the 16 served boxes 704 -> 685 us; non-temporal loads made the push 20 % slower).
 template <class T>
 __device__ inline void st_at(T* __restrict__ base, uint32_t i, T v)
 {
-    *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + (size_t)(i * (uint32_t)sizeof(T))) = v;
+    __builtin_nontemporal_store(v, reinterpret_cast<T*>(reinterpret_cast<char*>(base) + (size_t)(i * (uint32_t)sizeof(T))));
 }
 
 // ------------------------------------------------------------------ interpolation
