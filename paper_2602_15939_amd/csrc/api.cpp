@@ -662,7 +662,7 @@ KsbFin ksb_fin(const pic_box* b, int K, int last)
     KsbFin F{};
     F.G = b->G;
     F.conv = b->conv;
-    F.sweeps = reinterpret_cast<int32_t*>(b->conv + 2 * kKsbMaxSweeps);
+    F.sweeps = reinterpret_cast<int32_t*>(b->conv + kConvSweep * kKsbMaxSweeps);
     F.err = b->err;
     F.tol = (float)b->d.maxwell_tol;
     F.K = K;
@@ -730,7 +730,7 @@ int32_t maxwell_box(pic_box* b)
             if (scale_fields(b->G, b->set[sn], f.fwd, st) != hipSuccess) return PIC_EDEVICE;
         }
         const bool staged = ksb_staged(b->G) && !comb;
-        if (tol && zero_floats(reinterpret_cast<float*>(b->conv), 2 * K, st) != hipSuccess)
+        if (tol && zero_floats(reinterpret_cast<float*>(b->conv), kConvSweep * K, st) != hipSuccess)
             return PIC_EDEVICE;
         int sk = sn, so = sb2;
         // fixed count on the staged 3D grids: two sweeps per pass over memory (the same
@@ -1203,8 +1203,8 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
                 pic_box* b = boxes[i];
                 if (!sheared(&b->d) || !(b->d.maxwell_tol > 0.0)) continue;
                 const int K = b->d.maxwell_iters > 0 ? b->d.maxwell_iters : 8;
-                cz.push_back(ZeroArgs{b->conv, (int64_t)2 * K});
-                czb.push_back(grid_blocks(2 * K));
+                cz.push_back(ZeroArgs{b->conv, (int64_t)kConvSweep * K});
+                czb.push_back(grid_blocks(kConvSweep * K));
             }
             plan.grid(kBatchZero, cz, czb, 1);
         }
@@ -2148,7 +2148,7 @@ int32_t pic_box_get(pic_box* b, pic_box_info* info)
     }
     P.ctr = b->ctr;
     P.err = b->err;
-    P.sweeps = b->last_sweeps < 0 ? reinterpret_cast<const int32_t*>(b->conv + 2 * kKsbMaxSweeps) : nullptr;
+    P.sweeps = b->last_sweeps < 0 ? reinterpret_cast<const int32_t*>(b->conv + kConvSweep * kKsbMaxSweeps) : nullptr;
     BoxRecord R{};
     if (box_record(b->G, field_ptrs(b), P, b->red_part, kRedBlocks, b->record, st) != hipSuccess ||
         hipMemcpyAsync(&R, b->record, sizeof(R), hipMemcpyDeviceToHost, st) != hipSuccess ||

@@ -383,10 +383,16 @@ __device__ inline bool ksb_met(const uint32_t* pair, float tol)
     const float d = __uint_as_float(pair[0]);
     return d <= tol * __uint_as_float(pair[1]) && d <= 3.4028235e38f;
 }
-// the sweep before this one met the tolerance: uniform over the grid, tested before any work
+// the sweep before this one met the tolerance: uniform over the grid, tested before any work, by each
+// wave for itself
 __device__ inline bool ksb_skip(const KsbDev& K)
 {
-    return K.conv && K.k > 0 && ksb_met(K.conv + 2 * (K.k - 1), K.tol);
+    if (!K.conv || K.k == 0) return false;
+    const uint32_t* p = K.conv + kConvSweep * (K.k - 1) + kConvStride * (threadIdx.x % kConvSlots);
+    uint32_t pair[2] = {p[0], p[1]};
+    for (int o = kConvSlots / 2; o > 0; o >>= 1)
+        for (int j = 0; j < 2; j++) pair[j] = max(pair[j], (uint32_t)__shfl_xor(pair[j], o, 64));
+    return ksb_met(pair, K.tol);
 }
 // running maxima of |F^{k+1} - F^k| (NaN -> +inf) and |F^{k+1}|
 __device__ inline void ksb_track(float fo, float fk, float& dm, float& fm)
@@ -397,7 +403,7 @@ __device__ inline void ksb_track(float fo, float fk, float& dm, float& fm)
 }
 // workgroup maxima (NT threads, whole waves), one atomic pair per workgroup
 template <int NT>
-__device__ inline void ksb_reduce(float dm, float fm, uint32_t* pair)
+__device__ inline void ksb_reduce(float dm, float fm, uint32_t* sweep)
 {
     __shared__ float red[2][NT / 64];
     for (int o = 32; o > 0; o >>= 1) {
@@ -415,8 +421,9 @@ __device__ inline void ksb_reduce(float dm, float fm, uint32_t* pair)
             dm = fmaxf(dm, red[0][j]);
             fm = fmaxf(fm, red[1][j]);
         }
-        atomicMax(pair, __float_as_uint(dm));
-        atomicMax(pair + 1, __float_as_uint(fm));
+        uint32_t* const p = sweep + kConvStride * (blockIdx.x % kConvSlots);
+        atomicMax(p, __float_as_uint(dm));
+        atomicMax(p + 1, __float_as_uint(fm));
     }
 }
 
@@ -557,7 +564,7 @@ __device__ __attribute__((always_inline)) inline void ksb_sweep_body(const KsbDe
         for (int c = 0; c < 6; c++) Fk[c] = V(c, 0, 0, 0);
         ksb_store<FIRST>(K, i, L, Fk, dm, fm);
     }
-    if (K.conv) ksb_reduce<kBlock>(dm, fm, K.conv + 2 * K.k);
+    if (K.conv) ksb_reduce<kBlock>(dm, fm, K.conv + kConvSweep * K.k);
 }
 __device__ __attribute__((always_inline)) inline void ksb_first_body(const KsbDev& K, int blk, int n, int y) { ksb_sweep_body<true>(K, blk, n, y); }
 __device__ __attribute__((always_inline)) inline void ksb_next_body(const KsbDev& K, int blk, int n, int y) { ksb_sweep_body<false>(K, blk, n, y); }
@@ -712,7 +719,7 @@ __global__ __launch_bounds__(KX * KY) void ksb_sweep3_kernel(KsbDev K)
         sc = sp;
         sp = t;
     }
-    if (K.conv) ksb_reduce<NT>(dm, fm, K.conv + 2 * K.k);
+    if (K.conv) ksb_reduce<NT>(dm, fm, K.conv + kConvSweep * K.k);
 }
 
 // ---- two sweeps per pass (3D, fixed sweep count)
@@ -1092,22 +1099,23 @@ void ksb_pass3_kernel(KsbDev K)
 __device__ __attribute__((always_inline)) inline void ksb_final_body(const KsbFin& F, int blk, int nblk, int)
 {
     __shared__ int kstar;
-    if (threadIdx.x == 0) {
-        int k = F.K - 1;
-        bool met = false;
-        for (int j = 0; j < F.K && !met; j++)
-            if (ksb_met(F.conv + 2 * j, F.tol)) {
-                k = j;
-                met = true;
-            }
-        kstar = k;
-        if (blk == 0) {
-            *F.sweeps = k + 1;
-            if (!met) atomicOr(F.err, kErrNoConverge);
-        }
+    if (threadIdx.x == 0) kstar = F.K;
+    __syncthreads();
+    for (int j = threadIdx.x; j < F.K; j += kBlock) {
+        uint32_t pair[2] = {0u, 0u};
+#pragma unroll
+        for (int k = 0; k < kConvSlots; k++)
+            for (int i = 0; i < 2; i++) pair[i] = max(pair[i], F.conv[kConvSweep * j + kConvStride * k + i]);
+        if (ksb_met(pair, F.tol)) atomicMin(&kstar, j);
     }
     __syncthreads();
-    if (((F.K - 1 - kstar) & 1) == 0) return;
+    const bool met = kstar < F.K;
+    const int last = met ? kstar : F.K - 1;  // the sweep whose iterate the step hands on
+    if (blk == 0 && threadIdx.x == 0) {
+        *F.sweeps = last + 1;
+        if (!met) atomicOr(F.err, kErrNoConverge);
+    }
+    if (((F.K - 1 - last) & 1) == 0) return;
     const GridDev& G = F.G;
     const int64_t n = (int64_t)G.n[0] * G.n[1] * G.n[2];
     for (int64_t t = (int64_t)blk * kBlock + threadIdx.x; t < n; t += (int64_t)nblk * kBlock) {
@@ -1398,7 +1406,13 @@ hipError_t yee_e(const MaxwellDev& M, hipStream_t st)
     yee_e_kernel<<<std::min(nblocks((int64_t)M.G.n[0] * M.G.n[1] * M.G.n[2]), kStrideBlocks), kBlock, 0, st>>>(M);
     return hipGetLastError();
 }
-bool ksb_staged(const GridDev& G) { return G.dim == 3 && G.n[0] % KX == 0; }
+// The staged single sweep marches over planes, each waiting for the one before: on grids that the caches
+// hold, one thread a cell is faster.  us a sweep, staged / one thread a cell: 128 x 64 x 64 14.7 / 11.0,
+// 128^3 39.5 / 35.1, 256 x 128 x 128 72 / 86, 256^3 261 / 323; the line lies between the middle two.
+bool ksb_staged(const GridDev& G)
+{
+    return G.dim == 3 && G.n[0] % KX == 0 && (int64_t)G.n[0] * G.n[1] * G.n[2] > 3ll << 20;
+}
 bool ksb_pass_fits(const GridDev& G)
 {
     return G.dim == 3 && G.n[0] % kPassX == 0 && 4 * (int64_t)G.sz * G.n[2] < (int64_t(1) << 32);
@@ -1407,7 +1421,7 @@ bool ksb_pass_fits(const GridDev& G)
 // Planes per workgroup of the staged kernels and the workgroups of a launch over `columns` column
 // tiles: `most` planes on grids that fill the chip with them (two workgroups a CU), fewer on smaller
 // ones, down to 4 (a chunk reads two planes, a pass four, beyond its own).  On
-// 128 x 64 x 64 cells chunks of 64 planes are 16 workgroups: 61 us a sweep, 13 us in chunks of 4.
+// 128 x 64 x 64 cells chunks of 64 planes are 16 workgroups: a staged sweep took 61 us, in chunks of 4 15 us.
 static unsigned z_chunks(int columns, int nz, int most, int& zc)
 {
     zc = most;

@@ -354,9 +354,9 @@ struct KsbDev {
     int ydys_int;
     float ydys_w;
     // tolerance mode (conv != nullptr): sweep k adds max|F^{k+1} - F^k| and max|F^{k+1}| (FP32
-    // bit patterns, non-negative, so unsigned order is float order; NaN counts as +inf) into
-    // conv[2k], conv[2k+1], which start at zero; it returns at once when the sweep before it
-    // met the tolerance, leaving its pair at zero, which reads as met for the next one
+    // bit patterns, non-negative, so unsigned order is float order; NaN counts as +inf) into the
+    // pairs at conv + kConvSweep k, which start at zero; it returns at once when the sweep before it
+    // met the tolerance, leaving its pairs at zero, which reads as met for the next one
     uint32_t* conv;
     float tol;
     int k;
@@ -373,9 +373,13 @@ struct KsbDev {
     float kz;
 };
 constexpr int kKsbMaxSweeps = 64;
-// words of a box's convergence record: kKsbMaxSweeps pairs, then the sweep count of the last
+// A sweep's pair of maxima is kept in kConvSlots places of a cache line each, workgroup b adding to
+// place b % kConvSlots: at one place the atomics of 2048 workgroups took 24 us of a sweep that
+// itself takes 11 (128 x 64 x 64 cells).
+constexpr int kConvSlots = 16, kConvStride = 32, kConvSweep = kConvSlots * kConvStride;
+// words of a box's convergence record: kKsbMaxSweeps sweeps, then the sweep count of the last
 // step
-constexpr int kKsbConvWords = 2 * kKsbMaxSweeps + 2;
+constexpr int kKsbConvWords = kConvSweep * kKsbMaxSweeps + 2;
 
 // End of a tolerance-mode step: k* = the first sweep that met the tolerance (the last sweep K-1
 // if none did, which latches kErrNoConverge).  The iterate of sweep k* sits in the field set

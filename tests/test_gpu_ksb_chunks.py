@@ -24,3 +24,20 @@ def test_pass_equals_single_sweeps_for_any_chunks(n):
     finally:
         for b in boxes:
             b.close()
+
+
+# beyond 3 x 2^20 cells single sweeps are staged too (below, one thread a cell): a last chunk of one
+# plane, ragged y tiles, one and two x tiles; odd counts end in a single sweep
+@pytest.mark.parametrize("n,K", [((128, 255, 97), 4), ((256, 126, 100), 5)])
+def test_pass_equals_staged_single_sweeps(n, K):
+    J = _current(n, 7)
+    boxes = [_box(n, 0.003, 13, J, maxwell_iters=K, maxwell_tol=t)[0] for t in (0.0, 1e-30)]
+    try:
+        for b in boxes:
+            b.maxwell()
+            assert b.info().errors & ~(L.DERR_ORDER | L.DERR_NOCONVERGE) == 0
+        for fa, fb in zip(boxes[0].get_fields(), boxes[1].get_fields()):
+            np.testing.assert_array_equal(fa.cpu().numpy(), fb.cpu().numpy())
+    finally:
+        for b in boxes:
+            b.close()
