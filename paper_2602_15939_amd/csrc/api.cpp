@@ -358,7 +358,8 @@ StepDev make_step(pic_box* b)
     set_migration_shift(b, P.dys_int);
     P.count_mig = b->mig_ok ? 1 : 0;
     P.mig_latch = 0;
-    P.lsplit = tile_split(b->dim, b->tile, b->tl.n_tiles, slots_per_tile(b));
+    P.nsp = b->nsp;
+    split_tiles(P, b->tile, b->tl.n_tiles, slots_per_tile(b));
     P.mg = b->mg;
     for (int s = 0; s < b->nsp; s++) {
         P.mcnt[s] = b->sp[s].sb.mcnt;
@@ -400,7 +401,6 @@ StepDev make_step(pic_box* b)
     }
     P.err = b->err;
     P.ctr = b->ctr;
-    P.nsp = b->nsp;
     P.track_ids = b->track_ids ? 1 : 0;
     P.count_sl = (b->d.flags & PIC_BOX_COUNT_SUPERLUMINAL) ? 1 : 0;
     for (int s = 0; s < b->nsp; s++) {
@@ -1060,7 +1060,7 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             auto& gr = groups[group_of(b)];
             StepDev P = make_step(b);
             P.mig_latch = 1;  // no radix fallback behind a batched sort
-            P.lsplit = tile_split(b->dim, b->tile, group_tiles[group_of(b)], slots_per_tile(b));
+            split_tiles(P, b->tile, group_tiles[group_of(b)], slots_per_tile(b));
             gr.first.push_back(P);
             gr.second.push_back((uint32_t)b->tl.n_tiles << P.lsplit);
             for (int s = 0; s < b->nsp; s++) {

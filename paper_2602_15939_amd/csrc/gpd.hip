@@ -631,6 +631,19 @@ __device__ inline void flush_current(const unsigned long long* __restrict__ Jl, 
     }
 }
 
+// what a workgroup takes of a launch: its tile, of the species s0 .. s1 - 1 the rounds part, part + 2^lparts, ...
+struct Share {
+    int tile, part, lparts, s0, s1;
+    __device__ inline Share(const StepDev& P, int unit)
+    {
+        tile = unit >> P.lsplit;
+        part = (unit & ((1 << P.lsplit) - 1)) >> P.by_species;
+        lparts = P.lsplit - P.by_species;
+        s0 = P.by_species ? unit & 1 : 0;
+        s1 = P.by_species ? s0 + 1 : P.nsp;
+    }
+};
+
 // a particle as it is read through the sort permutation; in the leaky box with what its escape needs
 template <int DIM, int FRAME>
 struct Particle {
@@ -668,7 +681,8 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
     unsigned long long* const Jl = reinterpret_cast<unsigned long long*>(lds + G::FBYTES);  // J
 
     const int unit = xcd_contiguous(blk, nblk);
-    const int tile = unit >> P.lsplit, part = unit & ((1 << P.lsplit) - 1);
+    const Share share(P, unit);
+    const int tile = share.tile;
     int t0[3], ext[3];
     tile_origin<DIM>(P, tile, t0, ext);
     const int tid = threadIdx.x;
@@ -686,7 +700,7 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
     __syncthreads();
 
     const int nx = P.n[0], ny = P.n[1], nz = P.n[2];
-    for (int s = 0; s < P.nsp; s++) {
+    for (int s = share.s0; s < share.s1; s++) {
         const SpeciesDev& S = P.sp[s];
         bool far = false;   // a particle beyond the neighbouring tiles
         uint32_t nesc = 0;  // probabilistic escapes (one counter add per wave, at the end)
@@ -704,8 +718,8 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
             const uint32_t r = min(v, count - 1) + head;
             return beg + (r < count ? r : r - count);
         };
-        const uint32_t stride = (uint32_t)NT << P.lsplit;
-        uint32_t v = part * NT + tid, src = 0, src_next = 0;
+        const uint32_t stride = (uint32_t)NT << share.lparts;
+        uint32_t v = share.part * NT + tid, src = 0, src_next = 0;
         Particle<DIM, FRAME> p;
         if (v < count) {
             src = (uint32_t)ld_at(S.perm, slot_of(v));
@@ -977,16 +991,17 @@ __global__ __launch_bounds__(NT) void deposit_kernel(StepDev P)
     using G = Geo<DIM, TX, TY, TZ>;
     __shared__ unsigned long long Jl[G::JTOT];
     const int unit = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int tile = unit >> P.lsplit, part = unit & ((1 << P.lsplit) - 1);
+    const Share share(P, unit);
+    const int tile = share.tile;
     int t0[3], ext[3];
     tile_origin<DIM>(P, tile, t0, ext);
     const int tid = threadIdx.x;
     for (int e = tid; e < G::JTOT; e += NT) Jl[e] = 0ull;
     __syncthreads();
-    for (int s = 0; s < P.nsp; s++) {
+    for (int s = share.s0; s < share.s1; s++) {
         const SpeciesDev& S = P.sp[s];
         const uint32_t beg = (uint32_t)S.toff[tile], end = (uint32_t)S.toff[tile + 1];
-        for (uint32_t slot = beg + part * NT + tid; slot < end; slot += (uint32_t)NT << P.lsplit) {
+        for (uint32_t slot = beg + share.part * NT + tid; slot < end; slot += (uint32_t)NT << share.lparts) {
             int cx, cy, cz;
             P.cc.decode(ld_at(S.ws_cell, slot), cx, cy, cz);
             const float ox = ld_at(S.ws_off[0], slot), oy = ld_at(S.ws_off[1], slot);
@@ -1026,12 +1041,15 @@ constexpr int threads_for(int dim, int cells)
 // whole round of a species: more parts only add their staging and flush (four parts a tile instead of
 // two made the 384^2 box's push slower, 75 -> 84 us).  The 64^2 box of the parity tests (16 tiles of 4096
 // slots a species): 84 us whole, 19 us in 256 workgroups; 20 x 12 x 16 cells: 32 -> 28 us.
-int tile_split(int dim, const int t[3], int64_t n_tiles, int64_t slots_per_tile)
+// Where the parts still leave the chip idle, one of two species each halves the chain again: 20 x 12 x 16
+// cells 21.2 -> 15.8 us, the 64^2 box 15.6 -> 12.4 us.
+void split_tiles(StepDev& P, const int t[3], int64_t n_tiles, int64_t slots_per_tile)
 {
-    const int64_t want = dim == 3 ? 512 : 1024, nt = threads_for(dim, t[0] * t[1] * t[2]);
-    int l = 0;
-    while (l < 6 && (n_tiles << l) < want && (slots_per_tile >> l) > nt) l++;
-    return l;
+    const int64_t want = P.dim == 3 ? 512 : 1024, nt = threads_for(P.dim, t[0] * t[1] * t[2]);
+    P.lsplit = 0;
+    while (P.lsplit < 6 && (n_tiles << P.lsplit) < want && (slots_per_tile >> P.lsplit) > nt) P.lsplit++;
+    P.by_species = P.nsp == 2 && (n_tiles << P.lsplit) < want ? 1 : 0;
+    P.lsplit += P.by_species;
 }
 
 template <int DIM, int TX, int TY, int TZ>

@@ -172,9 +172,9 @@ struct StepDev {
     const float* mj;      // kMjBins + kMjTail values
     // fixed-point tile current: contribution * jscale -> integer units, units * junit -> J
     float jscale, junit;
-    // a tile's slots are shared out to 2^lsplit workgroups (part p takes every 2^lsplit-th round of
-    // them), where the tiles alone would leave the chip idle
-    int lsplit;
+    // a tile is shared out to 2^lsplit workgroups: by_species, the lowest bit names one of two species,
+    // and part p of the others takes every 2^(lsplit - by_species)-th round of a species' slots
+    int lsplit, by_species;
     // migration counts of the next sort, taken by the push: per species and source tile
     // (= this launch's tile), the particles per direction (mcnt[tile * kMigDirs + d], added to the
     // cleared counts by the parts of a split tile); a
@@ -434,9 +434,9 @@ struct MigPair {
 
 // ---- launchers (gpd.hip, sort.hip, grid.hip, xfer.hip)
 bool tile_shape_supported(int dim, const int t[3]);
-// log2 of the workgroups per tile of a push or deposit launch over n_tiles tiles (of all its boxes),
-// for a box with slots_per_tile slots of the fuller species a tile on average
-int tile_split(int dim, const int t[3], int64_t n_tiles, int64_t slots_per_tile);
+// share the tiles of a push or deposit out to workgroups (lsplit, by_species): n_tiles tiles in the launch
+// (of all its boxes), slots_per_tile slots of the fuller species a tile on average in this one
+void split_tiles(StepDev& P, const int t[3], int64_t n_tiles, int64_t slots_per_tile);
 // supported tile shapes (batched: those of the batched launch); the default shape comes first
 int tile_candidates(int dim, bool batched, int (*out)[3], int max);
 hipError_t launch_gather_push(const StepDev& P, const int t[3], int fuse, hipStream_t st);
