@@ -735,7 +735,9 @@ int32_t maxwell_box(pic_box* b)
         int sk = sn, so = sb2;
         // fixed count on the staged 3D grids: two sweeps per pass over memory (the same
         // iterates bit for bit), a last single sweep when the count is odd
-        const bool paired = !tol && !comb && ksb_pass_fits(b->G) && K >= 2;
+        // (small grids of any shape: two per launch)
+        const bool pairs = !tol && ksb_pairs(b->G);
+        const bool paired = !tol && (pairs || (!comb && ksb_pass_fits(b->G))) && K >= 2;
         for (int k = 0; k < K; k++) {
             const bool pass = paired && k + 1 < K;
             KsbDev Kd{};
@@ -766,7 +768,7 @@ int32_t maxwell_box(pic_box* b)
                 const double fl = std::floor(dys1);
                 Kd.y1_int = (int)fl;
                 Kd.y1_w = (float)(dys1 - fl);
-                if (ksb_pass(Kd, k == 0, st) != hipSuccess) return PIC_EDEVICE;
+                if ((pairs ? ksb_pair(Kd, k == 0, st) : ksb_pass(Kd, k == 0, st)) != hipSuccess) return PIC_EDEVICE;
                 k++;
             } else if ((staged ? ksb_sweep(Kd, k == 0, st) : ksb_sweep_unstaged(Kd, k == 0, st)) != hipSuccess) {
                 return PIC_EDEVICE;
@@ -1209,8 +1211,8 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             plan.grid(kBatchZero, cz, czb, 1);
         }
         for (int k = 0; k < kmax; k++) {
-            std::vector<KsbDev> ks;
-            std::vector<uint32_t> ksb;
+            std::vector<KsbDev> ks, kp;  // one sweep; two
+            std::vector<uint32_t> ksb, kpb;
             std::vector<KsbFin> kz;
             std::vector<uint32_t> kzb;
             for (int i = 0; i < nb; i++) {
@@ -1219,6 +1221,8 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
                 const int K = b->d.maxwell_iters > 0 ? b->d.maxwell_iters : 8;
                 if (k >= K) continue;
                 const bool tol = b->d.maxwell_tol > 0.0;
+                const bool pairs = !tol && ksb_pairs(b->G), two = pairs && k + 1 < K;
+                if (pairs && (k & 1)) continue;  // taken with the sweep before it
                 Rot& r = rot[i];
                 KsbDev Kd{};
                 Kd.G = b->G;
@@ -1236,6 +1240,9 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
                     const double dys = shear_offset(b, k == 0 ? tn : tn + b->d.dt), fl = std::floor(dys);
                     Kd.ydys_int = (int)fl;
                     Kd.ydys_w = (float)(dys - fl);
+                    const double dys1 = shear_offset(b, tn + b->d.dt), fl1 = std::floor(dys1);
+                    Kd.y1_int = (int)fl1;
+                    Kd.y1_w = (float)(dys1 - fl1);
                 }
                 if (tol) {
                     Kd.conv = b->conv;
@@ -1250,20 +1257,21 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
                     for (int c = 0; c < 3; c++) Kd.dfac[c] = 1.f;
                     Kd.kz = 1.f;
                 }
-                ks.push_back(Kd);
-                ksb.push_back(grid_blocks((int64_t)b->n[0] * b->n[1] * b->n[2]));
+                (two ? kp : ks).push_back(Kd);
+                (two ? kpb : ksb).push_back(two ? ksb_pair_blocks(b->G) : grid_blocks((int64_t)b->n[0] * b->n[1] * b->n[2]));
                 if (tol && k == K - 1) {
                     kz.push_back(ksb_fin(b, K, r.so));
                     kzb.push_back(kKsbFinBlocks);
                 }
                 r.sk = r.so;
                 r.so = r.so == r.sb2 ? r.sn : r.sb2;
-                if (k == K - 1) {
+                if (k == K - 1 || (two && k == K - 2)) {
                     b->cur_set = r.sk;
                     b->last_sweeps = tol ? -1 : K;
                 }
             }
             plan.grid(k == 0 ? kBatchKsbFirst : kBatchKsbNext, ks, ksb, 1);
+            plan.grid(k == 0 ? kBatchKsbPairFirst : kBatchKsbPairNext, kp, kpb, 1);
             plan.grid(kBatchKsbFinal, kz, kzb, 1);
         }
         // combined-frame boxes: the last iterate back to the frame's fields at t^{n+1}

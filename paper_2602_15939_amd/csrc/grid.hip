@@ -571,6 +571,149 @@ __device__ __attribute__((always_inline)) inline void ksb_next_body(const KsbDev
 PIC_BATCHED_KERNEL(ksb_first, KsbDev, kBlock)
 PIC_BATCHED_KERNEL(ksb_next, KsbDev, kBlock)
 
+// Two sweeps in one launch on small grids, where a sweep's launch and its one chain of loads (4.5 us) cost
+// more than its work: a thread per position of a tile and the cells around it computes F^{k+1} straight
+// from memory into LDS (FIRST also C), a thread per cell of the tile F^{k+2} from there.  Beyond an x face
+// F^{k+1} is interpolated between two rows of the other face, computed for the tile's rows and one more;
+// so no position needs another workgroup's result, and every value is the single sweeps' bit for bit.
+// A step of 8 sweeps: 64^2 38 -> 24 us, 512^2 71 -> 43 us, 20 x 12 x 16 42 -> 34 us.
+template <bool D3>
+struct PairTile {
+    static constexpr int TX = D3 ? 8 : 32, TY = D3 ? 8 : 16, TZ = D3 ? 4 : 1;
+    static constexpr int WX = TX + 2, WY = TY + 2, WZ = D3 ? TZ + 2 : 1;
+    static constexpr int N = TX * TY * TZ, W = WX * WY * WZ, RING = 2 * WX + 2 * TY;
+    static constexpr int XROWS = WY + 1, X = WZ * XROWS;  // rows of the other face, per component and side
+    static constexpr int LDS = 6 * (W + 2 * X);
+};
+constexpr int kPairBlock = 640;
+constexpr int kPairLds = PairTile<true>::LDS > PairTile<false>::LDS ? PairTile<true>::LDS : PairTile<false>::LDS;
+
+template <bool D3, bool FIRST>
+__device__ __attribute__((always_inline)) inline void ksb_pair_tile(const KsbDev& K, int blk, float* lds)
+{
+    using T = PairTile<D3>;
+    static_assert(T::W + 2 * T::WZ <= kPairBlock, "a thread per position and per additional row");
+    const GridDev& G = K.G;
+    const int nx = G.n[0], ny = G.n[1], nz = G.n[2];
+    const int ntx = (nx + T::TX - 1) / T::TX, nty = (ny + T::TY - 1) / T::TY;
+    const int x0 = blk % ntx * T::TX, y0 = blk / ntx % nty * T::TY, z0 = blk / (ntx * nty) * T::TZ;
+    const int ex = min(T::TX, nx - x0), ey = min(T::TY, ny - y0), ez = min(T::TZ, nz - z0);
+    const int tid = threadIdx.x;
+    float* const Bs = lds;                // F^{k+1}: [c][lz][ly][lx], position 1 the tile's first cell
+    float* const XB = lds + 6 * T::W;     // F^{k+1} of the other face: [side][c][lz][row]
+    int js[2];
+    float w1[2];
+    shear_image(false, K.y1_int, K.y1_w, js[0], w1[0]);
+    shear_image(true, K.y1_int, K.y1_w, js[1], w1[1]);
+
+    // the thread's position: the tile's cells, then those around it, then the additional rows
+    int lx = 0, ly = 0, lz = 0, side = -1;
+    bool need;
+    if (tid < T::N) {
+        lx = 1 + tid % T::TX;
+        ly = 1 + tid / T::TX % T::TY;
+        lz = D3 ? 1 + tid / (T::TX * T::TY) : 0;
+    } else if (tid < T::W) {
+        int h = tid - T::N;
+        if (D3 && h < 2 * T::WX * T::WY) {
+            lz = h < T::WX * T::WY ? 0 : T::WZ - 1;
+            lx = h % T::WX;
+            ly = h / T::WX % T::WY;
+        } else {
+            if (D3) h -= 2 * T::WX * T::WY;
+            lz = D3 ? 1 + h / T::RING : 0;
+            h %= T::RING;
+            if (h < 2 * T::WX) {
+                lx = h % T::WX;
+                ly = h < T::WX ? 0 : T::WY - 1;
+            } else {
+                lx = (h & 1) ? T::WX - 1 : 0;
+                ly = 1 + (h - 2 * T::WX) / 2;
+            }
+        }
+    }
+    const int gx = x0 - 1 + lx;
+    if (tid < T::W) {
+        need = lx <= ex + 1 && ly <= ey + 1 && (!D3 || lz <= ez + 1);
+        if (gx < 0) side = 0;
+        if (gx >= nx) side = 1;
+    } else {
+        const int e = tid - T::W;
+        side = e / T::WZ;
+        lz = e % T::WZ;
+        ly = ey + 2;
+        need = e < 2 * T::WZ && (side == 0 ? x0 == 0 : x0 + ex == nx) && (!D3 || lz <= ez + 1);
+    }
+    const int cx = side < 0 ? gx : (side == 0 ? nx - 1 : 0);
+    float C[6] = {};
+    const float h = 0.5f * K.dt;
+    if (need) {
+        const int cy = wrapn(y0 - 1 + ly + (side < 0 ? 0 : js[side]), ny), cz = D3 ? wrapn(z0 - 1 + lz, nz) : 0;
+        const int64_t i = gidx(G, cx, cy, cz);
+        const float fpdt = 4.f * 3.14159265358979f * K.dt;
+        const float v0 = -K.sO * ((float)cx - K.half_nx);
+        const float vh = -K.sO * ((float)cx + 0.5f - K.half_nx);
+#pragma unroll
+        for (int c = 0; c < 6; c++)
+            if (!FIRST || c >= EX) C[c] = FIRST ? K.J[c - EX][i] : K.C[c][i];
+        float L[6];
+        KsbCell V;
+        ksb_load<D3>(K, cx, cy, cz, i, V);
+        if (K.expand)
+            ksb_operator_f<D3>(V, v0, vh, K.sO, K.dfac, K.kz, L);
+        else
+            ksb_operator<D3>(V, v0, vh, K.sO, L);
+        const bool cell = tid < T::N && lx <= ex && ly <= ey && lz <= ez;
+        float* const to = side < 0 ? Bs + lx + T::WX * (ly + T::WY * lz) : XB + 6 * T::X * side + ly + T::XROWS * lz;
+        const int step = side < 0 ? T::W : T::X;
+#pragma unroll
+        for (int c = 0; c < 6; c++) {
+            if (FIRST) {
+                float cv = V(c, 0, 0, 0) + h * L[c];
+                if (c >= EX) cv -= fpdt * C[c];
+                C[c] = cv;
+                if (cell) K.C[c][i] = cv;
+            }
+            to[c * step] = C[c] + h * L[c];
+        }
+    }
+    __syncthreads();
+    if (need && side >= 0 && tid < T::W)
+#pragma unroll
+        for (int c = 0; c < 6; c++) {
+            const float* const r = XB + 6 * T::X * side + T::X * c + ly + T::XROWS * lz;
+            Bs[lx + T::WX * (ly + T::WY * lz) + T::W * c] = shear_lerp(r[0], r[1], w1[side]);
+        }
+    __syncthreads();
+    if (tid < T::N && lx <= ex && ly <= ey && lz <= ez) {
+        const float* const B = Bs + lx + T::WX * (ly + T::WY * lz);
+        auto V = [&](int c, int dx, int dy, int dz) { return B[T::W * c + dx + T::WX * (dy + T::WY * dz)]; };
+        const float v0 = -K.sO * ((float)gx - K.half_nx);
+        const float vh = -K.sO * ((float)gx + 0.5f - K.half_nx);
+        float L[6];
+        if (K.expand)
+            ksb_operator_f<D3>(V, v0, vh, K.sO, K.dfac, K.kz, L);
+        else
+            ksb_operator<D3>(V, v0, vh, K.sO, L);
+        const int64_t i = gidx(G, gx, y0 - 1 + ly, D3 ? z0 - 1 + lz : 0);
+#pragma unroll
+        for (int c = 0; c < 6; c++) K.Fo[c][i] = C[c] + h * L[c];
+    }
+}
+template <bool FIRST>
+__device__ __attribute__((always_inline)) inline void ksb_pair_body(const KsbDev& K, int blk)
+{
+    __shared__ float lds[kPairLds];
+    if (K.G.dim == 3)
+        ksb_pair_tile<true, FIRST>(K, blk, lds);
+    else
+        ksb_pair_tile<false, FIRST>(K, blk, lds);
+}
+__device__ __attribute__((always_inline)) inline void ksb_pair_first_body(const KsbDev& K, int blk, int, int) { ksb_pair_body<true>(K, blk); }
+__device__ __attribute__((always_inline)) inline void ksb_pair_next_body(const KsbDev& K, int blk, int, int) { ksb_pair_body<false>(K, blk); }
+PIC_BATCHED_KERNEL(ksb_pair_first, KsbDev, kPairBlock)
+PIC_BATCHED_KERNEL(ksb_pair_next, KsbDev, kPairBlock)
+
 // 3D: a workgroup owns a KX x KY column tile and marches over a chunk of KZ planes; three
 // consecutive planes of the iterate (tile plus a one-cell halo) sit in LDS.  Halo positions
 // outside the interior are read through the boundary maps of the guard fill (y, z periodic;
@@ -1413,9 +1556,11 @@ bool ksb_staged(const GridDev& G)
 {
     return G.dim == 3 && G.n[0] % KX == 0 && (int64_t)G.n[0] * G.n[1] * G.n[2] > 3ll << 20;
 }
+// The two-sweep pass on grids of a staged shape: us a step of 8 sweeps, passes / one thread a cell: 64^3
+// 74 / 62, 128 x 128 x 64 156 / 147, 128^3 265 / 272; the line lies between the last two.
 bool ksb_pass_fits(const GridDev& G)
 {
-    return G.dim == 3 && G.n[0] % kPassX == 0 && 4 * (int64_t)G.sz * G.n[2] < (int64_t(1) << 32);
+    return G.dim == 3 && G.n[0] % kPassX == 0 && (int64_t)G.n[0] * G.n[1] * G.n[2] > 3ll << 19 && 4 * (int64_t)G.sz * G.n[2] < (int64_t(1) << 32);
 }
 
 // Planes per workgroup of the staged kernels and the workgroups of a launch over `columns` column
@@ -1454,6 +1599,30 @@ hipError_t ksb_sweep_unstaged(const KsbDev& K, bool first, hipStream_t st)
         ksb_first_kernel<<<nb, kBlock, 0, st>>>(K);
     else
         ksb_next_kernel<<<nb, kBlock, 0, st>>>(K);
+    return hipGetLastError();
+}
+// Where two sweeps per launch win.  us a step of 8 sweeps, pairs / singles: 64^2 24 / 37, 512^2 43 / 71,
+// 1024^2 130 / 142 (there its memory bounds it); 20 x 12 x 16 34 / 42, 32^3 39 / 41, 48^3 70 / 50 (a 3D
+// tile computes 2.3 positions a cell, and many tiles share a CU).
+bool ksb_pairs(const GridDev& G)
+{
+    return G.n[0] >= 2 && (int64_t)G.n[0] * G.n[1] * G.n[2] <= (G.dim == 2 ? 1ll << 20 : 1ll << 15);
+}
+unsigned ksb_pair_blocks(const GridDev& G)
+{
+    using T3 = PairTile<true>;
+    using T2 = PairTile<false>;
+    auto tiles = [](int n, int t) { return (unsigned)((n + t - 1) / t); };
+    return G.dim == 3 ? tiles(G.n[0], T3::TX) * tiles(G.n[1], T3::TY) * tiles(G.n[2], T3::TZ)
+                      : tiles(G.n[0], T2::TX) * tiles(G.n[1], T2::TY);
+}
+hipError_t ksb_pair(const KsbDev& K, bool first, hipStream_t st)
+{
+    if (!ksb_pairs(K.G) || K.conv) return hipErrorInvalidValue;
+    if (first)
+        ksb_pair_first_kernel<<<ksb_pair_blocks(K.G), kPairBlock, 0, st>>>(K);
+    else
+        ksb_pair_next_kernel<<<ksb_pair_blocks(K.G), kPairBlock, 0, st>>>(K);
     return hipGetLastError();
 }
 hipError_t ksb_pass(const KsbDev& K, bool first, hipStream_t st)
@@ -1504,6 +1673,12 @@ hipError_t grid_batch(GridBatchKind k, const void* table, UnitMap m, int blocks,
         ksb_first_batch<<<grid, kBlock, 0, st>>>(static_cast<const KsbDev*>(table), m);
         break;
     case kBatchKsbNext: ksb_next_batch<<<grid, kBlock, 0, st>>>(static_cast<const KsbDev*>(table), m); break;
+    case kBatchKsbPairFirst:
+        ksb_pair_first_batch<<<grid, kPairBlock, 0, st>>>(static_cast<const KsbDev*>(table), m);
+        break;
+    case kBatchKsbPairNext:
+        ksb_pair_next_batch<<<grid, kPairBlock, 0, st>>>(static_cast<const KsbDev*>(table), m);
+        break;
     case kBatchKsbFinal: ksb_final_batch<<<grid, kBlock, 0, st>>>(static_cast<const KsbFin*>(table), m); break;
     case kBatchScale: scale_fields_batch<<<grid, kBlock, 0, st>>>(static_cast<const ScaleArgs*>(table), m); break;
     }

@@ -471,7 +471,7 @@ struct ScaleArgs {
 };
 enum GridBatchKind {
     kBatchZero, kBatchFill, kBatchFoldP, kBatchShearFold, kBatchYeeB, kBatchYeeE,
-    kBatchKsbFirst, kBatchKsbNext, kBatchKsbFinal, kBatchScale
+    kBatchKsbFirst, kBatchKsbNext, kBatchKsbPairFirst, kBatchKsbPairNext, kBatchKsbFinal, kBatchScale
 };
 hipError_t grid_batch(GridBatchKind k, const void* table, UnitMap m, int blocks, int ydim,
                       hipStream_t st);
@@ -493,10 +493,14 @@ hipError_t fold_current(const GridDev& G, float* const* J, float* const* out, in
                         double sO, double dt, double dys_half, hipStream_t st);
 hipError_t yee_b(const MaxwellDev& M, hipStream_t st);
 hipError_t yee_e(const MaxwellDev& M, hipStream_t st);
-// one sweep; 3D grids whose x size is a multiple of the staged kernel's column tile (128) take
+// one sweep; large 3D grids whose x size is a multiple of the staged kernel's column tile (128) take
 // the staged kernel, others one thread per cell; both read cells beyond the faces at their images
 bool ksb_staged(const GridDev& G);
-// the two-sweep pass applies: a staged grid whose arrays span less than 4 GiB (32-bit offsets)
+// two sweeps per launch (fixed sweep count, K.y1_*): small grids of any shape
+bool ksb_pairs(const GridDev& G);
+unsigned ksb_pair_blocks(const GridDev& G);
+hipError_t ksb_pair(const KsbDev& K, bool first, hipStream_t st);
+// the two-sweep pass applies: a large grid whose arrays span less than 4 GiB (32-bit offsets)
 bool ksb_pass_fits(const GridDev& G);
 hipError_t ksb_sweep(const KsbDev& K, bool first, hipStream_t st);
 // the one-thread-per-cell sweep on any grid
