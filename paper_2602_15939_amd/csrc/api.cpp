@@ -733,7 +733,7 @@ int32_t maxwell_box(pic_box* b)
         if (tol && zero_floats(reinterpret_cast<float*>(b->conv), kConvSweep * K, st) != hipSuccess)
             return PIC_EDEVICE;
         int sk = sn, so = sb2;
-        // fixed count on the staged 3D grids: two sweeps per pass over memory (the same
+        // fixed count on large 3D grids: two sweeps per pass over memory (the same
         // iterates bit for bit), a last single sweep when the count is odd
         // (small grids of any shape: two per launch)
         const bool pairs = !tol && ksb_pairs(b->G);

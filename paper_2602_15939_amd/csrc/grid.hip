@@ -576,10 +576,11 @@ PIC_BATCHED_KERNEL(ksb_next, KsbDev, kBlock)
 // from memory into LDS (FIRST also C), a thread per cell of the tile F^{k+2} from there.  Beyond an x face
 // F^{k+1} is interpolated between two rows of the other face, computed for the tile's rows and one more;
 // so no position needs another workgroup's result, and every value is the single sweeps' bit for bit.
-// A step of 8 sweeps: 64^2 38 -> 24 us, 512^2 71 -> 43 us, 20 x 12 x 16 42 -> 34 us.
+// A step of 8 sweeps: 64^2 38 -> 24 us, 512^2 71 -> 43 us, 20 x 12 x 16 42 -> 28 us.  2D tiles of 16 x 16 took
+// 22 and 52 us on these grids, 3D tiles of 8 x 8 x 4 35 us, of 4^3 27 us but 39 us on 32^3 (8 x 4 x 4: 32).
 template <bool D3>
 struct PairTile {
-    static constexpr int TX = D3 ? 8 : 32, TY = D3 ? 8 : 16, TZ = D3 ? 4 : 1;
+    static constexpr int TX = D3 ? 8 : 32, TY = D3 ? 4 : 16, TZ = D3 ? 4 : 1;
     static constexpr int WX = TX + 2, WY = TY + 2, WZ = D3 ? TZ + 2 : 1;
     static constexpr int N = TX * TY * TZ, W = WX * WY * WZ, RING = 2 * WX + 2 * TY;
     static constexpr int XROWS = WY + 1, X = WZ * XROWS;  // rows of the other face, per component and side
@@ -1602,8 +1603,8 @@ hipError_t ksb_sweep_unstaged(const KsbDev& K, bool first, hipStream_t st)
     return hipGetLastError();
 }
 // Where two sweeps per launch win.  us a step of 8 sweeps, pairs / singles: 64^2 24 / 37, 512^2 43 / 71,
-// 1024^2 130 / 142 (there its memory bounds it); 20 x 12 x 16 34 / 42, 32^3 39 / 41, 48^3 70 / 50 (a 3D
-// tile computes 2.3 positions a cell, and many tiles share a CU).
+// 1024^2 130 / 142 (there its memory bounds it); 20 x 12 x 16 28 / 42, 32^3 32 / 41, 48^3 80 / 50 (a 3D
+// tile computes 2.8 positions a cell, and many tiles share a CU).
 bool ksb_pairs(const GridDev& G)
 {
     return G.n[0] >= 2 && (int64_t)G.n[0] * G.n[1] * G.n[2] <= (G.dim == 2 ? 1ll << 20 : 1ll << 15);

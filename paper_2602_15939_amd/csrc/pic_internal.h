@@ -360,7 +360,7 @@ struct KsbDev {
     uint32_t* conv;
     float tol;
     int k;
-    // two sweeps per pass (3D grids of the staged sweep, fixed sweep count): the shift of the
+    // two sweeps per pass or launch (fixed sweep count): the shift of the
     // intermediate iterate's x images, Delta y_s at t^{n+1} = y1_int + y1_w
     int y1_int;
     float y1_w;
@@ -505,7 +505,7 @@ bool ksb_pass_fits(const GridDev& G);
 hipError_t ksb_sweep(const KsbDev& K, bool first, hipStream_t st);
 // the one-thread-per-cell sweep on any grid
 hipError_t ksb_sweep_unstaged(const KsbDev& K, bool first, hipStream_t st);
-// two sweeps F^k -> F^{k+2} in one pass over memory (staged 3D grids only); first: F^k = F^n,
+// two sweeps F^k -> F^{k+2} in one pass over memory (large 3D grids); first: F^k = F^n,
 // the pass also writes C
 hipError_t ksb_pass(const KsbDev& K, bool first, hipStream_t st);
 
