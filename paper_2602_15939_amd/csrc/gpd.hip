@@ -228,24 +228,30 @@ __device__ inline float renorm(float s, int& dc)
 
 // ------------------------------------------------------------------ Esirkepov deposit
 // CIC shape along one axis: L and U are the nodes around the old position (offset o from L, then o + D); a
-// particle that leaves [0, 1] also reaches the node beyond, X (below L or above U).
+// particle that leaves [0, 1] also reaches the node beyond, X (below L or above U).  Positions are taken
+// from the nearer node, where they round least; c is that node, s the other.
 struct Shape {
     float l, u;        // weights on L and U before the move
     float dl, du, dx;  // their changes and X's
     float e, x;        // what flows through the edge L-U, and through the one to X (towards +)
 };
+__device__ inline float flip(float v, uint32_t sign) { return __uint_as_float(__float_as_uint(v) ^ sign); }
 __device__ inline Shape shape(float o, float D)
 {
     Shape A;
     A.l = 1.f - o;
     A.u = o;
-    // each way's excess from the node that it crosses: no rounding at the size of o + D
-    const float below = fminf(D + A.u, 0.f), above = fmaxf(D - A.l, 0.f);
-    A.x = below + above;
-    A.e = D - A.x;
-    A.dl = below - A.e;
-    A.du = A.e - above;
-    A.dx = fabsf(A.x);
+    const bool up = o >= 0.5f;  // s lies below c; 1 - o is exact then
+    const float x0 = up ? -A.l : o, x1 = x0 + D;
+    const uint32_t sign = __float_as_uint(x0) & 0x80000000u;
+    const float t = flip(x1, sign);  // the new position counted towards s
+    const float s0 = fabsf(x0), c0 = 1.f - s0;
+    const float dc = (1.f - fabsf(x1)) - c0, ds = fmaxf(0.f, t) - s0;
+    A.dx = fmaxf(0.f, -t);
+    A.dl = up ? ds : dc;
+    A.du = up ? dc : ds;
+    A.e = flip(ds, sign);
+    A.x = flip(A.dx, sign ^ 0x80000000u);
     return A;
 }
 // transverse factors of an axis with the charge factor q/dt folded in: node weight w gives
@@ -304,11 +310,10 @@ __device__ inline void esirkepov(Acc& acc, const Shape& X, const Shape& Y, const
             acc.template add<0, 0, 0, 1>(d, X.x * yz01);
             acc.template add<0, 0, 1, 0>(d, X.x * yz10);
             acc.template add<0, 0, 1, 1>(d, X.x * yz11);
-            const float ey = Y.e * X.dx, ez = Z.e * X.dx;
-            acc.template add<1, 0, 0, 0>(k, ey * FZ.l2);
-            acc.template add<1, 0, 0, 1>(k, ey * FZ.u2);
-            acc.template add<2, 0, 0, 0>(k, ez * FY.l2);
-            acc.template add<2, 0, 1, 0>(k, ez * FY.u2);
+            acc.template add<1, 0, 0, 0>(k, Y.e * (X.dx * FZ.l2));
+            acc.template add<1, 0, 0, 1>(k, Y.e * (X.dx * FZ.u2));
+            acc.template add<2, 0, 0, 0>(k, Z.e * (X.dx * FY.l2));
+            acc.template add<2, 0, 1, 0>(k, Z.e * (X.dx * FY.u2));
         }
         if (cry) {
             const int d = acc.template edge<1>(Y.x), k = acc.template node<1>(Y.x);
@@ -316,9 +321,8 @@ __device__ inline void esirkepov(Acc& acc, const Shape& X, const Shape& Y, const
             acc.template add<1, 0, 0, 1>(d, Y.x * xz01);
             acc.template add<1, 1, 0, 0>(d, Y.x * xz10);
             acc.template add<1, 1, 0, 1>(d, Y.x * xz11);
-            const float ex = X.e * Y.dx;
-            acc.template add<0, 0, 0, 0>(k, ex * FZ.l2);
-            acc.template add<0, 0, 0, 1>(k, ex * FZ.u2);
+            acc.template add<0, 0, 0, 0>(k, X.e * (Y.dx * FZ.l2));
+            acc.template add<0, 0, 0, 1>(k, X.e * (Y.dx * FZ.u2));
             acc.template add<2, 0, 0, 0>(k, Z.e * (X.l * FY.x1 + X.dl * FY.x2));
             acc.template add<2, 1, 0, 0>(k, Z.e * (X.u * FY.x1 + X.du * FY.x2));
         }
@@ -336,22 +340,20 @@ __device__ inline void esirkepov(Acc& acc, const Shape& X, const Shape& Y, const
         if (crx && cry) {
             const int kx = acc.template node<0>(X.x), ky = acc.template node<1>(Y.x);
             const int ax = acc.template edge<0>(X.x) + ky, ay = kx + acc.template edge<1>(Y.x);
-            const float fx = X.x * Y.dx, fy = Y.x * X.dx;
-            acc.template add<0, 0, 0, 0>(ax, fx * FZ.l2);
-            acc.template add<0, 0, 0, 1>(ax, fx * FZ.u2);
-            acc.template add<1, 0, 0, 0>(ay, fy * FZ.l2);
-            acc.template add<1, 0, 0, 1>(ay, fy * FZ.u2);
-            acc.template add<2, 0, 0, 0>(kx + ky, Z.e * X.dx * FY.x2);
+            acc.template add<0, 0, 0, 0>(ax, X.x * (Y.dx * FZ.l2));
+            acc.template add<0, 0, 0, 1>(ax, X.x * (Y.dx * FZ.u2));
+            acc.template add<1, 0, 0, 0>(ay, Y.x * (X.dx * FZ.l2));
+            acc.template add<1, 0, 0, 1>(ay, Y.x * (X.dx * FZ.u2));
+            acc.template add<2, 0, 0, 0>(kx + ky, Z.e * (X.dx * FY.x2));
         }
         if (crx && crz) {
             const int kx = acc.template node<0>(X.x), kz = acc.template node<2>(Z.x);
             const int ax = acc.template edge<0>(X.x) + kz, az = kx + acc.template edge<2>(Z.x);
-            const float fz = Z.x * X.dx;
             acc.template add<0, 0, 0, 0>(ax, X.x * (Y.l * FZ.x1 + Y.dl * FZ.x2));
             acc.template add<0, 0, 1, 0>(ax, X.x * (Y.u * FZ.x1 + Y.du * FZ.x2));
-            acc.template add<2, 0, 0, 0>(az, fz * FY.l2);
-            acc.template add<2, 0, 1, 0>(az, fz * FY.u2);
-            acc.template add<1, 0, 0, 0>(kx + kz, Y.e * X.dx * FZ.x2);
+            acc.template add<2, 0, 0, 0>(az, Z.x * (X.dx * FY.l2));
+            acc.template add<2, 0, 1, 0>(az, Z.x * (X.dx * FY.u2));
+            acc.template add<1, 0, 0, 0>(kx + kz, Y.e * (X.dx * FZ.x2));
         }
         if (cry && crz) {
             const int ky = acc.template node<1>(Y.x), kz = acc.template node<2>(Z.x);
@@ -360,12 +362,12 @@ __device__ inline void esirkepov(Acc& acc, const Shape& X, const Shape& Y, const
             acc.template add<1, 1, 0, 0>(ay, Y.x * (X.u * FZ.x1 + X.du * FZ.x2));
             acc.template add<2, 0, 0, 0>(az, Z.x * (X.l * FY.x1 + X.dl * FY.x2));
             acc.template add<2, 1, 0, 0>(az, Z.x * (X.u * FY.x1 + X.du * FY.x2));
-            acc.template add<0, 0, 0, 0>(ky + kz, X.e * Y.dx * FZ.x2);
+            acc.template add<0, 0, 0, 0>(ky + kz, X.e * (Y.dx * FZ.x2));
             if (crx) {
                 const int kx = acc.template node<0>(X.x);
-                acc.template add<0, 0, 0, 0>(acc.template edge<0>(X.x) + ky + kz, X.x * Y.dx * FZ.x2);
-                acc.template add<1, 0, 0, 0>(kx + ay, Y.x * X.dx * FZ.x2);
-                acc.template add<2, 0, 0, 0>(kx + az, Z.x * X.dx * FY.x2);
+                acc.template add<0, 0, 0, 0>(acc.template edge<0>(X.x) + ky + kz, X.x * (Y.dx * FZ.x2));
+                acc.template add<1, 0, 0, 0>(kx + ay, Y.x * (X.dx * FZ.x2));
+                acc.template add<2, 0, 0, 0>(kx + az, Z.x * (X.dx * FY.x2));
             }
         }
     } else {
@@ -383,12 +385,12 @@ __device__ inline void esirkepov(Acc& acc, const Shape& X, const Shape& Y, const
         acc.template add<2, 1, 1, 0>(0, jz * (X.u * yu + X.du * yu2));
         if (crx) {
             const int d = acc.template edge<0>(X.x), k = acc.template node<0>(X.x);
-            const float fx = q_dt * X.x, jx = jz * X.dx;
+            const float fx = q_dt * X.x;
             acc.template add<0, 0, 0, 0>(d, fx * yl);
             acc.template add<0, 0, 1, 0>(d, fx * yu);
             acc.template add<1, 0, 0, 0>(k, ey * (0.5f * X.dx));
-            acc.template add<2, 0, 0, 0>(k, jx * yl2);
-            acc.template add<2, 0, 1, 0>(k, jx * yu2);
+            acc.template add<2, 0, 0, 0>(k, jz * (X.dx * yl2));
+            acc.template add<2, 0, 1, 0>(k, jz * (X.dx * yu2));
         }
         if (cry) {
             const int d = acc.template edge<1>(Y.x), k = acc.template node<1>(Y.x);
@@ -400,9 +402,9 @@ __device__ inline void esirkepov(Acc& acc, const Shape& X, const Shape& Y, const
             acc.template add<2, 1, 0, 0>(k, jz * (X.u * x1 + X.du * x2));
             if (crx) {
                 const int kx = acc.template node<0>(X.x);
-                acc.template add<0, 0, 0, 0>(acc.template edge<0>(X.x) + k, q_dt * X.x * x1);
+                acc.template add<0, 0, 0, 0>(acc.template edge<0>(X.x) + k, (q_dt * X.x) * x1);
                 acc.template add<1, 0, 0, 0>(kx + d, fy * (0.5f * X.dx));
-                acc.template add<2, 0, 0, 0>(kx + k, jz * X.dx * x2);
+                acc.template add<2, 0, 0, 0>(kx + k, jz * (X.dx * x2));
             }
         }
     }
