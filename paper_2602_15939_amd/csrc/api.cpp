@@ -1106,7 +1106,7 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             const Comp3 Jc{{b->J[0], b->J[1], b->J[2]}}, Tc{{b->Jt[0], b->Jt[1], b->Jt[2]}};
             adv.push_back(ShearFoldArgs{G, Jc, Tc, (float)(b->d.shear_s * b->d.shear_omega0 * b->d.dt / 2.0),
                                         0.5f * G.n[0], (int)fl, (float)(dh - fl)});
-            advb.push_back(grid_blocks((int64_t)G.n[0] * G.n[1] * G.n[2]));
+            advb.push_back(shear_fold_blocks(G));
             for (int c = 0; c < 3; c++) std::swap(b->J[c], b->Jt[c]);
         }
         plan.grid(kBatchFoldP, fp, fpb, 3);

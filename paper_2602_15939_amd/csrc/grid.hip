@@ -122,34 +122,42 @@ __device__ inline void cell_of(const GridDev& G, int64_t t, int& x, int& y, int&
 }
 
 // J' at guarded column xg moved along y by v_s(xg) dt/2 (Sec. 2.2), v_s taken at the
-// component's staggered x: first-order upwind, i.e. linear interpolation between rows
-__device__ inline float shear_transport(const GridDev& G, const float* __restrict__ F, int c, int xg,
-                                        int y, int z, float sO_hdt, float half_nx)
+// component's staggered x: first-order upwind, i.e. linear interpolation between rows; N rows from y on
+template <int N>
+__device__ inline void shear_transport(const GridDev& G, const float* __restrict__ F, int c, int xg, int y, int z,
+                                       float sO_hdt, float half_nx, float out[N])
 {
     const float xc = (float)xg + (c == 0 ? 0.5f : 0.f) - half_nx;
     const float d = -sO_hdt * xc;
     const float fl = floorf(d);
     const int m = (int)fl;
     const float w = d - fl;
-    const float fa = F[gidx(G, xg, wrapn(y - m, G.n[1]), z)];
-    const float fb = F[gidx(G, xg, wrapn(y - m - 1, G.n[1]), z)];
-    return (1.f - w) * fa + w * fb;
+    float f[N + 1];
+#pragma unroll
+    for (int k = 0; k <= N; k++) f[k] = F[gidx(G, xg, wrapn(y + k - m - 1, G.n[1]), z)];
+#pragma unroll
+    for (int k = 0; k < N; k++) out[k] = fmaf(1.f - w, f[k + 1], w * f[k]);
 }
 // The transport and the shearing-periodic x fold in one pass (out-of-place): an interior cell
 // takes its own transported value plus, on the first and last g columns, the transported
 // guard column of the other face at the y shift of the shearing-periodic map (the exact
-// transpose of the field guard fill's interpolation).
-__device__ __attribute__((always_inline)) inline void shear_fold_cell(const ShearFoldArgs& a, int64_t t, int c)
+// transpose of the field guard fill's interpolation).  A thread takes kFoldRows cells along y, each row of
+// which is read once for two of them, with all loads in flight together:
+// 256^3 216 -> 114 us beside the sort, 150 x 90 x 84 cells 20.5 -> 11.2 us, 96^3 17.9 -> 9.4 us (a cell a thread before).
+constexpr int kFoldRows = 4;
+__device__ __attribute__((always_inline)) inline void shear_fold_cells(const ShearFoldArgs& a, int x, int y0, int z, int c)
 {
+    constexpr int N = kFoldRows;
     const GridDev& G = a.G;
-    int x, y, z;
-    cell_of(G, t, x, y, z);
     const int nx = G.n[0], ny = G.n[1], ga = G.g[0];
     const float* F = a.in.p[c];
-    float v = shear_transport(G, F, c, x, y, z, a.sO_hdt, a.half_nx);
+    float v[N];
+    shear_transport<N>(G, F, c, x, y0, z, a.sO_hdt, a.half_nx, v);
     if (x < ga) {  // guard column x + nx, the image of (x, y + dys)
-        v += (1.f - a.dys_w) * shear_transport(G, F, c, x + nx, wrapn(y - a.dys_int, ny), z, a.sO_hdt, a.half_nx) +
-             a.dys_w * shear_transport(G, F, c, x + nx, wrapn(y - a.dys_int - 1, ny), z, a.sO_hdt, a.half_nx);
+        float t[N + 1];
+        shear_transport<N + 1>(G, F, c, x + nx, y0 - a.dys_int - 1, z, a.sO_hdt, a.half_nx, t);
+#pragma unroll
+        for (int k = 0; k < N; k++) v[k] += fmaf(1.f - a.dys_w, t[k + 1], a.dys_w * t[k]);
     }
     if (x >= nx - ga) {  // guard column x - nx, the image of (x, y - dys)
         // shift -dys = js + w with js = -dys_int - 1, w = 1 - dys_w (dys_w > 0), else -dys_int
@@ -159,17 +167,25 @@ __device__ __attribute__((always_inline)) inline void shear_fold_cell(const Shea
             js = -a.dys_int - 1;
             w = 1.f - a.dys_w;
         }
-        v += (1.f - w) * shear_transport(G, F, c, x - nx, wrapn(y - js, ny), z, a.sO_hdt, a.half_nx) +
-             w * shear_transport(G, F, c, x - nx, wrapn(y - js - 1, ny), z, a.sO_hdt, a.half_nx);
+        float t[N + 1];
+        shear_transport<N + 1>(G, F, c, x - nx, y0 - js - 1, z, a.sO_hdt, a.half_nx, t);
+#pragma unroll
+        for (int k = 0; k < N; k++) v[k] += fmaf(1.f - w, t[k + 1], w * t[k]);
     }
-    a.out.p[c][gidx(G, x, y, z)] = v;
+    float* out = a.out.p[c] + gidx(G, x, y0, z);
+#pragma unroll
+    for (int k = 0; k < N; k++)
+        if (y0 + k < ny) out[(int64_t)G.sy * k] = v[k];
 }
-// grid-stride over the cells (the batched launch gives every cell its own thread)
+// grid-stride over the threads' cells (the batched launch gives each its own thread)
 __device__ __attribute__((always_inline)) inline void shear_fold_body(const ShearFoldArgs& a, int blk, int nblk, int c)
 {
-    const int64_t n = (int64_t)a.G.n[0] * a.G.n[1] * a.G.n[2];
-    for (int64_t t = (int64_t)blk * kBlock + threadIdx.x; t < n; t += (int64_t)nblk * kBlock)
-        shear_fold_cell(a, t, c);
+    const uint32_t nx = (uint32_t)a.G.n[0], rows = (uint32_t)(a.G.n[1] + kFoldRows - 1) / kFoldRows;
+    const int64_t n = (int64_t)nx * rows * a.G.n[2];
+    for (int64_t t = (int64_t)blk * kBlock + threadIdx.x; t < n; t += (int64_t)nblk * kBlock) {
+        const uint32_t u = (uint32_t)t, r = a.G.div0.div(u), z = r / rows;
+        shear_fold_cells(a, (int)(u - r * nx), (int)(r - z * rows) * kFoldRows, (int)z, c);
+    }
 }
 PIC_BATCHED_KERNEL(shear_fold, ShearFoldArgs, kBlock)
 
@@ -1523,6 +1539,10 @@ FoldPArgs fold_args(const GridDev& G, float* const* J, int shear)
 }
 unsigned fold_blocks(const FoldPArgs& a) { return nblocks((int64_t)a.n[0] + a.n[1] + a.n[2]); }
 
+unsigned shear_fold_blocks(const GridDev& G)
+{
+    return nblocks((int64_t)G.n[0] * ((G.n[1] + kFoldRows - 1) / kFoldRows) * G.n[2]);
+}
 // Fold the deposited current: in place, or for the shearing box into `out`, every interior cell.
 hipError_t fold_current(const GridDev& G, float* const* J, float* const* out, int shear,
                         double sO, double dt, double dys_half, hipStream_t st)
@@ -1533,7 +1553,7 @@ hipError_t fold_current(const GridDev& G, float* const* J, float* const* out, in
     if (shear) {
         const double fl = floor(dys_half);
         const Comp3 Oc{{out[0], out[1], out[2]}};
-        const unsigned nb = std::min(nblocks((int64_t)G.n[0] * G.n[1] * G.n[2]), kStrideBlocks);
+        const unsigned nb = std::min(shear_fold_blocks(G), kStrideBlocks);
         shear_fold_kernel<<<dim3(nb, 3), kBlock, 0, st>>>(
             ShearFoldArgs{G, Jc, Oc, (float)(sO * dt / 2.0), 0.5f * G.n[0], (int)fl, (float)(dys_half - fl)});
     }

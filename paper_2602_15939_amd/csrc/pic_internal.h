@@ -489,6 +489,7 @@ hipError_t fill_guards(const GridDev& G, float* const* comps, int ncomp, int she
 // otherwise periodic in place.
 FoldPArgs fold_args(const GridDev& G, float* const* J, int shear);
 unsigned fold_blocks(const FoldPArgs& a);
+unsigned shear_fold_blocks(const GridDev& G);
 hipError_t fold_current(const GridDev& G, float* const* J, float* const* out, int shear,
                         double sO, double dt, double dys_half, hipStream_t st);
 hipError_t yee_b(const MaxwellDev& M, hipStream_t st);
