@@ -1339,18 +1339,25 @@ __global__ __launch_bounds__(kBlock) void clear_kernel(ClearArgs a)
 }
 
 // interior <-> dense copies of gridDim.y arrays: dense index x + n0*(y + n1*z)
-__global__ __launch_bounds__(kBlock) void interior_copy_kernel(GridDev G, Comp6 guarded, Comp6 dense, int to_dense)
+typedef float Quad __attribute__((ext_vector_type(4), aligned(4)));  // a row may start at any element
+// A thread moves up to four consecutive elements of a row (quads divides by the quads of a row).  E or B of
+// 256^3 138 -> 112 us, of 128 x 64 x 64 8.1 -> 4.9 us against an element a thread.
+__global__ __launch_bounds__(kBlock) void interior_copy_kernel(GridDev G, Comp6 guarded, Comp6 dense, int to_dense, FastDiv quads)
 {
-    const int c = (int)blockIdx.y;
-    const int64_t n = (int64_t)G.n[0] * G.n[1] * G.n[2];
+    const int c = (int)blockIdx.y, nx = G.n[0];
+    const uint32_t per_row = (uint32_t)(nx + 3) / 4;
+    const int64_t n = (int64_t)per_row * G.n[1] * G.n[2];
     for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < n; t += (int64_t)gridDim.x * kBlock) {
-        int x, y, z;
-        cell_of(G, t, x, y, z);
-        const int64_t i = gidx(G, x, y, z);
-        if (to_dense)
-            dense.p[c][t] = guarded.p[c][i];
+        const uint32_t r = quads.div((uint32_t)t), z = G.div1.div(r);
+        const int x = 4 * (int)((uint32_t)t - r * per_row);
+        float* const g = guarded.p[c] + gidx(G, x, (int)(r - z * (uint32_t)G.n[1]), (int)z);
+        float* const d = dense.p[c] + (int64_t)r * nx + x;
+        const float* const from = to_dense ? g : d;
+        float* const to = to_dense ? d : g;
+        if (x + 4 <= nx)
+            *reinterpret_cast<Quad*>(to) = *reinterpret_cast<const Quad*>(from);
         else
-            guarded.p[c][i] = dense.p[c][t];
+            for (int k = 0; k < nx - x; k++) to[k] = from[k];
     }
 }
 
@@ -1731,8 +1738,9 @@ hipError_t interior_copy(const GridDev& G, float* const* guarded, float* const* 
         A.p[c] = guarded[c];
         D.p[c] = dense[c];
     }
-    const unsigned nb = std::min(nblocks((int64_t)G.n[0] * G.n[1] * G.n[2]), kStrideBlocks);
-    interior_copy_kernel<<<dim3(nb, (unsigned)ncomp), kBlock, 0, st>>>(G, A, D, to_dense);
+    const int64_t per_row = (G.n[0] + 3) / 4;
+    const unsigned nb = std::min(nblocks(per_row * G.n[1] * G.n[2]), kStrideBlocks);
+    interior_copy_kernel<<<dim3(nb, (unsigned)ncomp), kBlock, 0, st>>>(G, A, D, to_dense, FastDiv::make((uint32_t)per_row));
     return hipGetLastError();
 }
 hipError_t box_record(const GridDev& G, float* const* comps, const SumArgs& P, double* part, int nblk, BoxRecord* out,

@@ -58,3 +58,20 @@ def test_histogram_beside_the_edges(static):
             assert list(h) == list(oracle.energy_histogram(u[0], u[1], u[2], e)), len(e)
     finally:
         b.close()
+
+
+@pytest.mark.parametrize("n", [(5, 4), (6, 7), (7, 5), (4, 4, 5), (9, 5, 4), (66, 5, 6)])
+def test_fields_in_and_out_at_any_row_length(n):
+    """Rows of one to four elements beyond whole quads, from and to dense arrays whose rows start anywhere."""
+    from paper_2602_15939_amd.box import Box
+
+    n3 = tuple(n) + (1,) * (3 - len(n))
+    g = torch.Generator().manual_seed(2)
+    E, B = (torch.randn((3, n3[2], n3[1], n3[0]), generator=g) for _ in range(2))
+    b = Box(len(n), n, frame=L.FRAME_PLAIN, species=((-1.0, 0.0, 16),))
+    try:
+        b.set_fields(E, B)
+        e, f = b.get_fields()
+        assert torch.equal(e.cpu(), E) and torch.equal(f.cpu(), B)
+    finally:
+        b.close()
