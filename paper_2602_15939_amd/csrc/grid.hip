@@ -278,7 +278,7 @@ __device__ __attribute__((always_inline)) inline void yee_b_cell(const MaxwellDe
 __device__ __attribute__((always_inline)) inline void yee_b_body(const MaxwellDev& M, int blk, int nblk, int)
 {
     const int64_t n = (int64_t)M.G.n[0] * M.G.n[1] * M.G.n[2];
-    for (int64_t t = (int64_t)blk * kBlock + threadIdx.x; t < n; t += (int64_t)nblk * kBlock) yee_b_cell(M, t);
+    for (int64_t t = (int64_t)xcd_contiguous(blk, nblk) * kBlock + threadIdx.x; t < n; t += (int64_t)nblk * kBlock) yee_b_cell(M, t);
 }
 PIC_BATCHED_KERNEL(yee_b, MaxwellDev, kBlock)
 
@@ -308,7 +308,7 @@ __device__ __attribute__((always_inline)) inline void yee_e_cell(const MaxwellDe
 __device__ __attribute__((always_inline)) inline void yee_e_body(const MaxwellDev& M, int blk, int nblk, int)
 {
     const int64_t n = (int64_t)M.G.n[0] * M.G.n[1] * M.G.n[2];
-    for (int64_t t = (int64_t)blk * kBlock + threadIdx.x; t < n; t += (int64_t)nblk * kBlock) yee_e_cell(M, t);
+    for (int64_t t = (int64_t)xcd_contiguous(blk, nblk) * kBlock + threadIdx.x; t < n; t += (int64_t)nblk * kBlock) yee_e_cell(M, t);
 }
 PIC_BATCHED_KERNEL(yee_e, MaxwellDev, kBlock)
 
@@ -545,15 +545,16 @@ __device__ inline void ksb_load(const KsbDev& K, int x, int y, int z, int64_t i,
 // 2D (and any size): one thread per cell, neighbours straight from memory, beyond a face at their
 // images, so that no guard fill runs between sweeps.  On small grids a step is bound by its launches
 // (the fills were two of three in 2D): the 64^2 box replayed as a graph 201 -> 176 us a step, a
-// 20 x 12 x 16 box stepped call by call 223 -> 155 us; on 150 x 90 x 84 cells a sweep takes 26 us
-// (2.9 TB/s of the 72 B a cell it must move).  A separate branch for the cells at the x faces was
+// 20 x 12 x 16 box stepped call by call 223 -> 155 us.  A separate branch for the cells at the x faces was
 // slower than the fills (213 us on 64^2: every wave of a row has such a lane and ran both branches).
+// An XCD takes a contiguous range of the cells, so that its L2 serves the rows above and below (on
+// 150 x 90 x 84 cells 25.5 -> 18.4 us a sweep, on 96^3 17.6 -> 13.7 us).
 template <bool FIRST>
-__device__ __attribute__((always_inline)) inline void ksb_sweep_body(const KsbDev& K, int blk, int, int)
+__device__ __attribute__((always_inline)) inline void ksb_sweep_body(const KsbDev& K, int blk, int nblk, int)
 {
     if (ksb_skip(K)) return;
     const GridDev& G = K.G;
-    const int64_t t = (int64_t)blk * kBlock + threadIdx.x;
+    const int64_t t = (int64_t)xcd_contiguous(blk, nblk) * kBlock + threadIdx.x;
     float dm = 0.f, fm = 0.f;
     if (t < (int64_t)G.n[0] * G.n[1] * G.n[2]) {
         int x, y, z;
@@ -1577,18 +1578,18 @@ hipError_t yee_e(const MaxwellDev& M, hipStream_t st)
     yee_e_kernel<<<std::min(nblocks((int64_t)M.G.n[0] * M.G.n[1] * M.G.n[2]), kStrideBlocks), kBlock, 0, st>>>(M);
     return hipGetLastError();
 }
-// The staged single sweep marches over planes, each waiting for the one before: on grids that the caches
-// hold, one thread a cell is faster.  us a sweep, staged / one thread a cell: 128 x 64 x 64 14.7 / 11.0,
-// 128^3 39.5 / 35.1, 256 x 128 x 128 72 / 86, 256^3 261 / 323; the line lies between the middle two.
+// Where the staged sweep and the pass over z, which march over planes that each wait for the one before,
+// win: on grids that the last-level cache does not hold.  us a step of 8 sweeps, passes / staged sweeps /
+// one thread a cell: 64^3 74 / 54 / 56, 128 x 64 x 64 99 / 146 / 74, 128^3 265 / 336 / 221,
+// 256 x 128 x 128 454 / 577 / 674, 256^3 1849 / 2117 / 2611; the line lies between the middle two.
+constexpr int64_t kStagedCells = 3ll << 20;
 bool ksb_staged(const GridDev& G)
 {
-    return G.dim == 3 && G.n[0] % KX == 0 && (int64_t)G.n[0] * G.n[1] * G.n[2] > 3ll << 20;
+    return G.dim == 3 && G.n[0] % KX == 0 && (int64_t)G.n[0] * G.n[1] * G.n[2] > kStagedCells;
 }
-// The two-sweep pass on grids of a staged shape: us a step of 8 sweeps, passes / one thread a cell: 64^3
-// 74 / 62, 128 x 128 x 64 156 / 147, 128^3 265 / 272; the line lies between the last two.
 bool ksb_pass_fits(const GridDev& G)
 {
-    return G.dim == 3 && G.n[0] % kPassX == 0 && (int64_t)G.n[0] * G.n[1] * G.n[2] > 3ll << 19 && 4 * (int64_t)G.sz * G.n[2] < (int64_t(1) << 32);
+    return G.dim == 3 && G.n[0] % kPassX == 0 && (int64_t)G.n[0] * G.n[1] * G.n[2] > kStagedCells && 4 * (int64_t)G.sz * G.n[2] < (int64_t(1) << 32);
 }
 
 // Planes per workgroup of the staged kernels and the workgroups of a launch over `columns` column

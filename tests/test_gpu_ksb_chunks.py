@@ -26,15 +26,15 @@ def test_pass_equals_single_sweeps_for_any_chunks(n):
             b.close()
 
 
-# passes begin beyond 3 x 2^19 cells: one, three and sixteen x tiles, ragged y tiles, y smaller than the
-# windows, chunks of several planes and a ragged last one, odd counts (a last single sweep, one thread a cell)
-@pytest.mark.parametrize("n,K", [((64, 250, 100), 4), ((192, 91, 91), 3), ((1024, 4, 401), 5)])
+# passes and staged single sweeps begin beyond 3 x 2^20 cells: one, three and sixteen x tiles, ragged y tiles,
+# y smaller than the windows, a ragged last chunk, odd counts (a last single sweep, one thread a cell unless
+# the x size is a multiple of 128)
+@pytest.mark.parametrize("n,K", [((64, 250, 200), 4), ((192, 91, 181), 3), ((1024, 4, 801), 5)])
 def test_pass_equals_single_sweeps_beyond_its_line(n, K):
     test_pass_equals_staged_single_sweeps(n, K)
 
 
-# beyond 3 x 2^20 cells single sweeps are staged too (below, one thread a cell): a last chunk of one
-# plane, ragged y tiles, one and two x tiles; odd counts end in a single sweep
+# a last chunk of one plane, ragged y tiles, one and two x tiles; odd counts end in a single sweep
 @pytest.mark.parametrize("n,K", [((128, 255, 97), 4), ((256, 126, 100), 5)])
 def test_pass_equals_staged_single_sweeps(n, K):
     J = _current(n, 7)
