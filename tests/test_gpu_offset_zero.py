@@ -1,0 +1,46 @@
+"""An in-cell offset of zero with either sign: a particle at -0.0 (what a subtraction or a remainder of negative
+zeros leaves in a caller's arrays) deposits the current of the one at +0.0, in every direction of motion on every
+axis, fused and not."""
+import itertools
+
+import numpy as np
+import pytest
+import torch
+
+from _cases import Case
+from paper_2602_15939_amd import _lib as L
+
+pytestmark = pytest.mark.gpu
+
+
+def current(dim, n, zero, fuse, combos):
+    cell = torch.tensor([sum((2 + 4 * k[d]) * n[0] ** d for d in range(dim)) for k, _ in combos], dtype=torch.int32)
+    off = torch.full((dim, len(combos)), zero)
+    u = torch.tensor([list(v) + [0.4] * (3 - dim) for _, v in combos]).T.contiguous()
+    other = dict(cell=torch.zeros(1, dtype=torch.int32), off=torch.full((dim, 1), 0.25), u=torch.zeros((3, 1)))
+    field = np.zeros((3,) + ((n[2],) if dim == 3 else (1,)) + (n[1], n[0]), np.float32)
+    c = Case(dim, n, "plain", parts=[dict(cell=cell, off=off, u=u), other], q=1e-4, fields=(field, field))
+    try:
+        c.gpu.sort()
+        c.gpu.push(fuse=fuse)
+        if not fuse:
+            c.gpu.deposit()
+        c.gpu.remap(L.REMAP_CURRENT)
+        c.oracle_step()
+        return c.gpu.get_current().cpu().numpy(), c.J
+    finally:
+        c.close()
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("fuse", [True, False])
+def test_negative_zero_offset_deposits_as_zero(dim, fuse):
+    n = (12,) * dim
+    # a particle apart from the others for every direction of motion on every axis
+    combos = list(zip(itertools.product(range(3), repeat=dim), itertools.product((0.9, 0.0, -0.9), repeat=dim)))
+    (J, ref), (Jn, refn) = (current(dim, n, z, fuse, combos) for z in (0.0, -0.0))
+    np.testing.assert_array_equal(ref, refn)
+    assert np.abs(ref).max() > 0
+    # one weight or displacement is a few units of 2^-24 off, a current that times q/dt
+    assert np.abs(Jn - ref).max() <= 1e-6 * 1e-4 / 0.45
+    assert np.abs(J - ref).max() <= 1e-6 * 1e-4 / 0.45
