@@ -221,9 +221,10 @@ __device__ inline float renorm(float s, int& dc)
 {
     const float f = __builtin_amdgcn_fmed3f(floorf(s), -1.f, 1.f);
     const float r = __fsub_rn(s, f);
-    const bool full = r >= 1.f && f < 0.f;  // s + 1 rounded up to 1
+    // s + 1 rounded up to 1; or s is no number, for which f is -1: the particle stays in its cell, its offset NaN
+    const bool full = !(r < 1.f) && f < 0.f;
     dc = (int)f + (full ? 1 : 0);
-    return full ? 0.f : r;
+    return full ? __fsub_rn(r, 1.f) : r;
 }
 
 // ------------------------------------------------------------------ Esirkepov deposit
