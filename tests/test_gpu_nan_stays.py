@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dim,n,frame", [(2, (40, 33), "plain"), (2, (48, 32), "shear"), (3, (24, 16, 9), "shear"),
                                          (3, (16, 16, 24), "expand")])
 def test_non_finite_momentum_stays(dim, n, frame):
-    at = [0, 7, 8, 15, 16, n[0] - 1]  # x, on every edge kind; y and z at both faces
+    at = sorted({0, 7, 8, 15, 16 % n[0], n[0] - 1})  # x, on every edge kind; y and z at both faces
     cells = [x + n[0] * (y + n[1] * z) for x in at for y in (0, n[1] - 1) for z in ((0, n[2] - 1) if dim == 3 else (0,))]
     base = synth.pair_plasma(n, 3, 0.3, 5)
     m = len(cells)
