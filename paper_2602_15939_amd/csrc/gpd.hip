@@ -243,8 +243,8 @@ __device__ inline Shape shape(float o, float D)
     A.l = 1.f - o;
     A.u = o;
     const bool up = o >= 0.5f;  // s lies below c; 1 - o is exact then
-    const float x0 = up ? -A.l : o, x1 = x0 + D;
-    const uint32_t sign = up ? 0x80000000u : 0u;  // s below c; not x0's own sign, which -0 at an offset of 0 has too
+    const float x0 = up ? -A.l : fabsf(o), x1 = x0 + D;  // an offset of -0 has c = L and s = U as one of 0
+    const uint32_t sign = __float_as_uint(x0) & 0x80000000u;
     const float t = flip(x1, sign);  // the new position counted towards s
     const float s0 = fabsf(x0), c0 = 1.f - s0;
     const float dc = (1.f - fabsf(x1)) - c0, ds = fmaxf(0.f, t) - s0;
