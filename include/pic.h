@@ -103,7 +103,7 @@ enum pic_leaky_mode { PIC_LEAKY_DISPLACEMENT = 0, PIC_LEAKY_PROBABILISTIC = 1 };
 #define PIC_DERR_NAN 2u      /* non-finite momentum */
 #define PIC_DERR_ORDER 4u    /* a particle outside its tile: handled on the slow path */
 #define PIC_DERR_CELL 8u     /* pic_set_particles met a cell index outside the grid */
-#define PIC_DERR_SORT 16u    /* a batched sort found a particle beyond the neighbouring tiles */
+#define PIC_DERR_SORT 16u    /* a batched step found a particle beyond the neighbouring tiles */
 #define PIC_DERR_NOCONVERGE 32u /* shearing box, maxwell_tol > 0: the fixed-point sweeps of a
                                    Maxwell step did not meet the tolerance within maxwell_iters */
 
@@ -361,9 +361,8 @@ int32_t pic_escape_compact(pic_box* const* boxes, int32_t nb, uint32_t flags);
    runs as one launch per kernel over all nb boxes (independent boxes of any frame and size,
    sharing one stream; 2D tiles 16x16 or 8x8, 3D 8x8x8): per-box argument tables are staged in
    pinned host memory, copied once per step, and each launch maps its workgroups to boxes
-   through a prefix table.  The sorts of a batched step use the neighbour-migration counting
-   sort only; a particle found beyond the neighbouring tiles latches PIC_DERR_SORT on its box
-   (that box's sort is then not valid).  Results equal the unbatched step's up to the order of
+   through a prefix table.  A particle that the push of a batched step finds beyond the
+   neighbouring tiles latches PIC_DERR_SORT on its box.  Results equal the unbatched step's up to the order of
    the FP32 additions of the tile-halo current.  PIC_EINVAL if the boxes do not share one
    stream, appear twice or have an unsupported tile shape.
    With PIC_STEP_GRAPH the table transfer and the launches of the batched step are captured

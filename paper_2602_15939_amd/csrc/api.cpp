@@ -1014,8 +1014,7 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             }
             const int nt = b->tl.n_tiles;
             for (int s = 0; s < b->nsp; s++) {
-                MigArgs a = mig_args(b, b->sp[s]);
-                a.keys[0] = nullptr;  // the push has latched kErrSort
+                const MigArgs a = mig_args(b, b->sp[s]);
                 mo.push_back(a);
                 mob.push_back(mig_offset_blocks(nt));
                 if (mig_needs_scan(nt)) {
@@ -1061,7 +1060,7 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             }
             auto& gr = groups[group_of(b)];
             StepDev P = make_step(b);
-            P.mig_latch = 1;  // no radix fallback behind a batched sort
+            P.mig_latch = 1;
             split_tiles(P, b->tile, group_tiles[group_of(b)], slots_per_tile(b));
             gr.first.push_back(P);
             gr.second.push_back((uint32_t)b->tl.n_tiles << P.lsplit);

@@ -892,6 +892,8 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
                     if (frame_sheared(FRAME) && xwrap && P.mg.nt[1] > 1)
                         dy = ring_step((ncy >> P.tl.lt[1]) - (dx > 0 ? mco : mci), P.mg.nt[1]);
                     d = dy == 2 ? -1 : (dx + 1) + 3 * (dy + 1) + 9 * (dz + 1);
+                    // the caller moved the particle since the sort: any number of tiles away
+                    if (!in_tile && ((unsigned)(dx + 1) > 2u || (unsigned)(dy + 1) > 2u || (unsigned)(dz + 1) > 2u)) d = -1;
                 }
                 if (ncell < 0) d = kMigDead;
                 // the particles that stay in the tile (the common direction) are not counted: the

@@ -178,9 +178,9 @@ struct StepDev {
     // migration counts of the next sort, taken by the push: per species and source tile
     // (= this launch's tile), the particles per direction (mcnt[tile * kMigDirs + d], added to the
     // cleared counts by the parts of a split tile); a
-    // particle beyond the neighbouring tiles sets mfb (the radix fallback runs then)
+    // particle beyond the neighbouring tiles sets mfb (the next sort is a radix sort then)
     int count_mig;
-    int mig_latch;  // batched steps (no radix fallback behind the sort): latch kErrSort too
+    int mig_latch;  // batched steps: latch kErrSort too
     MigGeo mg;
     uint32_t* mcnt[kMaxSpecies];
     int32_t* mfb[kMaxSpecies];
@@ -414,7 +414,7 @@ struct SortBufs {
 };
 
 // Migration sort of one species: its arrays, the push's counts, and the general sort's buffers for
-// a species that turns out to be beyond it (keys[0] null: none, the error is latched by the push)
+// a species that turns out to be beyond it
 struct MigArgs {
     const int32_t* cell;
     const int32_t* toff_prev;

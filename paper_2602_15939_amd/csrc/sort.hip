@@ -274,7 +274,8 @@ hipError_t tile_sort(const int32_t* cell, const int32_t* n_live_in, int n_upper,
 // increasing source tile, i.e. increasing slot, for the live slots (the permutation's
 // observable part).  Slots from the previous dead bin stay dead at the end, after the
 // particles that died since.  A push that meets a particle beyond the neighbouring tiles (none of
-// its moves does) sets a flag, on which the scatter's first workgroup sorts the species alone.
+// its own moves does: only one that the caller moved in its memory between sort and push) sets a
+// flag, on which the scatter's first workgroup sorts the species alone.
 
 __device__ inline void dir_steps(int d, int& dx, int& dy, int& dz)
 {
@@ -511,7 +512,7 @@ __device__ __attribute__((always_inline)) inline void mig_scatter_body(const Mig
     __shared__ uint32_t sl[kMigSmall + 1], ws[2][kBlock / 64];
     static_assert(sizeof(lcell) >= 4 * (256 * (1 + kBlock / 64) + kBlock / 64), "the lone sort's LDS");
     if (*a.fallback) {
-        if (blk == 0 && a.keys[0]) radix_alone(a, lcell[0]);
+        if (blk == 0) radix_alone(a, lcell[0]);
         return;
     }
     const int nt = g.n_tiles, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
