@@ -144,6 +144,8 @@ struct pic_box {
     unsigned long long* ctr = nullptr;
     uint32_t* conv = nullptr;  // shearing box: convergence record of the tolerance-mode sweeps
     int last_sweeps = 0;       // sweeps of the last Maxwell step (-1: the device record has it)
+    unsigned long long* tsum = nullptr;  // split tiles: sums of their parts ...
+    uint32_t* tdone = nullptr;           // ... and parts done
     double* red_part = nullptr;
     BoxRecord* record = nullptr;
     double* hist_edges = nullptr;               // energy histogram: edges ...
@@ -360,6 +362,8 @@ StepDev make_step(pic_box* b)
     P.mig_latch = 0;
     P.nsp = b->nsp;
     split_tiles(P, b->tile, b->tl.n_tiles, slots_per_tile(b));
+    P.tsum = b->tsum;
+    P.tdone = b->tdone;
     P.mg = b->mg;
     for (int s = 0; s < b->nsp; s++) {
         P.mcnt[s] = b->sp[s].sb.mcnt;
@@ -461,16 +465,18 @@ void set_tiling(pic_box* b, const int tile[3])
     b->mig_ok = !(g.shear && (g.nt[0] < 3 || (g.nt[1] > 2 && b->n[1] % tile[1] == 1)));
 }
 
-// the largest tile count over the supported shapes (tile-indexed workspace is sized for it)
-int max_tiles(int dim, const int n[3])
+// the largest tile count and split_words over the supported shapes (tile-indexed workspace is sized for them)
+int max_tiles(int dim, const int n[3], int64_t& words)
 {
     int c[8][3];
     const int nc = tile_candidates(dim, false, c, 8);
     int m = 1;
+    words = 0;
     for (int i = 0; i < nc; i++) {
         int t = 1;
         for (int k = 0; k < 3; k++) t *= (n[k] + c[i][k] - 1) / c[i][k];
         m = std::max(m, t);
+        words = std::max(words, split_words(dim, c[i], t));
     }
     return m;
 }
@@ -1484,7 +1490,8 @@ bool unfused_reserved(const pic_box* b) { return (b->d.flags & PIC_BOX_UNFUSED) 
 int32_t alloc_all(pic_box* b, const pic_box_mem* m)
 {
     const pic_box_desc* d = &b->d;
-    const int tiles_ws = max_tiles(b->dim, b->n);  // any supported tiling fits the workspace
+    int64_t split_ws;
+    const int tiles_ws = max_tiles(b->dim, b->n, split_ws);  // any supported tiling fits the workspace
     int32_t r = PIC_OK;
     const bool measuring = b->alloc_pass == 1;
     // a buffer the caller may own: taken from m (checked: non-null, 256-byte aligned) or carved
@@ -1560,6 +1567,8 @@ int32_t alloc_all(pic_box* b, const pic_box_mem* m)
     if (!r) r = dalloc(b, b->err, 4);
     if (!r) r = dalloc(b, b->ctr, 4);
     if (!r && sheared(d)) r = dalloc(b, b->conv, kKsbConvWords);
+    if (!r && split_ws > 0) r = dalloc(b, b->tsum, (size_t)split_ws);
+    if (!r && split_ws > 0) r = dalloc(b, b->tdone, (size_t)tiles_ws);
     if (!r) r = dalloc(b, b->red_part, (size_t)(6 + kPartSums * kMaxSpecies) * kRedBlocks);
     if (!r) r = dalloc(b, b->record, 1);
     if (!r) r = dalloc(b, b->hist_edges, kHistMaxBins + 1);
@@ -1569,6 +1578,9 @@ int32_t alloc_all(pic_box* b, const pic_box_mem* m)
     if (measuring || r) return r;
     if (hipMemsetAsync(b->err, 0, 4 * sizeof(uint32_t), b->st) != hipSuccess) return PIC_EDEVICE;
     if (hipMemsetAsync(b->ctr, 0, 4 * sizeof(unsigned long long), b->st) != hipSuccess) return PIC_EDEVICE;
+    if (split_ws > 0 && (hipMemsetAsync(b->tsum, 0, (size_t)split_ws * sizeof(unsigned long long), b->st) != hipSuccess ||
+                         hipMemsetAsync(b->tdone, 0, (size_t)tiles_ws * sizeof(uint32_t), b->st) != hipSuccess))
+        return PIC_EDEVICE;
     if (b->conv && hipMemsetAsync(b->conv, 0, kKsbConvWords * sizeof(uint32_t), b->st) != hipSuccess)
         return PIC_EDEVICE;
     if (b->mj) {

@@ -5,7 +5,8 @@
 // One workgroup owns one tile: it stages E and B of the tile plus the guard layers the gather
 // reaches in LDS (one region per Yee component, sized for that component's lattice),
 // accumulates the tile's current (plus the deposit halo) in LDS as 64-bit fixed point, and
-// flushes it once to HBM with float atomics (only the halo overlaps a neighbour tile).
+// flushes it once to HBM with float atomics (only the halo overlaps a neighbour tile).  In boxes
+// of few tiles several workgroups share one and the last of them flushes their sum.
 // Particles are read through the sort permutation and written in sorted slot order, so the
 // tile sort's scatter is fused into this pass.  A particle found outside its tile (only
 // possible without a sort since the last push) takes the global-memory path.
@@ -614,11 +615,35 @@ __device__ inline float fixed_to_float(unsigned long long a, float unit)
     return (float)(((double)hi * 4294967296.0 + (double)lo) * (double)unit);
 }
 
-// Flush the tile current (interior + deposit halo) to the global arrays with float atomics.
+// Flush the tile current (interior + deposit halo) to the global arrays with float atomics.  The parts of a
+// split tile add their integers to the tile's words of P.tsum first, and the one that comes last flushes
+// the whole sum: exact and converted once, however the tile was split.  It leaves words and count at zero
+// for the next launch; nobody waits.  The parts meet in device-scope atomics alone, so each needs only its
+// own to be done before it counts itself; __threadfence() would write back and invalidate the L2 for every
+// part (a step of the 64^2 box 115 us, an unfused one of the 384^2 box 333 us; 90 and 145 us this way).  Parts
+// that rounded to FP32 each and met in the current's atomics took 83 and 140 us, but put the rounding of their
+// gross sums and the order of the additions into every node.
+// flag: a shared word that nothing else uses any more.
 template <class G, int DIM, int NT>
-__device__ inline void flush_current(const unsigned long long* __restrict__ Jl, const StepDev& P,
-                                     const int t0[3], const int ext[3], int tid)
+__device__ inline void flush_current(unsigned long long* Jl, const StepDev& P, int tile,
+                                     const int t0[3], const int ext[3], int tid, uint32_t* flag)
 {
+    if (P.lsplit) {
+        unsigned long long* const sum = P.tsum + (size_t)tile * G::JTOT;
+        for (int e = tid; e < G::JTOT; e += NT)
+            if (Jl[e]) __hip_atomic_fetch_add(&sum[e], Jl[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0)
+            *flag = __hip_atomic_fetch_add(&P.tdone[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == 1u << P.lsplit;
+        __syncthreads();
+        if (!*flag) return;
+        for (int e = tid; e < G::JTOT; e += NT) {  // its own entries below: no barrier
+            Jl[e] = __hip_atomic_load(&sum[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&sum[e], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (tid == 0) __hip_atomic_store(&P.tdone[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     for (int e = tid; e < G::JTOT; e += NT) {
         const unsigned long long a = Jl[e];
         if (a == 0ull) continue;
@@ -966,7 +991,7 @@ __device__ __attribute__((always_inline)) inline void gpd_body(const StepDev& P,
         else if (mc[tid])
             atomicAdd(cnt, mc[tid]);
     }
-    if (fuse) flush_current<G, DIM, NT>(Jl, P, t0, ext, tid);
+    if (fuse) flush_current<G, DIM, NT>(Jl, P, tile, t0, ext, tid, mc);
 }
 
 // Register budgets: 3D for the 6 waves per SIMD of two 12-wave workgroups a CU; 2D tiles of 8x8 (7 KB of
@@ -995,6 +1020,7 @@ __global__ __launch_bounds__(NT) void deposit_kernel(StepDev P)
 {
     using G = Geo<DIM, TX, TY, TZ>;
     __shared__ unsigned long long Jl[G::JTOT];
+    __shared__ uint32_t flag;
     const int unit = xcd_contiguous(blockIdx.x, gridDim.x);
     const Share share(P, unit);
     const int tile = share.tile;
@@ -1027,7 +1053,7 @@ __global__ __launch_bounds__(NT) void deposit_kernel(StepDev P)
         }
     }
     __syncthreads();
-    flush_current<G, DIM, NT>(Jl, P, t0, ext, tid);
+    flush_current<G, DIM, NT>(Jl, P, tile, t0, ext, tid, &flag);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1048,13 +1074,24 @@ constexpr int threads_for(int dim, int cells)
 // slots a species): 84 us whole, 19 us in 256 workgroups; 20 x 12 x 16 cells: 32 -> 28 us.
 // Where the parts still leave the chip idle, one of two species each halves the chain again: 20 x 12 x 16
 // cells 21.2 -> 15.8 us, the 64^2 box 15.6 -> 12.4 us.
+static int64_t split_below(int dim) { return dim == 3 ? 512 : 1024; }
 void split_tiles(StepDev& P, const int t[3], int64_t n_tiles, int64_t slots_per_tile)
 {
-    const int64_t want = P.dim == 3 ? 512 : 1024, nt = threads_for(P.dim, t[0] * t[1] * t[2]);
+    const int64_t want = split_below(P.dim), nt = threads_for(P.dim, t[0] * t[1] * t[2]);
     P.lsplit = 0;
     while (P.lsplit < 6 && (n_tiles << P.lsplit) < want && (slots_per_tile >> P.lsplit) > nt) P.lsplit++;
     P.by_species = P.nsp == 2 && (n_tiles << P.lsplit) < want ? 1 : 0;
     P.lsplit += P.by_species;
+}
+
+// words of P.tsum: a launch has at least the box's tiles, so a box of more is never split
+int64_t split_words(int dim, const int t[3], int64_t n_tiles)
+{
+    if (n_tiles >= split_below(dim)) return 0;
+    if (dim == 3) return n_tiles * (t[0] == 8 ? Geo<3, 8, 8, 8>::JTOT : Geo<3, 4, 4, 4>::JTOT);
+    if (t[0] == 16) return n_tiles * Geo<2, 16, 16, 1>::JTOT;
+    if (t[0] == 8) return n_tiles * Geo<2, 8, 8, 1>::JTOT;
+    return n_tiles * (t[1] == 16 ? Geo<2, 32, 16, 1>::JTOT : Geo<2, 32, 32, 1>::JTOT);
 }
 
 template <int DIM, int TX, int TY, int TZ>
