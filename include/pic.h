@@ -156,7 +156,7 @@ typedef struct pic_batch pic_batch;
    interior x = 0 of every row starts a 128-byte line).  Particle arrays are dense, one
    element per slot. */
 typedef struct pic_box_layout_info {
-    int64_t workspace_bytes;    /* the workspace block (sort buffers, tile offsets, counters,
+    int64_t workspace_bytes;    /* the workspace block (sort buffers, tile offsets and sums, counters,
                                    reductions, reinjection table, the unfused record with
                                    PIC_BOX_UNFUSED) */
     int32_t field_sets;         /* field sets: 3 for the shearing box (F^n and the fixed-point

@@ -142,7 +142,7 @@ struct pic_box {
     float* mj = nullptr;
     uint32_t* err = nullptr;
     unsigned long long* ctr = nullptr;
-    uint32_t* conv = nullptr;  // shearing box: convergence record of the tolerance-mode sweeps
+    uint32_t* conv = nullptr;  // shearing box with a tolerance: convergence record of the sweeps
     int last_sweeps = 0;       // sweeps of the last Maxwell step (-1: the device record has it)
     unsigned long long* tsum = nullptr;  // split tiles: sums of their parts ...
     uint32_t* tdone = nullptr;           // ... and parts done
@@ -1566,7 +1566,7 @@ int32_t alloc_all(pic_box* b, const pic_box_mem* m)
     }
     if (!r) r = dalloc(b, b->err, 4);
     if (!r) r = dalloc(b, b->ctr, 4);
-    if (!r && sheared(d)) r = dalloc(b, b->conv, kKsbConvWords);
+    if (!r && sheared(d) && d->maxwell_tol > 0.0) r = dalloc(b, b->conv, kKsbConvWords);
     if (!r && split_ws > 0) r = dalloc(b, b->tsum, (size_t)split_ws);
     if (!r && split_ws > 0) r = dalloc(b, b->tdone, (size_t)tiles_ws);
     if (!r) r = dalloc(b, b->red_part, (size_t)(6 + kPartSums * kMaxSpecies) * kRedBlocks);

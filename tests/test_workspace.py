@@ -1,0 +1,29 @@
+"""What the workspace of a box holds (pic_workspace_bytes, host only): the sweeps' convergence record only with a
+tolerance, the sums of split tiles only in boxes of few tiles."""
+import pytest
+
+from paper_2602_15939_amd import _lib as L
+from paper_2602_15939_amd.box import describe
+
+
+def bytes_of(dim, n, frame=L.FRAME_SHEAR, **kw):
+    return L.pic_workspace_bytes(describe(dim, n, frame=frame, species=((-1.0, -1e-3, 1000),), shear_s=1.5,
+                                          shear_omega0=1e-4, **kw))
+
+
+@pytest.mark.parametrize("frame", [L.FRAME_SHEAR, L.FRAME_SHEAR_EXPAND])
+def test_convergence_record_only_with_a_tolerance(frame):
+    record = bytes_of(3, (32, 32, 32), frame, maxwell_tol=1e-6) - bytes_of(3, (32, 32, 32), frame)
+    assert 64 * 2048 <= record <= 64 * 2048 + 512  # 64 sweeps of 16 places of 128 bytes, and the sweep count
+    assert bytes_of(3, (32, 32, 32), L.FRAME_PLAIN, maxwell_tol=0.0) > 0
+
+
+@pytest.mark.parametrize("dim,few,many,extra", [
+    # 8^3 tiles: 511 and 512; 4^3 tiles are 8 times as many (11 x 11 (10 + 9) + ... words a tile of 8^3)
+    (3, (8, 8, 8 * 511), (8, 8, 8 * 512), 511 * 8 * 3861),
+    # 32 x 32 tiles: 1023 and 1024
+    (2, (32, 32 * 1023), (32, 32 * 1024), 1023 * 8 * 3640),
+])
+def test_split_sums_only_with_few_tiles(dim, few, many, extra):
+    a, b = (bytes_of(dim, n, L.FRAME_PLAIN) for n in (few, many))
+    assert 0.9 * extra <= a - b <= 1.01 * extra  # b: a larger box's tile arrays, but no sums
