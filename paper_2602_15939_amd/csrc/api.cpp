@@ -723,7 +723,7 @@ int32_t maxwell_box(pic_box* b)
         const bool tol = b->d.maxwell_tol > 0.0;
         // combined frame: the sweeps run on the expanding-frame fields (l/l_c) F_c, converted
         // from F^n at t^n here and back at t^{n+1} after the last sweep, with the curl factors
-        // l_c^2/l and kz = (l_y/l_z)^2 at t^{n+1/2}; one-thread-per-cell sweeps only
+        // l_c^2/l and kz = (l_y/l_z)^2 at t^{n+1/2}; no staged sweeps, no passes
         const bool comb = b->d.frame == PIC_FRAME_SHEAR_EXPAND;
         float back[3] = {1.f, 1.f, 1.f}, dfac[3] = {1.f, 1.f, 1.f}, kz = 1.f;
         if (comb) {
@@ -776,7 +776,7 @@ int32_t maxwell_box(pic_box* b)
                 Kd.y1_w = (float)(dys1 - fl);
                 if ((pairs ? ksb_pair(Kd, k == 0, st) : ksb_pass(Kd, k == 0, st)) != hipSuccess) return PIC_EDEVICE;
                 k++;
-            } else if ((staged ? ksb_sweep(Kd, k == 0, st) : ksb_sweep_unstaged(Kd, k == 0, st)) != hipSuccess) {
+            } else if ((staged ? ksb_sweep_staged(Kd, k == 0, st) : ksb_sweep(Kd, k == 0, st)) != hipSuccess) {
                 return PIC_EDEVICE;
             }
             if (tol && k == K - 1 && ksb_finalize(ksb_fin(b, K, so), st) != hipSuccess)

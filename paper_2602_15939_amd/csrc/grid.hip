@@ -1594,34 +1594,28 @@ bool ksb_pass_fits(const GridDev& G)
 
 // Planes per workgroup of the staged kernels and the workgroups of a launch over `columns` column
 // tiles: `most` planes on grids that fill the chip with them (two workgroups a CU), fewer on smaller
-// ones, down to 4 (a chunk reads two planes, a pass four, beyond its own).  On
-// 128 x 64 x 64 cells chunks of 64 planes are 16 workgroups: a staged sweep took 61 us, in chunks of 4 15 us.
+// ones (a chunk reads two planes, a pass four, beyond its own); on the grids of more than kStagedCells a
+// staged sweep is down to 8 planes, a pass to 16.  A step of 8 sweeps, us, so / in chunks of 64: 128 x 255 x 97
+// passes 465 / 630, single sweeps 616 / 1110; 256 x 128 x 128 464 / 605 and 606 / 1187; 256 x 256 x 128 871 / 872 and 1100 / 1351.
 static unsigned z_chunks(int columns, int nz, int most, int& zc)
 {
     zc = most;
-    while (zc > 4 && (int64_t)columns * ((nz + zc - 1) / zc) < 2 * 256) zc /= 2;
+    while (zc > 8 && (int64_t)columns * ((nz + zc - 1) / zc) < 2 * 256) zc /= 2;
     return (unsigned)(columns * ((nz + zc - 1) / zc));
 }
 
-hipError_t ksb_sweep(const KsbDev& K, bool first, hipStream_t st)
+hipError_t ksb_sweep_staged(const KsbDev& K, bool first, hipStream_t st)
 {
-    if (ksb_staged(K.G)) {
-        KsbDev Z = K;
-        const unsigned grid = z_chunks((K.G.n[0] / KX) * ((K.G.n[1] + KY - 1) / KY), K.G.n[2], KZ, Z.zc);
-        if (first)
-            ksb_sweep3_kernel<true><<<grid, KX * KY, 0, st>>>(Z);
-        else
-            ksb_sweep3_kernel<false><<<grid, KX * KY, 0, st>>>(Z);
-    } else {
-        const unsigned nb = nblocks((int64_t)K.G.n[0] * K.G.n[1] * K.G.n[2]);
-        if (first)
-            ksb_first_kernel<<<nb, kBlock, 0, st>>>(K);
-        else
-            ksb_next_kernel<<<nb, kBlock, 0, st>>>(K);
-    }
+    if (!ksb_staged(K.G) || K.expand) return hipErrorInvalidValue;
+    KsbDev Z = K;
+    const unsigned grid = z_chunks((K.G.n[0] / KX) * ((K.G.n[1] + KY - 1) / KY), K.G.n[2], KZ, Z.zc);
+    if (first)
+        ksb_sweep3_kernel<true><<<grid, KX * KY, 0, st>>>(Z);
+    else
+        ksb_sweep3_kernel<false><<<grid, KX * KY, 0, st>>>(Z);
     return hipGetLastError();
 }
-hipError_t ksb_sweep_unstaged(const KsbDev& K, bool first, hipStream_t st)
+hipError_t ksb_sweep(const KsbDev& K, bool first, hipStream_t st)
 {
     const unsigned nb = nblocks((int64_t)K.G.n[0] * K.G.n[1] * K.G.n[2]);
     if (first)
@@ -1635,7 +1629,7 @@ hipError_t ksb_sweep_unstaged(const KsbDev& K, bool first, hipStream_t st)
 // tile computes 2.8 positions a cell, and many tiles share a CU).
 bool ksb_pairs(const GridDev& G)
 {
-    return G.n[0] >= 2 && (int64_t)G.n[0] * G.n[1] * G.n[2] <= (G.dim == 2 ? 1ll << 20 : 1ll << 15);
+    return (int64_t)G.n[0] * G.n[1] * G.n[2] <= (G.dim == 2 ? 1ll << 20 : 1ll << 15);
 }
 unsigned ksb_pair_blocks(const GridDev& G)
 {

@@ -247,18 +247,20 @@ __device__ inline int unit_of(const UnitMap& m, int b)  // the unit owning block
     }
     return __builtin_amdgcn_readfirstlane(lo);  // uniform: descriptor loads stay scalar
 }
-// name##_kernel(Args): one unit, arguments by value; name##_batch(table, map): many units.
-#define PIC_BATCHED_KERNEL(name, Args, NT)                                                       \
-    __global__ __launch_bounds__(NT) void name##_kernel(Args a)                                  \
-    {                                                                                            \
-        name##_body(a, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y);                        \
-    }                                                                                            \
+// name##_kernel(Args): one unit, arguments by value; name##_batch(table, map): many units (PIC_BATCH_KERNEL: these alone).
+#define PIC_BATCH_KERNEL(name, Args, NT)                                                         \
     __global__ __launch_bounds__(NT) void name##_batch(const Args* __restrict__ t, UnitMap m)   \
     {                                                                                            \
         const int u = unit_of(m, (int)blockIdx.x);                                               \
         name##_body(t[u], (int)blockIdx.x - (int)m.prefix[u], (int)(m.prefix[u + 1] - m.prefix[u]), \
                     (int)blockIdx.y);                                                            \
     }
+#define PIC_BATCHED_KERNEL(name, Args, NT)                                                       \
+    __global__ __launch_bounds__(NT) void name##_kernel(Args a)                                  \
+    {                                                                                            \
+        name##_body(a, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y);                        \
+    }                                                                                            \
+    PIC_BATCH_KERNEL(name, Args, NT)
 
 // Geometry of a guarded grid array.
 // Division of 32-bit unsigned integers by an invariant divisor d >= 1 (Granlund and Montgomery,
@@ -370,7 +372,7 @@ struct KsbDev {
     int y1_int;
     float y1_w;
     int zc;  // planes per workgroup of the staged kernels (set by their launchers)
-    // combined shearing and expanding frame (one-thread-per-cell sweeps only): the iterates are
+    // combined shearing and expanding frame (sweeps of one thread per cell, one or two a launch): the iterates are
     // the expanding-frame fields, the curls act on dfac[c] F_c and kz multiplies the z
     // transport of E'_y in dE'_z/dt
     int expand;
@@ -501,18 +503,18 @@ hipError_t fold_current(const GridDev& G, float* const* J, float* const* out, in
                         double sO, double dt, double dys_half, hipStream_t st);
 hipError_t yee_b(const MaxwellDev& M, hipStream_t st);
 hipError_t yee_e(const MaxwellDev& M, hipStream_t st);
-// one sweep; large 3D grids whose x size is a multiple of the staged kernel's column tile (128) take
-// the staged kernel, others one thread per cell; both read cells beyond the faces at their images
+// one sweep, one thread per cell: any grid, any sheared frame; the cells beyond the faces are read at their images
+// (as by the kernels below)
+hipError_t ksb_sweep(const KsbDev& K, bool first, hipStream_t st);
+// the staged sweep: large 3D grids whose x size is a multiple of its column tile (128), the shearing box
 bool ksb_staged(const GridDev& G);
-// two sweeps per launch (fixed sweep count, K.y1_*): small grids of any shape
+hipError_t ksb_sweep_staged(const KsbDev& K, bool first, hipStream_t st);
+// two sweeps per launch (fixed sweep count, K.y1_*): small grids of any shape, any sheared frame
 bool ksb_pairs(const GridDev& G);
 unsigned ksb_pair_blocks(const GridDev& G);
 hipError_t ksb_pair(const KsbDev& K, bool first, hipStream_t st);
 // the two-sweep pass applies: a large grid whose arrays span less than 4 GiB (32-bit offsets)
 bool ksb_pass_fits(const GridDev& G);
-hipError_t ksb_sweep(const KsbDev& K, bool first, hipStream_t st);
-// the one-thread-per-cell sweep on any grid
-hipError_t ksb_sweep_unstaged(const KsbDev& K, bool first, hipStream_t st);
 // two sweeps F^k -> F^{k+2} in one pass over memory (large 3D grids); first: F^k = F^n,
 // the pass also writes C
 hipError_t ksb_pass(const KsbDev& K, bool first, hipStream_t st);

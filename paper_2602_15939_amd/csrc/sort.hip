@@ -378,7 +378,7 @@ __device__ __attribute__((always_inline)) inline void mig_offsets_body(const Mig
         a.dcnt[t] = dead;
     }
 }
-PIC_BATCHED_KERNEL(mig_offsets, MigArgs, kBlock)
+PIC_BATCH_KERNEL(mig_offsets, MigArgs, kBlock)
 
 // Exclusive scans of the arrivals and of the dead per tile, one workgroup each, 16 words a thread
 // and round.
@@ -416,7 +416,7 @@ __device__ __attribute__((always_inline)) inline void mig_scan_body(const MigArg
         __syncthreads();
     }
 }
-PIC_BATCHED_KERNEL(mig_scan, MigArgs, kScanBlock)
+PIC_BATCH_KERNEL(mig_scan, MigArgs, kScanBlock)
 
 // The whole sort by one workgroup (a particle was found beyond the neighbouring tiles): stable LSD
 // radix passes over (key, slot), 8 bits each, as the general sort does with many workgroups.
@@ -665,7 +665,7 @@ __device__ __attribute__((always_inline)) inline void mig_scatter_body(const Mig
         p ^= 1;
     }
 }
-PIC_BATCHED_KERNEL(mig_scatter, MigArgs, kBlock)
+PIC_BATCH_KERNEL(mig_scatter, MigArgs, kBlock)
 
 // the species of one box side by side
 #define PIC_PAIR_KERNEL(name, NT)                                            \
