@@ -55,8 +55,9 @@ enum pic_frame { PIC_FRAME_PLAIN = 0, PIC_FRAME_SHEAR = 1, PIC_FRAME_EXPAND = 2,
    positions move by dt L^-1 u'/gamma' plus the shear move, and the field step is the implicit
    midpoint of Sec. 2.2 on the expanding-frame fields (l/l_c) F_c with the (1/l) L^2 curl factors
    of eqs. EBB/EBE.  x and y scale together: expand_axis_mask 0, 4 (z), 3 (xy) or 7; other masks
-   are PIC_EINVAL.  The field step takes the one-thread-per-cell sweeps (also in a batched
-   step, where the conversions to and from the expanding-frame fields are batched launches). */
+   are PIC_EINVAL.  The field step takes sweeps of one thread per cell, two a launch on small
+   grids (also in a batched step, where the conversions to and from the expanding-frame fields are
+   batched launches). */
 enum pic_leaky_mode { PIC_LEAKY_DISPLACEMENT = 0, PIC_LEAKY_PROBABILISTIC = 1 };
 
 /* pic_gather_push flags */
@@ -319,9 +320,10 @@ int32_t pic_tile_candidates(int32_t dim, uint32_t flags, int32_t* shapes_out, in
 /* Tile counting sort (stable): key = tile of the particle's cell, dead particles go to a
    dead bin and are dropped.  Produces the permutation used by the next pic_gather_push and
    the per-tile offsets.  After a push the particles are still grouped by the tiles of the
-   previous sort and each moved less than a cell, so (in the shearing box with at least three
-   tiles in x and no last y tile of one row) the sort only counts moves to the neighbouring tiles;
-   a particle found farther away sends that sort to a radix sort on the device.
+   previous sort and each moved less than a cell, so the sort only counts moves to the
+   neighbouring tiles (in the shearing box with at least three tiles in x and no last y tile of one
+   row, in the other frames on any grid); a particle found farther away, where the caller moved it
+   in its memory between sort and push, sends that sort to a radix sort by one workgroup.
    Both give the same permutation.  PIC_ESTATE while an unfused push awaits pic_deposit. */
 int32_t pic_tile_sort(pic_box* const* boxes, int32_t nb, uint32_t flags);
 

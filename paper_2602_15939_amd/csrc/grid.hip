@@ -732,12 +732,12 @@ __device__ __attribute__((always_inline)) inline void ksb_pair_next_body(const K
 PIC_BATCHED_KERNEL(ksb_pair_first, KsbDev, kPairBlock)
 PIC_BATCHED_KERNEL(ksb_pair_next, KsbDev, kPairBlock)
 
-// 3D: a workgroup owns a KX x KY column tile and marches over a chunk of KZ planes; three
+// 3D: a workgroup owns a KX x KY column tile and marches over a chunk of at most KZ planes; three
 // consecutive planes of the iterate (tile plus a one-cell halo) sit in LDS.  Halo positions
 // outside the interior are read through the boundary maps of the guard fill (y, z periodic;
 // x shearing-periodic with the fractional shift interpolated along y, the same arithmetic), so
 // the iterates need no guard fill between sweeps (only the last one's guards are filled, for
-// the push).  128 x 4 columns of 64-plane chunks (512 threads, 56 KB of LDS, two workgroups
+// the push).  128 x 4 columns and chunks of 64 planes, which 256^3 cells still take (512 threads, 56 KB of LDS, two workgroups
 // per CU) measured fastest at 256^3 among 32..128 x 2..16 x 16..128 (8 % below 32 x 8 x 32).  The iterate written and C read once per sweep use
 // nontemporal (streaming) stores and loads: a sweep moves far more than the caches hold, and
 // the halo reads of the iterate, which neighbouring workgroups share, keep the normal policy
@@ -1501,9 +1501,10 @@ __global__ __launch_bounds__(kBlock) void box_record_kernel(SumArgs P, const dou
 
 // ------------------------------------------------------------------ host launchers
 static inline unsigned nblocks(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
-// grid of the grid-stride cell kernels (the shear fold, the Yee updates): 16 blocks per CU,
-// each thread taking a few cells, measured faster than one thread per cell (fold at 256^3:
-// 0.18 against 0.22 ms)
+// grid of the grid-stride cell kernels (the shear fold, the Yee updates, field copies): 16 blocks per CU, each
+// thread taking a few cells.  It was faster for a fold of one cell a thread; now, a thread per cell (fold: per
+// four rows) is as fast on 128 x 128 x 257 cells (fold 27.2 us, Yee step 98 us both ways) and slightly faster on
+// 256^3 (fold 95 against 100 us, Yee step 512 against 549 us).
 constexpr unsigned kStrideBlocks = 4096;
 
 FillArgs fill_args(const GridDev& G, float* const* comps, int ncomp, int shear, double dys)
@@ -1581,7 +1582,7 @@ hipError_t yee_e(const MaxwellDev& M, hipStream_t st)
 // Where the staged sweep and the pass over z, which march over planes that each wait for the one before,
 // win: on grids that the last-level cache does not hold.  us a step of 8 sweeps, passes / staged sweeps /
 // one thread a cell: 64^3 74 / 54 / 56, 128 x 64 x 64 99 / 146 / 74, 128^3 265 / 336 / 221,
-// 256 x 128 x 128 454 / 577 / 674, 256^3 1849 / 2117 / 2611; the line lies between the middle two.
+// 256 x 128 x 128 454 / 577 / 674, 256^3 1849 / 2117 / 2611; the line lies between 128^3 and 256 x 128 x 128.
 constexpr int64_t kStagedCells = 3ll << 20;
 bool ksb_staged(const GridDev& G)
 {

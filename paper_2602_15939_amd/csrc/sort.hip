@@ -419,7 +419,9 @@ __device__ __attribute__((always_inline)) inline void mig_scan_body(const MigArg
 PIC_BATCH_KERNEL(mig_scan, MigArgs, kScanBlock)
 
 // The whole sort by one workgroup (a particle was found beyond the neighbouring tiles): stable LSD
-// radix passes over (key, slot), 8 bits each, as the general sort does with many workgroups.
+// radix passes over (key, slot), 8 bits each, as the general sort does with many workgroups.  Only a caller
+// that moves particles in its memory between sort and push comes here; it saves every other step the gated
+// launches of the general sort, and costs that one 12 ms a million particles (two digits).
 __device__ __attribute__((always_inline)) inline void radix_alone(const MigArgs& a, uint32_t* lds)
 {
     uint32_t* const base = lds;  // 256 words, then 256 a wave, then one a wave
