@@ -18,6 +18,7 @@ The fused push kernel is timed with HIP events on the box stream for the rooflin
 from __future__ import annotations
 
 import argparse
+import gc
 import json
 import math
 import os
@@ -398,6 +399,10 @@ def measure(args, w):
     for _ in range(args.warmup):
         one_step()
     torch.cuda.synchronize()
+    # Python's first full garbage collection walks every object that the imports made, 35 ms once a process: as
+    # much as 400 steps of the parity box, in whichever of its timed loops it fell
+    gc.collect()
+    gc.freeze()
     print(f"[bench] warmup done, timing {args.steps} steps", file=sys.stderr, flush=True)
     evs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
            for _ in range(args.steps)]
