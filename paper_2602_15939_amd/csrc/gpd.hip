@@ -455,7 +455,7 @@ struct Geo {
 template <class G, int DIM>
 struct LdsAcc {
     char* J;
-    unsigned at;  // place in bytes of the particle's cell, counted from the tile's first
+    int at;  // place in bytes of the particle's cell, counted from the tile's first
     static constexpr int pitch(int a) { return 8 * (a == 0 ? 1 : (a == 1 ? G::JX : G::JX * G::JY)); }
     template <int C, int IX, int IY, int IZ>
     __device__ inline void add(int way, float v)
@@ -474,8 +474,8 @@ __device__ inline LdsAcc<G, DIM> lds_acc(unsigned long long* Jl, int rx, int ry,
 {
     using A = LdsAcc<G, DIM>;
     // 24-bit multiply-adds; region places are non-negative
-    return A{reinterpret_cast<char*>(Jl), 8u * (unsigned)rx + __umul24((unsigned)A::pitch(1), (unsigned)ry) +
-                                              (DIM == 3 ? __umul24((unsigned)A::pitch(2), (unsigned)rz) : 0u)};
+    return A{reinterpret_cast<char*>(Jl), (int)(8u * (unsigned)rx + __umul24((unsigned)A::pitch(1), (unsigned)ry) +
+                                                (DIM == 3 ? __umul24((unsigned)A::pitch(2), (unsigned)rz) : 0u))};
 }
 
 // Global accumulator on the guarded current arrays (slow path).
