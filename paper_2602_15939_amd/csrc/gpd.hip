@@ -638,9 +638,18 @@ __device__ inline void flush_current(unsigned long long* Jl, const StepDev& P, i
             *flag = __hip_atomic_fetch_add(&P.tdone[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == 1u << P.lsplit;
         __syncthreads();
         if (!*flag) return;
-        for (int e = tid; e < G::JTOT; e += NT) {  // its own entries below: no barrier
-            Jl[e] = __hip_atomic_load(&sum[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&sum[e], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        constexpr int N = (G::JTOT + NT - 1) / NT;  // all loads on their way before the first is used
+        unsigned long long v[N];
+        int t = tid;
+        asm volatile("" : "+v"(t));  // keeps the places out of the particle loop's registers
+#pragma unroll
+        for (int k = 0; k < N; k++)
+            v[k] = t + k * NT < G::JTOT ? __hip_atomic_load(&sum[t + k * NT], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+#pragma unroll
+        for (int k = 0; k < N; k++) {  // its own entries below: no barrier
+            if (t + k * NT >= G::JTOT) break;
+            Jl[t + k * NT] = v[k];
+            __hip_atomic_store(&sum[t + k * NT], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         if (tid == 0) __hip_atomic_store(&P.tdone[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
