@@ -396,13 +396,14 @@ def measure(args, w):
     if not args.serial_sort:
         L.pic_tile_sort(h)
 
+    # Python's first full garbage collection walks every object that the imports made, 35 ms once a process: as
+    # much as 400 steps of the parity box, in whichever of its timed loops it fell
+    # (before the warm-up: the first steps after a pause are slow)
+    gc.collect()
+    gc.freeze()
     for _ in range(args.warmup):
         one_step()
     torch.cuda.synchronize()
-    # Python's first full garbage collection walks every object that the imports made, 35 ms once a process: as
-    # much as 400 steps of the parity box, in whichever of its timed loops it fell
-    gc.collect()
-    gc.freeze()
     print(f"[bench] warmup done, timing {args.steps} steps", file=sys.stderr, flush=True)
     evs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
            for _ in range(args.steps)]
