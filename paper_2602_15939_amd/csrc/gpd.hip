@@ -1077,26 +1077,36 @@ constexpr int threads_for(int dim, int cells)
 
 // A tile's workgroup walks its particles a round of NT slots after another, each round waiting for
 // its loads (3 to 5 us), so a box of few tiles is bound by that chain on an idle chip.  Its tiles are
-// split until the launch has two (3D) or four (2D) workgroups a CU, as long as a part keeps a
-// whole round of a species: more parts only add their staging and flush (four parts a tile instead of
-// two made the 384^2 box's push slower, 75 -> 84 us).  The 64^2 box of the parity tests (16 tiles of 4096
-// slots a species): 84 us whole, 19 us in 256 workgroups; 20 x 12 x 16 cells: 32 -> 28 us.
-// Where the parts still leave the chip idle, one of two species each halves the chain again: 20 x 12 x 16
-// cells 21.2 -> 15.8 us, the 64^2 box 15.6 -> 12.4 us.
-static int64_t split_below(int dim) { return dim == 3 ? 512 : 1024; }
+// split as long as the launch has fewer workgroups than split_below, a tile more than a round of a species, and
+// the workgroups are all resident at once; beyond that only parts of more than sixteen rounds.  Where the
+// parts still leave the chip idle, one of two species each halves the chain again.  The push with its clears,
+// us, whole / split: 64^2 with 16 particles a cell and species 66 / 25 (tiles of 8 x 8 29 / 19), 20 x 12 x 16 with 4
+// 35 / 25, 24^3 with 8 52 / 29, 384^2 with 32 166 / 142; not resident at once: 48^3 with 8 60 / 86 (432 workgroups
+// 65), 512^2 with 32 in tiles of 32 x 32 210 / 259, but 56^3 with 32 291 / 257; the species apart: 20 x 12 x 16 31 -> 25.
+static int64_t split_below(int dim, const int t[3])  // 2 (3D, 32 x 16), 4 (to 16 x 16) or 1 (32 x 32) workgroups a CU
+{
+    const int cells = t[0] * t[1] * t[2];
+    return dim == 3 ? 512 : (cells <= 256 ? 1024 : 256 * (1024 / cells));
+}
 void split_tiles(StepDev& P, const int t[3], int64_t n_tiles, int64_t slots_per_tile)
 {
-    const int64_t want = split_below(P.dim), nt = threads_for(P.dim, t[0] * t[1] * t[2]);
+    const int cells = t[0] * t[1] * t[2];
+    const int64_t want = split_below(P.dim, t), nt = threads_for(P.dim, cells);
+    const int64_t resident = P.dim == 2 && cells <= 256 ? 7 * 256 : want;
     P.lsplit = 0;
-    while (P.lsplit < 6 && (n_tiles << P.lsplit) < want && (slots_per_tile >> P.lsplit) > nt) P.lsplit++;
-    P.by_species = P.nsp == 2 && (n_tiles << P.lsplit) < want ? 1 : 0;
+    auto more = [&] {
+        return (n_tiles << P.lsplit) < want &&
+               ((n_tiles << (P.lsplit + 1)) <= resident || (slots_per_tile >> P.lsplit) > 16 * nt);
+    };
+    while (P.lsplit < 6 && (slots_per_tile >> P.lsplit) > nt && more()) P.lsplit++;
+    P.by_species = P.nsp == 2 && more() ? 1 : 0;
     P.lsplit += P.by_species;
 }
 
 // words of P.tsum: a launch has at least the box's tiles, so a box of more is never split
 int64_t split_words(int dim, const int t[3], int64_t n_tiles)
 {
-    if (n_tiles >= split_below(dim)) return 0;
+    if (n_tiles >= split_below(dim, t)) return 0;
     if (dim == 3) return n_tiles * (t[0] == 8 ? Geo<3, 8, 8, 8>::JTOT : Geo<3, 4, 4, 4>::JTOT);
     if (t[0] == 16) return n_tiles * Geo<2, 16, 16, 1>::JTOT;
     if (t[0] == 8) return n_tiles * Geo<2, 8, 8, 1>::JTOT;
