@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cmath>
 #include <cstring>
@@ -144,8 +145,7 @@ struct pic_box {
     unsigned long long* ctr = nullptr;
     uint32_t* conv = nullptr;  // shearing box with a tolerance: convergence record of the sweeps
     int last_sweeps = 0;       // sweeps of the last Maxwell step (-1: the device record has it)
-    unsigned long long* tsum = nullptr;  // split tiles: sums of their parts ...
-    uint32_t* tdone = nullptr;           // ... and parts done
+    unsigned long long* tsum = nullptr;  // split tiles: the sums of their parts
     double* red_part = nullptr;
     BoxRecord* record = nullptr;
     double* hist_edges = nullptr;               // energy histogram: edges ...
@@ -323,6 +323,7 @@ void build_mj_table(double theta, std::vector<float>& out)
 void set_migration_shift(pic_box* b, int dys_int);
 
 int64_t slots_per_tile(const pic_box* b);
+int64_t whole_tiles(const pic_box* b);
 
 StepDev make_step(pic_box* b)
 {
@@ -361,9 +362,8 @@ StepDev make_step(pic_box* b)
     P.count_mig = b->mig_ok ? 1 : 0;
     P.mig_latch = 0;
     P.nsp = b->nsp;
-    split_tiles(P, b->tile, b->tl.n_tiles, slots_per_tile(b));
+    split_tiles(P, b->tile, b->tl.n_tiles, whole_tiles(b), slots_per_tile(b));
     P.tsum = b->tsum;
-    P.tdone = b->tdone;
     P.mg = b->mg;
     for (int s = 0; s < b->nsp; s++) {
         P.mcnt[s] = b->sp[s].sb.mcnt;
@@ -559,6 +559,13 @@ void set_migration_shift(pic_box* b, int dys_int)
     auto wrap = [&](int v) { return ((v % b->n[1]) + b->n[1]) % b->n[1]; };
     b->mg.first[1] = wrap(dys_int - 1);
     b->mg.first[0] = wrap(-dys_int - 2);
+}
+
+// the box's cells in tiles of the full size
+int64_t whole_tiles(const pic_box* b)
+{
+    const int64_t cells = (int64_t)b->n[0] * b->n[1] * b->n[2], t = (int64_t)b->tile[0] * b->tile[1] * b->tile[2];
+    return (cells + t - 1) / t;
 }
 
 // slots per tile of the fuller species, on average
@@ -1053,11 +1060,15 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
         std::vector<ZeroArgs> z;
         std::vector<uint32_t> zb;
         std::map<std::tuple<int, int, int, int, int>, std::pair<std::vector<StepDev>, std::vector<uint32_t>>> groups;
-        std::map<std::tuple<int, int, int, int, int>, int64_t> group_tiles;  // tiles of each launch
+        std::map<std::tuple<int, int, int, int, int>, std::array<int64_t, 2>> group_tiles;  // tiles of each launch; by cells
         auto group_of = [](const pic_box* b) {
             return std::make_tuple(b->dim, b->tile[0], b->tile[1], b->tile[2], b->d.frame);
         };
-        for (int i = 0; i < nb; i++) group_tiles[group_of(boxes[i])] += boxes[i]->tl.n_tiles;
+        for (int i = 0; i < nb; i++) {
+            auto& g = group_tiles[group_of(boxes[i])];
+            g[0] += boxes[i]->tl.n_tiles;
+            g[1] += whole_tiles(boxes[i]);
+        }
         for (int i = 0; i < nb; i++) {
             pic_box* b = boxes[i];
             for (int c = 0; c < 3; c++) {
@@ -1067,7 +1078,8 @@ int32_t step_batched(pic_box* const* boxes, int nb, bool graph, Stager& sg_all, 
             auto& gr = groups[group_of(b)];
             StepDev P = make_step(b);
             P.mig_latch = 1;
-            split_tiles(P, b->tile, group_tiles[group_of(b)], slots_per_tile(b));
+            const auto& gt = group_tiles[group_of(b)];
+            split_tiles(P, b->tile, gt[0], gt[1], slots_per_tile(b));
             gr.first.push_back(P);
             gr.second.push_back((uint32_t)b->tl.n_tiles << P.lsplit);
             for (int s = 0; s < b->nsp; s++) {
@@ -1568,7 +1580,6 @@ int32_t alloc_all(pic_box* b, const pic_box_mem* m)
     if (!r) r = dalloc(b, b->ctr, 4);
     if (!r && sheared(d) && d->maxwell_tol > 0.0) r = dalloc(b, b->conv, kKsbConvWords);
     if (!r && split_ws > 0) r = dalloc(b, b->tsum, (size_t)split_ws);
-    if (!r && split_ws > 0) r = dalloc(b, b->tdone, (size_t)tiles_ws);
     if (!r) r = dalloc(b, b->red_part, (size_t)(6 + kPartSums * kMaxSpecies) * kRedBlocks);
     if (!r) r = dalloc(b, b->record, 1);
     if (!r) r = dalloc(b, b->hist_edges, kHistMaxBins + 1);
@@ -1578,8 +1589,7 @@ int32_t alloc_all(pic_box* b, const pic_box_mem* m)
     if (measuring || r) return r;
     if (hipMemsetAsync(b->err, 0, 4 * sizeof(uint32_t), b->st) != hipSuccess) return PIC_EDEVICE;
     if (hipMemsetAsync(b->ctr, 0, 4 * sizeof(unsigned long long), b->st) != hipSuccess) return PIC_EDEVICE;
-    if (split_ws > 0 && (hipMemsetAsync(b->tsum, 0, (size_t)split_ws * sizeof(unsigned long long), b->st) != hipSuccess ||
-                         hipMemsetAsync(b->tdone, 0, (size_t)tiles_ws * sizeof(uint32_t), b->st) != hipSuccess))
+    if (split_ws > 0 && hipMemsetAsync(b->tsum, 0, (size_t)split_ws * sizeof(unsigned long long), b->st) != hipSuccess)
         return PIC_EDEVICE;
     if (b->conv && hipMemsetAsync(b->conv, 0, kKsbConvWords * sizeof(uint32_t), b->st) != hipSuccess)
         return PIC_EDEVICE;

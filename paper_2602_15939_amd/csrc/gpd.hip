@@ -442,6 +442,8 @@ struct Geo {
     static constexpr int jsize(int c) { return JX * (JY * (jdim(c, 2) - 1) + jdim(c, 1)); }
     static constexpr int joff(int c) { return c == 0 ? 0 : joff(c - 1) + jsize(c - 1); }
     static constexpr int JTOT = joff(2) + jsize(2);
+    // words per tile of P.tsum: its sums, and in a line of its own the count of the parts that are done
+    static constexpr int JSPLIT = (JTOT + 15) / 16 * 16 + 16;
     static constexpr int FTOT = foff(5) + fsize(5);
     static constexpr int FBYTES = (8 * FTOT + 15) & ~15;   // E, B first, then J (8-byte words)
     static constexpr int LDS_BYTES = FBYTES + 8 * JTOT;
@@ -620,22 +622,24 @@ __device__ inline float fixed_to_float(unsigned long long a, float unit)
 // the whole sum: exact and converted once, however the tile was split.  It leaves words and count at zero
 // for the next launch; nobody waits.  The parts meet in device-scope atomics alone, so each needs only its
 // own to be done before it counts itself; __threadfence() would write back and invalidate the L2 for every
-// part (a step of the 64^2 box 115 us, an unfused one of the 384^2 box 333 us; 90 and 145 us this way).  Parts
-// that rounded to FP32 each and met in the current's atomics took 83 and 140 us, but put the rounding of their
-// gross sums and the order of the additions into every node.
+// part (a step of the 64^2 box 115 us, an unfused one of the 384^2 box 333 us; 87 and 144 us this way), and
+// counts of several tiles in one line made the parts queue for it (90 us).  Parts that rounded to FP32 each and
+// met in the current's atomics took 83 and 140 us, but put the rounding of their gross sums and the order of the
+// additions into every node.
 // flag: a shared word that nothing else uses any more.
 template <class G, int DIM, int NT>
 __device__ inline void flush_current(unsigned long long* Jl, const StepDev& P, int tile,
                                      const int t0[3], const int ext[3], int tid, uint32_t* flag)
 {
     if (P.lsplit) {
-        unsigned long long* const sum = P.tsum + (size_t)tile * G::JTOT;
+        unsigned long long* const sum = P.tsum + (size_t)tile * G::JSPLIT;
+        uint32_t* const done = reinterpret_cast<uint32_t*>(sum + G::JSPLIT - 16);
         for (int e = tid; e < G::JTOT; e += NT)
             if (Jl[e]) __hip_atomic_fetch_add(&sum[e], Jl[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid == 0)
-            *flag = __hip_atomic_fetch_add(&P.tdone[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == 1u << P.lsplit;
+            *flag = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == 1u << P.lsplit;
         __syncthreads();
         if (!*flag) return;
         constexpr int N = (G::JTOT + NT - 1) / NT;  // all loads on their way before the first is used
@@ -651,7 +655,7 @@ __device__ inline void flush_current(unsigned long long* Jl, const StepDev& P, i
             Jl[t + k * NT] = v[k];
             __hip_atomic_store(&sum[t + k * NT], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        if (tid == 0) __hip_atomic_store(&P.tdone[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     for (int e = tid; e < G::JTOT; e += NT) {
         const unsigned long long a = Jl[e];
@@ -1078,9 +1082,10 @@ constexpr int threads_for(int dim, int cells)
 // A tile's workgroup walks its particles a round of NT slots after another, each round waiting for
 // its loads (3 to 5 us), so a box of few tiles is bound by that chain on an idle chip.  Its tiles are
 // split as long as the launch has fewer workgroups than split_below, a tile more than a round of a species, and
-// the workgroups are all resident at once; beyond that only parts of more than sixteen rounds.  Where the
+// the workgroups are all resident at once (ragged tiles counted by their cells: a step of 17 x 199 x 14 cells, 150
+// tiles, takes 210 us in 600 workgroups and 232 in 300); beyond that only parts of more than sixteen rounds.  Where the
 // parts still leave the chip idle, one of two species each halves the chain again.  The push with its clears,
-// us, whole / split: 64^2 with 16 particles a cell and species 66 / 25 (tiles of 8 x 8 29 / 19), 20 x 12 x 16 with 4
+// us, whole / split: 64^2 with 16 particles a cell and species 66 / 21 (tiles of 8 x 8 29 / 19), 20 x 12 x 16 with 4
 // 35 / 25, 24^3 with 8 52 / 29, 384^2 with 32 166 / 142; not resident at once: 48^3 with 8 60 / 86 (432 workgroups
 // 65), 512^2 with 32 in tiles of 32 x 32 210 / 259, but 56^3 with 32 291 / 257; the species apart: 20 x 12 x 16 31 -> 25.
 static int64_t split_below(int dim, const int t[3])  // 2 (3D, 32 x 16), 4 (to 16 x 16) or 1 (32 x 32) workgroups a CU
@@ -1088,7 +1093,7 @@ static int64_t split_below(int dim, const int t[3])  // 2 (3D, 32 x 16), 4 (to 1
     const int cells = t[0] * t[1] * t[2];
     return dim == 3 ? 512 : (cells <= 256 ? 1024 : 256 * (1024 / cells));
 }
-void split_tiles(StepDev& P, const int t[3], int64_t n_tiles, int64_t slots_per_tile)
+void split_tiles(StepDev& P, const int t[3], int64_t n_tiles, int64_t whole_tiles, int64_t slots_per_tile)
 {
     const int cells = t[0] * t[1] * t[2];
     const int64_t want = split_below(P.dim, t), nt = threads_for(P.dim, cells);
@@ -1096,7 +1101,7 @@ void split_tiles(StepDev& P, const int t[3], int64_t n_tiles, int64_t slots_per_
     P.lsplit = 0;
     auto more = [&] {
         return (n_tiles << P.lsplit) < want &&
-               ((n_tiles << (P.lsplit + 1)) <= resident || (slots_per_tile >> P.lsplit) > 16 * nt);
+               ((whole_tiles << (P.lsplit + 1)) <= resident || (slots_per_tile >> P.lsplit) > 16 * nt);
     };
     while (P.lsplit < 6 && (slots_per_tile >> P.lsplit) > nt && more()) P.lsplit++;
     P.by_species = P.nsp == 2 && more() ? 1 : 0;
@@ -1107,10 +1112,10 @@ void split_tiles(StepDev& P, const int t[3], int64_t n_tiles, int64_t slots_per_
 int64_t split_words(int dim, const int t[3], int64_t n_tiles)
 {
     if (n_tiles >= split_below(dim, t)) return 0;
-    if (dim == 3) return n_tiles * (t[0] == 8 ? Geo<3, 8, 8, 8>::JTOT : Geo<3, 4, 4, 4>::JTOT);
-    if (t[0] == 16) return n_tiles * Geo<2, 16, 16, 1>::JTOT;
-    if (t[0] == 8) return n_tiles * Geo<2, 8, 8, 1>::JTOT;
-    return n_tiles * (t[1] == 16 ? Geo<2, 32, 16, 1>::JTOT : Geo<2, 32, 32, 1>::JTOT);
+    if (dim == 3) return n_tiles * (t[0] == 8 ? Geo<3, 8, 8, 8>::JSPLIT : Geo<3, 4, 4, 4>::JSPLIT);
+    if (t[0] == 16) return n_tiles * Geo<2, 16, 16, 1>::JSPLIT;
+    if (t[0] == 8) return n_tiles * Geo<2, 8, 8, 1>::JSPLIT;
+    return n_tiles * (t[1] == 16 ? Geo<2, 32, 16, 1>::JSPLIT : Geo<2, 32, 32, 1>::JSPLIT);
 }
 
 template <int DIM, int TX, int TY, int TZ>

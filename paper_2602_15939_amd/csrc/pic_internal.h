@@ -177,9 +177,9 @@ struct StepDev {
     // a tile is shared out to 2^lsplit workgroups: by_species, the lowest bit names one of two species,
     // and part p of the others takes every 2^(lsplit - by_species)-th round of a species' slots
     int lsplit, by_species;
-    // split tiles: the integer sums of each tile's parts (split_words) and the parts done, zero between launches
+    // split tiles: the integer sums of each tile's parts and the count of those done (split_words), zero between
+    // launches
     unsigned long long* tsum;
-    uint32_t* tdone;
     // migration counts of the next sort, taken by the push: per species and source tile
     // (= this launch's tile), the particles per direction (mcnt[tile * kMigDirs + d], added to the
     // cleared counts by the parts of a split tile); a
@@ -442,8 +442,8 @@ struct MigPair {
 // ---- launchers (gpd.hip, sort.hip, grid.hip, xfer.hip)
 bool tile_shape_supported(int dim, const int t[3]);
 // share the tiles of a push or deposit out to workgroups (lsplit, by_species): n_tiles tiles in the launch
-// (of all its boxes), slots_per_tile slots of the fuller species a tile on average in this one
-void split_tiles(StepDev& P, const int t[3], int64_t n_tiles, int64_t slots_per_tile);
+// (of all its boxes), whole_tiles tiles' worth of cells, slots_per_tile slots of the fuller species a tile on average in this one
+void split_tiles(StepDev& P, const int t[3], int64_t n_tiles, int64_t whole_tiles, int64_t slots_per_tile);
 // 64-bit words that the parts' sums need for a box of n_tiles tiles
 int64_t split_words(int dim, const int t[3], int64_t n_tiles);
 // supported tile shapes (batched: those of the batched launch); the default shape comes first

@@ -19,10 +19,10 @@ def test_convergence_record_only_with_a_tolerance(frame):
 
 
 @pytest.mark.parametrize("dim,few,many,extra", [
-    # 8^3 tiles: 511 and 512; 4^3 tiles are 8 times as many (11 x 11 (10 + 9) + ... words a tile of 8^3)
-    (3, (8, 8, 8 * 511), (8, 8, 8 * 512), 511 * 8 * 3861),
-    # 16 x 16 tiles: 1020 and 1024 (19 (19 + 18 + 19) words a tile); 32 x 32 tiles: 255 and 256
-    (2, (32, 32 * 255), (32, 32 * 256), 1020 * 8 * 1064),
+    # 8^3 tiles: 511 and 512 (3861 sums a tile, in whole lines, and a line for its count)
+    (3, (8, 8, 8 * 511), (8, 8, 8 * 512), 511 * 8 * 3888),
+    # 16 x 16 tiles: 1020 and 1024 (1064 sums); 32 x 32 tiles: 255 and 256
+    (2, (32, 32 * 255), (32, 32 * 256), 1020 * 8 * 1088),
 ])
 def test_split_sums_only_with_few_tiles(dim, few, many, extra):
     a, b = (bytes_of(dim, n, L.FRAME_PLAIN) for n in (few, many))
