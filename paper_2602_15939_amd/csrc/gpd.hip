@@ -1081,7 +1081,8 @@ constexpr int threads_for(int dim, int cells)
 
 // A tile's workgroup walks its particles a round of NT slots after another, each round waiting for
 // its loads (3 to 5 us), so a box of few tiles is bound by that chain on an idle chip.  Its tiles are
-// split as long as the launch has fewer workgroups than split_below, a tile more than a round of a species, and
+// split as long as the launch has fewer workgroups than split_below, a part more than a round of a species (four
+// from a workgroup a CU on: 320^2 with 4 particles a cell and species takes 31.5 us so and 35.0 in parts of one), and
 // the workgroups are all resident at once (ragged tiles counted by their cells: a step of 17 x 199 x 14 cells, 150
 // tiles, takes 210 us in 600 workgroups and 232 in 300); beyond that only parts of more than sixteen rounds.  Where the
 // parts still leave the chip idle, one of two species each halves the chain again.  The push with its clears,
@@ -1103,7 +1104,8 @@ void split_tiles(StepDev& P, const int t[3], int64_t n_tiles, int64_t whole_tile
         return (n_tiles << P.lsplit) < want &&
                ((whole_tiles << (P.lsplit + 1)) <= resident || (slots_per_tile >> P.lsplit) > 16 * nt);
     };
-    while (P.lsplit < 6 && (slots_per_tile >> P.lsplit) > nt && more()) P.lsplit++;
+    auto rounds = [&] { return (n_tiles << P.lsplit) < 256 ? 1 : 4; };
+    while (P.lsplit < 6 && (slots_per_tile >> P.lsplit) > rounds() * nt && more()) P.lsplit++;
     P.by_species = P.nsp == 2 && more() ? 1 : 0;
     P.lsplit += P.by_species;
 }
