@@ -700,7 +700,7 @@ size_t migrate_scratch_words(int n_tiles) { return scan_scratch_words((int64_t)n
 // The scans take one workgroup each up to this many tiles, twelve launches (three for each of two scans and
 // species) beyond.  The whole sort of two sparse species on 8 x 8 tiles, us, one workgroup / launches: 4096 tiles
 // 40 / 84, 16384 118 / 160, 32761 220 / 251, 65536 430 / 432, 90000 586 / 565, 160000 1028 / 947; beside the
-// Maxwell step of the 256^3 shearing box (32768 tiles) and the 2048^2 leaky box (16384) 1 and 3 % of a step.
+// Maxwell step of the 256^3 shearing box (32768 tiles) and the 2048^2 leaky box (16384) a step takes as long either way.
 constexpr int kScanAlone = 1 << 16;
 
 hipError_t migrate_sort(const MigPair& a, int n_species, uint32_t* const* scratch, hipStream_t st)
