@@ -244,7 +244,8 @@ __device__ inline Shape shape(float o, float D)
     A.l = 1.f - o;
     A.u = o;
     const bool up = o >= 0.5f;  // s lies below c; 1 - o is exact then
-    const float x0 = up ? -A.l : fabsf(o), x1 = x0 + D;  // an offset of -0 has c = L and s = U as one of 0
+    // by the magnitudes, so that an offset of -0, or rounded a unit beyond 0 or 1, has s on the side of one within
+    const float x0 = up ? -fabsf(A.l) : fabsf(o), x1 = x0 + D;
     const uint32_t sign = __float_as_uint(x0) & 0x80000000u;
     const float t = flip(x1, sign);  // the new position counted towards s
     const float s0 = fabsf(x0), c0 = 1.f - s0;

@@ -1,6 +1,7 @@
-"""An in-cell offset of zero with either sign: a particle at -0.0 (what a subtraction or a remainder of negative
+"""In-cell offsets at the ends of a cell.  Of zero with either sign: a particle at -0.0 (what a subtraction or a remainder of negative
 zeros leaves in a caller's arrays) deposits the current of the one at +0.0, in every direction of motion on every
-axis, fused and not."""
+axis, fused and not.  Of one, or a rounding unit beyond either end (what an FP32 fraction of a position can come to):
+the current of the place that cell and offset name."""
 import itertools
 
 import numpy as np
@@ -43,4 +44,14 @@ def test_negative_zero_offset_deposits_as_zero(dim, fuse):
     assert np.abs(ref).max() > 0
     # one weight or displacement is a few units of 2^-24 off, a current that times q/dt
     assert np.abs(Jn - ref).max() <= 1e-6 * 1e-4 / 0.45
+    assert np.abs(J - ref).max() <= 1e-6 * 1e-4 / 0.45
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("off", [1.0, 1.0 + 2.0 ** -23, -(2.0 ** -24)])
+def test_offset_at_or_a_unit_beyond_the_end(dim, off):
+    n = (12,) * dim
+    combos = list(zip(itertools.product(range(3), repeat=dim), itertools.product((0.9, 0.0, -0.9), repeat=dim)))
+    J, ref = current(dim, n, off, True, combos)
+    # as above; a unit beyond counts as one within: two units in each weight
     assert np.abs(J - ref).max() <= 1e-6 * 1e-4 / 0.45
